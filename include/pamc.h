@@ -71,7 +71,9 @@ typedef enum { PAMC_MEM_HOST = 0, PAMC_MEM_DEVICE = 1 } pamc_mem;
  * the neighbours' spins when a spin is visited.  The integer fields, hence
  * every decision and the trajectory, are the same; the default picks PULL
  * when the average degree is at most 16 and no vertex has more than 64
- * neighbours.  PULL with at most two longer rows ("hubs") keeps the hubs'
+ * neighbours, and when all couplings have one magnitude and no vertex has
+ * more than 256 neighbours: such instances (and with the PULL flag too)
+ * sweep with their spins packed one bit each.  PULL with at most two longer rows ("hubs") keeps the hubs'
  * fields.  With neither flag, a graph whose only long rows are one or two
  * hubs keeps both forms: pamc_anneal and pamc_anneal_batch sweep with PULL
  * while the scheduled beta is below 0.8 and with PUSH after, recomputing
@@ -206,7 +208,9 @@ pamc_status pamc_reset_population(pamc_instance* inst, uint64_t seed);
  * fields computed on the matrix cores as int8 products of 16 x 64 coupling
  * blocks with the spins (n <= 1024, int8 couplings), one work-group per
  * 16-replica group of a tile while the launch has at most 128 tiles, else
- * one per tile; hubs: vertices whose fields are kept while the others are
+ * one per tile (couplings of one magnitude: tile_sweeps 1, and 2 in batches
+ * of more than 128 such tiles, sweep bit-packed instead, one launch per
+ * colour class); hubs: vertices whose fields are kept while the others are
  * gathered. */
 typedef struct {
   int32_t n, replicas, num_classes, dense, pull;

@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpamc.so")
-SOURCES = ["capi.hip", "sparse.hip", "dense.hip"]
+SOURCES = ["capi.hip", "sparse.hip", "bits.hip", "dense.hip"]
 ARCH = os.environ.get("PAMC_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

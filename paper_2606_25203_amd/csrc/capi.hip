@@ -99,7 +99,8 @@ void free_instance(pamc_instance* I) {
                   I->rs_parent, I->cl_targets, I->cl_sel, I->cl_sizes, I->tr_mstar, I->tr_beta,
                   I->tr_lnq, I->tr_events, I->tr_time, I->tr_dh, I->m3_row_ptr, I->m3_col, I->m3_w,
                   I->m3_labels, I->m3_cut, I->Jd, I->Sd, I->Sd2, I->Gd, I->Cd, I->Ed[0], I->Ed[1],
-                  I->flip_ctr, I->H_scratch, I->ptab, I->g.hubJ, I->pop.HF[0], I->pop.HF[1], I->g.Jt};
+                  I->flip_ctr, I->H_scratch, I->ptab, I->g.hubJ, I->pop.HF[0], I->pop.HF[1], I->g.Jt,
+                  I->g.brows, I->g.bent, I->btab, I->bphases};
   for (void* p : ptrs) dev_free(I, p);
   if (I->pinned) hipHostFree(I->pinned);
   for (hipEvent_t e : I->ev_pool) hipEventDestroy(e);
@@ -221,7 +222,40 @@ struct HostSparse {
   int32_t hub_tpw = 1, hub_qpw = 1, push_tpw = 1, push_qpw = 1;  // the two forms' wave shapes
   int64_t nnz = 0, W = 0, X = 0;
   std::vector<int32_t> class_ptr, to_internal, to_input, rp2, col2, J2, grow, gcol, gJ, hubJ;
+  int32_t bits_ok = 0, bits = 0, bcoup = 0, bcopies = 1, bmaxdeg = 0, bstride = 0;  // bit-packed sweeps
+  int32_t allow_bits = 1;  // set by the caller
+  std::vector<int32_t> brows, bent;
 };
+
+// Bit-packed sweeps (bits.hip) take graphs whose couplings all have one
+// magnitude and whose rows all have at most kBitsMaxDegree entries.  Returns
+// that magnitude, or 0; *both: couplings of both signs.
+int32_t one_magnitude(int32_t n, const int32_t* rp, const int32_t* J, bool* both) {
+  *both = false;
+  if (rp[n] == 0 || n > (1 << 24) || J[0] == INT32_MIN) return 0;
+  const int32_t c = std::abs(J[0]);
+  for (int32_t v = 0; v < n; ++v)
+    if (rp[v + 1] - rp[v] > pamc::kBitsMaxDegree) return 0;
+  for (int32_t e = 0; e < rp[n]; ++e) {
+    if (J[e] != c && J[e] != -c) return 0;
+    if (J[e] != J[0]) *both = true;
+  }
+  return c;
+}
+
+// Row stride of the bit-packed rows (0: rows follow each other), from the
+// longest row and the entries of all rows padded to multiples of 4.
+int32_t bits_row_stride(int64_t n, int64_t maxdeg, int64_t padded) {
+  const int64_t stride = (maxdeg + 3) & ~3;
+  return stride * n <= 3 * padded ? (int32_t)stride : 0;
+}
+
+// A shape forced from the environment means the sweep kernels it names.
+bool shape_forced() {
+  for (const char* k : {"PAMC_TILE", "PAMC_TPW", "PAMC_QPW", "PAMC_JMODE"})
+    if (getenv(k)) return true;
+  return false;
+}
 
 // Field storage of a sparse graph: gathered at visit time (pull) or kept
 // incrementally (push); both give the same integer fields and trajectory.
@@ -398,6 +432,20 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
     h.pull = 1;
     hubs.clear();
   }
+  // Couplings of one magnitude sweep bit-packed (PAMC_BITS = 0: never).
+  bool both_signs = false;
+  const char* be = getenv("PAMC_BITS");
+  if (h.allow_bits && !h.potts_K && !(flags & PAMC_FLAG_FIELDS_PUSH) && hubs.empty() && !shape_forced() &&
+      !(be && atoi(be) == 0)) {
+    const int32_t c = one_magnitude(n, rp, Jin.data(), &both_signs);
+    if (c > 0) {
+      h.bits_ok = 1;
+      h.pull = 1;
+      h.bmaxdeg = (int32_t)maxdeg;
+      h.bcopies = both_signs ? 2 : 1;
+      h.bcoup = !both_signs && Jin[0] < 0 ? -c : c;
+    }
+  }
   // Graphs whose only long rows are a few hubs (at most kMaxHubs rows of
   // more than 64 entries) keep both field forms when no form is forced: a
   // run takes gathered fields with the hubs' fields kept while its
@@ -445,6 +493,32 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
       }
     }
   }
+  // Rows of the bit-packed sweeps: the higher neighbours first (the energy
+  // sum's edges), padded to multiples of 4 with the mask that is always 0.
+  // Rows start at multiples of one stride where that costs at most three
+  // times the entries: a wave then finds its row without reading bounds.
+  if (h.bits_ok) {
+    int64_t total = 0;
+    for (int32_t iv = 0; iv < n; ++iv) total += (h.rp2[iv + 1] - h.rp2[iv] + 3) & ~3;
+    h.bstride = bits_row_stride(n, maxdeg, total);
+    h.brows.assign((size_t)h.np * 4, 0);
+    int32_t *bounds = h.brows.data(), *base = bounds + 2 * (size_t)h.np, *higher = base + h.np;
+    for (int32_t iv = 0; iv < h.np; ++iv) {
+      if (h.bstride) h.bent.resize((size_t)iv * h.bstride, 8 * h.np);
+      bounds[2 * iv] = bounds[2 * iv + 1] = (int32_t)h.bent.size();
+      if (iv >= n) continue;
+      for (int upper = 1; upper >= 0; --upper)
+        for (int32_t e = h.rp2[iv]; e < h.rp2[iv + 1]; ++e)
+          if ((h.col2[e] > iv) == (upper == 1)) {
+            h.bent.push_back(8 * (h.col2[e] + (both_signs && h.J2[e] < 0 ? h.np + 1 : 0)));
+            higher[iv] += upper;
+          }
+      while (h.bent.size() % 4) h.bent.push_back(8 * h.np);
+      bounds[2 * iv + 1] = (int32_t)h.bent.size();
+      base[iv] = 4 * (h.bmaxdeg - (h.rp2[iv + 1] - h.rp2[iv]));
+    }
+    h.bent.resize(h.bent.size() + 16 + 4 * (size_t)h.bstride, 8 * h.np);
+  }
   const bool tile_candidate = h.pull && !h.nhub && !h.potts_K && tile_fits(h.nq, X);
   if (tile_candidate) {  // a class's gathered rows are staged in LDS next to the spins
     for (int32_t c = 0; c < h.ncls; ++c)
@@ -479,13 +553,17 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
   }
   if (h.tile == 1 && !h.tile_ok) {  // the rows do not fit: per-class launches
     h.tile = 0;
-    if (!choose_fields(n, rp, flags, false, &hubs)) {  // back to the field storage it would have had
+    if (!h.bits_ok && !choose_fields(n, rp, flags, false, &hubs)) {  // back to the field storage it would have had
       h.pull = 0;
       h.grow.clear();
       h.gcol.clear();
       h.gJ.clear();
     }
   }
+  // Bit-packed sweeps leave the matrix-core tile form to lone instances and
+  // small batches, whose step it makes in one launch (PAMC_BITS = 1: not even
+  // that).
+  if (h.bits_ok) h.bits = h.tile == 2 && !(be && atoi(be) == 1) ? 2 : 1;
   // Tiles per wavefront: share the per-vertex scalar work among up to 4
   // tiles while keeping enough work-groups (one quad per wave) to fill the
   // chip.  Then quads per wave: the most (fewer partial energy sums) that
@@ -526,7 +604,7 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
 
 // Sweep shapes chosen by pamc_autotune, per instance shape (this process).
 struct TuneShape {
-  int32_t tile, tpw, qpw;
+  int32_t tile, tpw, qpw, bits;
 };
 
 std::mutex g_tune_mutex;
@@ -536,11 +614,13 @@ std::string tune_key(const pamc_instance* I) {
   return std::to_string(I->n) + "/" + std::to_string(I->nnz) + "/" + std::to_string(I->R) + "/" +
          std::to_string(I->ncls) + "/" + std::to_string(I->max_class_quads) + "/" + std::to_string(I->pull) + "/" +
          std::to_string(I->jmode) + "/" + std::to_string(I->potts_K) + "/" + std::to_string(I->nhub) + "/" +
-         std::to_string(I->tile_ok) + "/" + std::to_string(I->tmma_ok) + "/" + std::to_string(I->rule);
+         std::to_string(I->tile_ok) + "/" + std::to_string(I->tmma_ok) + "/" + std::to_string(I->rule) + "/" +
+         std::to_string(I->bits_ok);
 }
 
 void apply_shape(pamc_instance* I, const TuneShape& t) {
   I->tile = t.tile;
+  I->bits = t.bits;
   I->tpw = t.tpw;
   I->qpw = t.qpw;
   if (I->dual && !I->pull) {  // the incremental-field form's shape
@@ -586,6 +666,12 @@ pamc_status upload_sparse(pamc_instance* I, HostSparse& h) {
   I->hub_qpw = h.hub_qpw;
   I->push_tpw = h.push_tpw;
   I->push_qpw = h.push_qpw;
+  I->bits_ok = h.bits_ok;
+  I->bits = h.bits;
+  I->bcoup = h.bcoup;
+  I->bcopies = h.bcopies;
+  I->bmaxdeg = h.bmaxdeg;
+  I->bstride = h.bstride;
   I->max_class_quads = h.max_class_quads;
   I->class_ptr = std::move(h.class_ptr);
   I->to_internal = std::move(h.to_internal);
@@ -604,6 +690,11 @@ pamc_status upload_sparse(pamc_instance* I, HostSparse& h) {
   HIP_TRY(dalloc(I, &I->g.class_ptr, ncls + 1), "alloc");
   if (I->nhub) HIP_TRY(dalloc(I, &I->g.hubJ, h.hubJ.size()), "alloc");
   if (I->tmma_ok) HIP_TRY(dalloc(I, &I->g.Jt, h.Jt.size()), "alloc");
+  if (I->bits_ok) {
+    HIP_TRY(dalloc(I, &I->g.brows, h.brows.size()), "alloc");
+    HIP_TRY(dalloc(I, &I->g.bent, h.bent.size()), "alloc");
+    HIP_TRY(dalloc(I, &I->btab, 2 * (2 * (size_t)I->bmaxdeg + 2)), "alloc");
+  }
   for (int b = 0; b < 2; ++b) {
     HIP_TRY(dalloc(I, &I->pop.S[b], words), "alloc population");
     if (!I->pull) HIP_TRY(dalloc(I, &I->pop.H[b], hs), "alloc population");
@@ -619,6 +710,7 @@ pamc_status upload_sparse(pamc_instance* I, HostSparse& h) {
   HIP_TRY(dalloc(I, &I->thr, I->potts_K ? 1 : 2 * I->X + 1), "alloc");
   I->order_cap = 64;
   HIP_TRY(dalloc(I, &I->order, (size_t)I->order_cap * ncls), "alloc");
+  if (I->bits_ok) HIP_TRY(dalloc(I, &I->bphases, 4 * (size_t)I->order_cap * ncls), "alloc");
   HIP_TRY(dalloc(I, &I->rs_parent, I->R), "alloc");
   HIP_TRY(dalloc(I, &I->flip_ctr, 512), "alloc");
   HIP_TRY(hipMemsetAsync(I->flip_ctr, 0, sizeof(int64_t) * 512, I->stream), "memset");
@@ -640,6 +732,10 @@ pamc_status upload_sparse(pamc_instance* I, HostSparse& h) {
     HIP_TRY(hipMemcpyAsync(I->g.hubJ, h.hubJ.data(), sizeof(int32_t) * h.hubJ.size(), hipMemcpyHostToDevice, I->stream), "upload");
   if (I->tmma_ok)
     HIP_TRY(hipMemcpyAsync(I->g.Jt, h.Jt.data(), h.Jt.size(), hipMemcpyHostToDevice, I->stream), "upload");
+  if (I->bits_ok) {
+    HIP_TRY(hipMemcpyAsync(I->g.brows, h.brows.data(), sizeof(int32_t) * h.brows.size(), hipMemcpyHostToDevice, I->stream), "upload");
+    HIP_TRY(hipMemcpyAsync(I->g.bent, h.bent.data(), sizeof(int32_t) * h.bent.size(), hipMemcpyHostToDevice, I->stream), "upload");
+  }
   HIP_TRY(hipMemcpyAsync(I->to_internal_dev, I->to_internal.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, I->stream), "upload");
   HIP_TRY(pamc::prepare_kernel_lds(), "hipFuncSetAttribute");
   apply_cached_shape(I);
@@ -749,8 +845,17 @@ pamc_status ensure_trace(pamc_instance* I, int32_t steps) {
 pamc_status ensure_order(pamc_instance* I, int32_t sweeps) {
   if (sweeps <= I->order_cap) return PAMC_OK;
   HIP_TRY(hipStreamSynchronize(I->stream), "sync");
-  int32_t* fresh = nullptr;
+  int32_t *fresh = nullptr, *fresh_phases = nullptr;
   HIP_TRY(dalloc(I, &fresh, (size_t)sweeps * I->ncls), "alloc order");  // the old orders stay on failure
+  if (I->bits_ok) {
+    const hipError_t e = dalloc(I, &fresh_phases, 4 * (size_t)sweeps * I->ncls);
+    if (e != hipSuccess) {
+      dfree(I, fresh, (size_t)sweeps * I->ncls);
+      return dev_fail(e, "alloc order");
+    }
+    dfree(I, I->bphases, 4 * (size_t)I->order_cap * I->ncls);
+    I->bphases = fresh_phases;
+  }
   dfree(I, I->order, (size_t)I->order_cap * I->ncls);
   I->order = fresh;
   I->order_cap = sweeps;
@@ -1838,7 +1943,7 @@ pamc_status pamc_autotune(pamc_instance* I, double beta, int32_t sweeps, int32_t
     return fail(PAMC_ERR_INVALID_ARG, "bad tuning sweeps or beta");
   hipSetDevice(I->device);
   memset(out, 0, sizeof *out);
-  const TuneShape initial{I->tile, I->tpw, I->qpw};
+  const TuneShape initial{I->tile, I->tpw, I->qpw, I->bits};
   const std::string key = tune_key(I);
   if (!force) {
     std::lock_guard<std::mutex> g(g_tune_mutex);
@@ -1853,16 +1958,18 @@ pamc_status pamc_autotune(pamc_instance* I, double beta, int32_t sweeps, int32_t
     }
   }
   std::vector<TuneShape> cand;
-  if (I->tmma_ok) cand.push_back({2, initial.tpw, initial.qpw});  // matrix-core fields
+  if (I->bits_ok) cand.push_back({initial.tile, initial.tpw, initial.qpw, 1});  // bit-packed
+  // matrix-core fields (bit-packed in large batches all the same)
+  if (I->tmma_ok) cand.push_back({2, initial.tpw, initial.qpw, I->bits_ok ? 2 : 0});
   for (int tile : {0, 1}) {
     if (tile && !I->tile_ok) continue;
     if (tile) {
-      cand.push_back({1, initial.tpw, initial.qpw});  // the tile-resident sweep ignores the wave shape
+      cand.push_back({1, initial.tpw, initial.qpw, 0});  // the tile-resident sweep ignores the wave shape
       continue;
     }
     for (int tpw : {1, 2, 4}) {
       if (tpw > 1 && (!I->pull || I->potts_K || I->T % tpw)) continue;
-      for (int qpw : {1, 2, 4}) cand.push_back({0, tpw, qpw});
+      for (int qpw : {1, 2, 4}) cand.push_back({0, tpw, qpw, 0});
     }
   }
   // scratch copy of the run state and of what sweeps change
@@ -1911,7 +2018,7 @@ pamc_status pamc_autotune(pamc_instance* I, double beta, int32_t sweeps, int32_t
     }
     if (e != hipSuccess) break;
     const double per = ms / sweeps;
-    if (c.tile == initial.tile && c.tpw == initial.tpw && c.qpw == initial.qpw) dflt = per;
+    if (c.tile == initial.tile && c.tpw == initial.tpw && c.qpw == initial.qpw && c.bits == initial.bits) dflt = per;
     if (per < best) {
       best = per;
       best_shape = c;
@@ -2145,8 +2252,10 @@ double now_seconds() {
 // the largest degree + 1.  It is an upper bound of the instance's
 // device_bytes, so admission against it never overruns the budget.  The
 // threshold table has 2X + 1 entries, X = max_v sum_j |w_vj| of this graph.
+// bits: with the bit-packed sweeps' rows where the graph takes them (then no
+// field array either).
 int64_t estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pamc_config& cfg,
-                       const pamc_schedule& sc) {
+                       const pamc_schedule& sc, bool bits) {
   auto a = [](int64_t bytes) { return std::max<int64_t>(bytes, 16); };
   const int64_t R = cfg.replicas, np = (n + 3) & ~3, nnz = rp[n];
   int64_t maxdeg = 0, X = 0, gathered = 0;
@@ -2162,6 +2271,9 @@ int64_t estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pam
   bool pull = choose_fields(n, rp, cfg.flags, false, &hubs);
   const bool tile = !(cfg.flags & PAMC_FLAG_FIELDS_PUSH) && tile_fits(np / 4, X);
   const int64_t ncls = maxdeg + 1;
+  bool both;
+  bits = bits && !(cfg.flags & PAMC_FLAG_FIELDS_PUSH) && hubs.empty() && one_magnitude(n, rp, w, &both) > 0;
+  if (bits) pull = true;
   int64_t b = a(4 * (int64_t)(n + 1)) + 2 * a(4 * (nnz + 16));                 // CSR
   if (pull || tile) b += a(4 * (int64_t)(n + 1)) + 2 * a(4 * std::max<int64_t>(gathered, 4));  // gathered CSR
   if (pull && !hubs.empty()) b += a(4 * np * pamc::kMaxHubs) + 2 * a(4 * pamc::kMaxHubs * R);  // hubs
@@ -2171,6 +2283,11 @@ int64_t estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pam
   b += a(4 * (2 * X + 1));                                                     // threshold table
   b += a(4 * std::max<int64_t>(64, sc.sweeps) * ncls);                        // class orders
   b += a(4 * R) + a(8 * 512);                                                  // parents, counters
+  if (bits) {
+    const int64_t stride = bits_row_stride(n, maxdeg, gathered);
+    b += a(16 * np) + a(4 * (std::max(stride * np, gathered) + 16 + 4 * stride)) + a(8 * (2 * maxdeg + 2)) +
+         a(16 * std::max<int64_t>(64, sc.sweeps) * ncls);
+  }
   b += 4 * a(8 * (int64_t)std::max(sc.steps, 1)) + a(4 * (int64_t)std::max(sc.steps, 1)) +
        a(8 * (int64_t)std::max(sc.steps, 1));                                  // trace
   if (sc.augmented && sc.resample && sc.n_top > 0 && sc.mis_trials > 0) {    // cluster scratch
@@ -2180,12 +2297,13 @@ int64_t estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pam
   return b;
 }
 
-void server_prepare(ServerPrep& p, uint32_t flags, int32_t T) {
+void server_prepare(ServerPrep& p, uint32_t flags, int32_t T, bool bits) {
   const double t0 = now_seconds();
   pamc_status st = validate_csr(p.n, p.rp.data(), p.col.data(), p.w.data(), false);
   if (!st) {
     std::vector<int32_t> J(std::max(p.rp[p.n], 1));
     for (int32_t e = 0; e < p.rp[p.n]; ++e) J[e] = p.objective == PAMC_OBJ_MAXCUT ? -p.w[e] : p.w[e];
+    p.h.allow_bits = bits;
     st = prepare_sparse(p.h, p.n, p.rp.data(), p.col.data(), J, flags, T, false);
   }
   std::lock_guard<std::mutex> g(p.m);
@@ -2368,8 +2486,12 @@ pamc_status pamc_server_submit(pamc_server* S, int32_t n, const int32_t* row_ptr
   pamc_status st = check_schedule(&probe, sched);
   if (st) return st;
   pamc_server::Req q;
-  q.est = estimate_bytes(n, row_ptr, w ? w : row_ptr, S->cfg, *sched);
+  q.est = estimate_bytes(n, row_ptr, w ? w : row_ptr, S->cfg, *sched, false);
   if (q.est > S->budget) return fail(PAMC_ERR_OUT_OF_MEMORY, "request larger than the server's memory budget");
+  // bit-packed where that fits the budget too
+  const int64_t est_bits = estimate_bytes(n, row_ptr, w ? w : row_ptr, S->cfg, *sched, true);
+  const bool bits = est_bits <= S->budget;
+  if (bits) q.est = est_bits;
   auto prep = std::make_shared<ServerPrep>();
   prep->n = n;
   prep->objective = objective;
@@ -2383,7 +2505,7 @@ pamc_status pamc_server_submit(pamc_server* S, int32_t n, const int32_t* row_ptr
   q.t_submit = now_seconds();
   const uint32_t flags = S->cfg.flags;
   const int32_t T = S->cfg.replicas / 64;
-  S->workers->push([prep, flags, T] { server_prepare(*prep, flags, T); });
+  S->workers->push([prep, flags, T, bits] { server_prepare(*prep, flags, T, bits); });
   S->pending[q.ticket] = 0;
   *ticket = q.ticket;
   S->queue.push_back(std::move(q));

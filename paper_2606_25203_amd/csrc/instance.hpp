@@ -47,7 +47,14 @@ struct GraphDev {
   // hubs of the gathered-field mode: J between each vertex and each hub
   // [np][kMaxHubs] (0 where not adjacent)
   int32_t* hubJ = nullptr;
+  // rows of the bit-packed sweeps (see BitDesc)
+  int32_t* brows = nullptr;
+  int32_t* bent = nullptr;
 };
+
+// Longest row of a bit-packed instance: one wavefront walks a row, and the
+// threshold table (4 deg + 4 entries) is staged in LDS by every work-group.
+constexpr int32_t kBitsMaxDegree = 256;
 
 }  // namespace pamc
 
@@ -92,6 +99,15 @@ struct pamc_instance {
   double* ptab = nullptr;   // Potts weight table, 2X+1 entries
   int32_t* order = nullptr; // [order_cap][ncls]
   int32_t order_cap = 0;
+  // bit-packed sweeps: every coupling is +-|bcoup| (bits.hip)
+  int32_t bits_ok = 0;      // possible
+  int32_t bits = 0;         // taken for the sweeps: 1 always, 2 in large batches
+  int32_t bcoup = 0;        // the coupling's magnitude; negative when every coupling is
+  int32_t bcopies = 1;      // 2: couplings of both signs, masks kept with their complements
+  int32_t bmaxdeg = 0;      // the longest row
+  int32_t bstride = 0;      // > 0: rows start at multiples of it
+  uint32_t* btab = nullptr;   // threshold table and its mirror image
+  int32_t* bphases = nullptr; // [order_cap][ncls][4]: class bounds, stream index and buffer of each phase
   // resampling scratch
   int32_t* rs_parent = nullptr;
   // cluster scratch
@@ -195,6 +211,39 @@ struct Desc {
   int32_t n, np, nq, R, T, ncls, rule, pull, dense, shuffle, tr_cap, order_cap, qpw;
   int32_t sweep_stride;   // incremental-field sweeps: a tile's work-groups take chunks c, c + stride, ...
   uint32_t k0, k1;
+  // bit-packed sweeps (bits != 0): what k_thresholds fills for them
+  uint32_t* btab;
+  int32_t* bphases;
+  int32_t bits, bcoup, bmaxdeg, bpad;
+};
+
+// What the bit-packed sweep kernels read of an instance.  Masks: a group of
+// G tiles holds [copies][np + 1][G] 64-bit words in the population buffer
+// that is not current; the words after the last vertex are 0.
+struct alignas(64) BitDesc {
+  const int32_t* rows;    // [np][2]: first entry, end (multiples of 4)
+  const int32_t* base;    // [np]: table offset in bytes of a count of 0
+  const int32_t* higher;  // [np]: entries of higher vertices (the first ones of the row)
+  const int32_t* ent;     // byte offset of the neighbour's mask (copy included) in a group of one tile, padded by 16
+  const int32_t* phases;  // [order_cap][ncls][4]: class bounds (equal: idle), stream index, current buffer
+  const uint32_t* tab;    // 2 tab_half thresholds
+  const RunState* st;
+  uint32_t *S0, *S1;
+  int64_t *E0, *E1;
+  int64_t* flip_ctr;      // null unless profiling
+  uint64_t le_xor;        // Metropolis: complement of the range below (all ones or 0)
+  uint32_t le_first, le_span;  // table bytes at which x <= 0 (or, complemented, x > 0)
+  int32_t n, np, nq, T, ncls, order_cap, tab_half, copies, coupling, qpw, unpack_qpw;
+  int32_t row_stride;     // > 0: row v starts at entry v row_stride
+  uint32_t k0, k1;
+};
+
+// Where a launch's work-groups find their descriptors: through a map, or
+// (map null) all of them in `lone`.
+struct BitLaunch {
+  const uint64_t* map = nullptr;
+  const BitDesc* D = nullptr;
+  BitDesc lone{};
 };
 
 // A set of instances advanced by the same launches.  Grid kernels read a map
@@ -212,6 +261,15 @@ struct Batch {
   int64_t tile_lds[4] = {0, 0, 0, 0};  // their dynamic LDS bytes
   int32_t tmma_waves = 16;             // waves per work-group of the matrix-core form (16 or 8)
   bool tmma_groups = false;            // matrix-core form: one work-group per 16-replica group
+  // bit-packed sweeps: forms 0..2 a quad per work-group of groups of 1, 2, 4
+  // tiles, 3..5 a quad per wave (grids); instances in order of falling class count, so that
+  // the blocks of those with a class p are a prefix of the map
+  static constexpr int kBitForms = 6;
+  Launch bit_sweep[2][kBitForms], bit_pack[kBitForms], bit_unpack[kBitForms];  // sweeps per update rule
+  std::vector<int32_t> bit_grid[2][kBitForms];  // per class index: work-groups of the phase's launch
+  BitDesc* d_bits = nullptr;
+  BitDesc lone_bits;  // the descriptor of a batch of one
+  bool has_bits = false;
   Desc* d_desc = nullptr;
   int32_t n = 0;
   hipStream_t stream = nullptr;
@@ -283,6 +341,14 @@ int32_t tmma_max_n();                               // largest padded n of the m
 int64_t tmma_lds_bytes(int32_t nks, int32_t rows);                // its LDS: replica-major spins, table
 int64_t tile_lds_limit();
 hipError_t prepare_kernel_lds();
+
+// bit-packed sweeps (bits.hip)
+// Work-groups per tile group of a launch over that many quads, each taking
+// qpw (quad_per_block) or 4 qpw of them.
+int32_t bits_work_groups(int32_t quads, int32_t qpw, bool quad_per_block);
+int32_t bits_pack_chunks(int32_t nq);                  // pack and unpack work-groups per tile group
+void launch_bits_sweep(int rule, int form, const BitLaunch& b, int grid, int sweep, int phase, hipStream_t s);
+void launch_bits_pack(int form, const BitLaunch& b, int grid, bool pack, hipStream_t s);
 
 // controller pieces (sparse.hip) shared with the dense path
 hipError_t ctl_step_begin(Batch& b);

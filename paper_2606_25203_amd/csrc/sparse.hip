@@ -487,6 +487,7 @@ __global__ void __launch_bounds__(kTileWaves * 64) k_sweep_tile(const Desc* __re
 // and thresholds), so the trajectory is the same.
 // ---------------------------------------------------------------------------
 constexpr int kComputeUnits = 256;      // MI355X
+constexpr int kMfmaGroupTiles = 128;    // tiles up to which a batch takes one work-group per 16-replica group
 constexpr int64_t kCuLdsBytes = 160 * 1024;
 constexpr int kTmmaMaxN = 1024;  // vertices (padded): 64 x 1040 B of LDS spins
 constexpr int kTmmaMaxKs = kTmmaMaxN / 64;
@@ -1342,13 +1343,32 @@ __global__ void __launch_bounds__(256) k_thresholds(const Desc* __restrict__ D,
   if (!resolve(map, inst, lb)) return;
   const Desc& d = D[inst];
   const RunState* st = d.st;
-  if (!st->active) return;
-  if (commit >= 0 && lb == 0 && threadIdx.x == 0) commit_step(d, commit);
+  if (!st->active) {
+    // an instance at rest: its bit-packed phases are empty
+    if (d.bits && lb == 0)
+      for (int i = threadIdx.x; i < d.order_cap * d.ncls; i += blockDim.x)
+        reinterpret_cast<int4*>(d.bphases)[i] = make_int4(0, 0, 0, 0);
+    return;
+  }
+  if (commit >= 0 && lb == 0) {
+    if (threadIdx.x == 0) commit_step(d, commit);
+    __syncthreads();  // the phase records below name the buffer it makes current
+  }
   const int64_t Xt = st->table_x;
   const double beta = st->sweep_beta;
   if (d.potts_K) {  // e^{beta (syn_k - max syn)} for max syn - syn_k = i
     for (int64_t i = (int64_t)lb * blockDim.x + threadIdx.x; i <= Xt; i += (int64_t)kThrBlocks * blockDim.x)
       d.ptab[i] = exp_cw(beta * (double)(-i));
+  } else if (d.bits) {
+    // bit-packed sweeps: entry i of one half is T[c (i - X)], of the other
+    // T[-c (i - X)] (X the longest row, c the coupling's magnitude)
+    const int32_t half = 2 * d.bmaxdeg + 2;
+    for (int32_t i = lb * blockDim.x + threadIdx.x; i < 2 * half; i += kThrBlocks * blockDim.x) {
+      const int32_t k = i % half;
+      int64_t x = (int64_t)(k - d.bmaxdeg) * d.bcoup;
+      if (i < half) x = -x;
+      d.btab[i] = k > 2 * d.bmaxdeg ? 0u : flip_threshold(beta, d.rule, x < -Xt ? -Xt : (x > Xt ? Xt : x));
+    }
   } else {
     for (int64_t i = (int64_t)lb * blockDim.x + threadIdx.x; i <= 2 * Xt; i += (int64_t)kThrBlocks * blockDim.x)
       d.thr[i] = flip_threshold(beta, d.rule, i - Xt);
@@ -1368,7 +1388,14 @@ __global__ void __launch_bounds__(256) k_thresholds(const Desc* __restrict__ D,
           o[j] = t;
         }
       }
+      if (d.bits)  // the phases in visiting order
+        for (int k = 0; k < d.ncls; ++k)
+          reinterpret_cast<int4*>(d.bphases)[(size_t)s * d.ncls + k] =
+              make_int4(d.class_ptr[o[k]], d.class_ptr[o[k] + 1], (int32_t)(st->gs + (uint32_t)s), st->cur);
     }
+    if (d.bits)  // sweeps that other instances of a batch still make
+      for (int i = nsw * d.ncls + threadIdx.x; i < d.order_cap * d.ncls; i += blockDim.x)
+        reinterpret_cast<int4*>(d.bphases)[i] = make_int4(0, 0, 0, 0);
   }
 }
 
@@ -2320,7 +2347,53 @@ Desc make_desc(const pamc_instance* I) {
   d.order_cap = I->order_cap;
   d.k0 = (uint32_t)I->seed;
   d.k1 = (uint32_t)(I->seed >> 32);
+  d.btab = I->btab;
+  d.bphases = I->bphases;
+  d.bits = I->bits;
+  d.bcoup = I->bcoup;
+  d.bmaxdeg = I->bmaxdeg;
   return d;
+}
+
+static BitDesc make_bit_desc(const pamc_instance* I, const Desc& d, int32_t qpw, int32_t unpack_qpw) {
+  BitDesc b;
+  memset(&b, 0, sizeof b);
+  b.rows = I->g.brows;
+  b.base = I->g.brows + 2 * (size_t)I->np;
+  b.higher = I->g.brows + 3 * (size_t)I->np;
+  b.ent = I->g.bent;
+  b.phases = d.bphases;
+  b.tab = I->btab;
+  b.st = I->st;
+  b.S0 = d.S0;
+  b.S1 = d.S1;
+  b.E0 = d.E0;
+  b.E1 = d.E1;
+  b.flip_ctr = d.flip_ctr;
+  const uint32_t X4 = 4u * (uint32_t)I->bmaxdeg;  // byte offset of x = 0 in a half
+  b.tab_half = 2 * I->bmaxdeg + 2;
+  if (I->bcoup > 0) {  // x <= 0: the first half's upper part, the second half's lower part
+    b.le_first = X4;
+    b.le_span = 4u * (uint32_t)b.tab_half;
+  } else {  // the halves are exchanged: everything but x > 0
+    b.le_first = X4 + 4;
+    b.le_span = 4u * (uint32_t)b.tab_half - 8;
+    b.le_xor = ~0ull;
+  }
+  b.n = I->n;
+  b.np = I->np;
+  b.nq = I->nq;
+  b.T = I->T;
+  b.ncls = I->ncls;
+  b.order_cap = d.order_cap;
+  b.copies = I->bcopies;
+  b.coupling = I->bcoup;
+  b.qpw = qpw;
+  b.unpack_qpw = unpack_qpw;
+  b.row_stride = I->bstride;
+  b.k0 = d.k0;
+  b.k1 = d.k1;
+  return b;
 }
 
 int Batch::group_of(const pamc_instance* I) {
@@ -2359,6 +2432,18 @@ void Batch::free_device() {
     l.grid = 0;
   }
   for (int64_t& x : tile_lds) x = 0;
+  for (int f = 0; f < kBitForms; ++f) {
+    for (int r = 0; r < 2; ++r) {
+      release(bit_sweep[r][f].map);
+      bit_sweep[r][f] = Launch();
+      bit_grid[r][f].clear();
+    }
+    release(bit_pack[f].map);
+    release(bit_unpack[f].map);
+    bit_pack[f] = bit_unpack[f] = Launch();
+  }
+  release(d_bits);
+  d_bits = nullptr;
   tmma_waves = 16;
   arena_used = 0;
   if (step_graph) hipGraphExecDestroy(step_graph);
@@ -2426,7 +2511,8 @@ static int64_t field_blocks(const pamc_instance* I) {
   return std::min<int64_t>((int64_t)I->T * ((I->n + 63) / 64), kFieldBlocks);
 }
 
-hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const std::vector<Schedule>* scheds) {
+static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts, const std::vector<Schedule>* scheds,
+                              bool allow_bits) {
   // the old maps may still be read by queued kernels
   if (b.stream && b.n > 0) {
     const hipError_t e = hipStreamSynchronize(b.stream);
@@ -2439,10 +2525,23 @@ hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const
   b.stream = insts[0]->stream;
   std::vector<Desc> desc(b.n);
   const int64_t push_wgs = push_budget(insts);
+  // Small instances of the matrix-core tile form sweep bit-packed in batches
+  // of more tiles than that form spreads over 16-replica groups.
+  int64_t mfma_tiles = 0;
+  for (const pamc_instance* I : insts)
+    if (!I->dense && I->tile == 2) mfma_tiles += I->T;
+  auto sweeps_bits = [&](int i) {
+    const pamc_instance* I = insts[i];
+    return allow_bits && !I->dense && (I->bits == 1 || (I->bits == 2 && mfma_tiles > kMfmaGroupTiles));
+  };
+  bool any_bits = false;
   for (int i = 0; i < b.n; ++i) {
     desc[i] = make_desc(insts[i]);
     desc[i].sweep_stride = (int32_t)sweep_slots(insts[i], push_wgs);
+    desc[i].bits = sweeps_bits(i);
+    any_bits = any_bits || desc[i].bits;
   }
+  b.has_bits = any_bits;
   // arena mode: per-run scratch sized for each instance's schedule
   std::vector<int32_t> cl_top(b.n), cl_trials(b.n);
   for (int i = 0; i < b.n; ++i) {
@@ -2459,6 +2558,8 @@ hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const
       d.tr_cap = 0;
       d.order_cap = std::max(s.sweeps, 1);
       hipError_t e = batch_alloc(b, (void**)&d.order, sizeof(int32_t) * (size_t)d.order_cap * std::max(I->ncls, 1));
+      if (e == hipSuccess && d.bits)
+        e = batch_alloc(b, (void**)&d.bphases, 4 * sizeof(int32_t) * (size_t)d.order_cap * std::max(I->ncls, 1));
       if (e != hipSuccess) return e;
       const bool cl = s.augmented && s.resample && s.n_top > 0 && s.mis_trials > 0 && !I->potts_K && !I->dense;
       cl_top[i] = cl ? std::min(s.n_top, I->R) : 0;
@@ -2491,10 +2592,11 @@ hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const
   {
     int64_t mt = 0;
     for (int i = 0; i < b.n; ++i)
-      if (!insts[i]->dense && insts[i]->tile == 2) mt += insts[i]->T;
-    b.tmma_groups = mt <= 128;
+      if (!insts[i]->dense && insts[i]->tile == 2 && !sweeps_bits(i)) mt += insts[i]->T;
+    b.tmma_groups = mt <= kMfmaGroupTiles;
     if (const char* g = getenv("PAMC_TMMA_GROUPS")) b.tmma_groups = atoi(g) != 0;
   }
+  std::vector<int> bit_insts;
   for (int i = 0; i < b.n; ++i) {
     pamc_instance* I = insts[i];
     b.max_R = std::max(b.max_R, I->R);
@@ -2503,7 +2605,9 @@ hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const
     add_blocks(m_fields, i, field_blocks(I), false);
     add_blocks(m_thr, i, kThrBlocks, false);
     add_blocks(m_gather, i, (int64_t)I->T * ((I->nq + kGatherQuadsPerBlock - 1) / kGatherQuadsPerBlock), true);
-    if (I->tile == 2) {  // the same with matrix-core fields
+    if (sweeps_bits(i)) {
+      bit_insts.push_back(i);
+    } else if (I->tile == 2) {  // the same with matrix-core fields
       add_blocks(m_tile[3], i, (int64_t)I->T * (b.tmma_groups ? 4 : 1), false);
       b.tile_lds[3] = std::max<int64_t>(b.tile_lds[3], tmma_lds_bytes(I->nks, b.tmma_groups ? 16 : 64));
     } else if (I->tile) {  // one work-group per replica tile walks the whole step
@@ -2520,6 +2624,48 @@ hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const
       add_blocks(m_mis, i, (int64_t)nt * cl_trials[i], false);
       add_blocks(m_apply, i, (int64_t)nt * kApplyChunks, false);
       b.max_lds = std::max<int64_t>(b.max_lds, (int64_t)I->np * 5);
+    }
+  }
+  // bit-packed sweeps
+  std::vector<std::vector<uint64_t>> m_bits(2 * Batch::kBitForms), m_bpack(Batch::kBitForms),
+      m_bunpack(Batch::kBitForms);
+  std::vector<BitDesc> bdesc;
+  if (!bit_insts.empty()) {
+    bdesc.resize(b.n);
+    std::stable_sort(bit_insts.begin(), bit_insts.end(),
+                     [&](int x, int y) { return insts[x]->ncls > insts[y]->ncls; });
+    int64_t quads = 0;  // quads x tiles of a phase, over the batch
+    for (int i : bit_insts) quads += (int64_t)insts[i]->T * insts[i]->max_class_quads;
+    // Rows of at most four entries that fill the chip: a quad per wave, else
+    // a quad per work-group.  A scalar load costs a compute unit about 8
+    // cycles whatever its width, so wide tile groups pay once there are
+    // enough quads to go round.  Runs timed with groups of 1, 2 and 4 tiles:
+    // 100 x 200 torus, R = 4096 (160,000 quads x tiles a phase), 120 steps x
+    // 10 sweeps: 200, 107 and 89 ms with a quad per wave, 190 ms with a quad
+    // per work-group of 4 tiles; G(11999, degree 34), R = 512 (2,000): 37.6,
+    // 30.6 and 31.7 ms; G(5003, degree 9), R = 512: 15.2, 13.6 and 14.1 ms; 32
+    // served requests at once: 378, 287 and 248 ms.  Quads per wave on the
+    // torus: 1 90.6, 2 89.2, 3 88.5, 4 91.1, 5 92.9 ms.
+    int form = quads >= 8192 ? 5 : 1;
+    int qpw = quads >= 65536 ? 2 : 1;
+    if (const char* e = getenv("PAMC_BITS_FORM")) form = std::min(5, std::max(0, atoi(e)));
+    if (const char* e = getenv("PAMC_BITS_QPW")) qpw = std::max(1, atoi(e));
+    int uq = 4;
+    if (const char* e = getenv("PAMC_BITS_UQ")) uq = std::max(1, atoi(e));
+    for (int i : bit_insts) {
+      const pamc_instance* I = insts[i];
+      int f = form;
+      if (f >= 3 && I->bstride != 4) f -= 3;
+      while (f % 3 > 0 && I->T % (f % 3 == 2 ? 4 : 2) != 0) --f;
+      const int G = 1 << (f % 3);
+      std::vector<uint64_t>& m = m_bits[I->rule * Batch::kBitForms + f];
+      std::vector<int32_t>& grid = b.bit_grid[I->rule][f];
+      add_blocks(m, i, (int64_t)(I->T / G) * bits_work_groups(I->max_class_quads, qpw, f < 3), true);
+      if ((int)grid.size() < I->ncls) grid.resize(I->ncls);
+      for (int p = 0; p < I->ncls; ++p) grid[p] = (int32_t)m.size();
+      add_blocks(m_bpack[f], i, (int64_t)(I->T / G) * bits_pack_chunks(I->nq), true);
+      add_blocks(m_bunpack[f], i, (int64_t)(I->T / G) * bits_work_groups(I->nq, uq, f < 3), true);
+      bdesc[i] = make_bit_desc(I, desc[i], qpw, uq);
     }
   }
   // diversity samples: one work-group per replica.  A batch without
@@ -2555,6 +2701,24 @@ hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const
   if ((e = up(m_mis, b.cl_mis)) != hipSuccess) return e;
   if ((e = up(m_apply, b.cl_apply)) != hipSuccess) return e;
   if ((e = up(m_dh, b.dh)) != hipSuccess) return e;
+  // (a lone instance's launches need no maps)
+  auto up_bits = [&](std::vector<uint64_t>& m, Batch::Launch& l) -> hipError_t {
+    if (b.n > 1) return up(m, l);
+    l.grid = (int32_t)m.size();
+    return hipSuccess;
+  };
+  for (int f = 0; f < Batch::kBitForms; ++f) {
+    for (int r = 0; r < 2; ++r)
+      if ((e = up_bits(m_bits[r * Batch::kBitForms + f], b.bit_sweep[r][f])) != hipSuccess) return e;
+    if ((e = up_bits(m_bpack[f], b.bit_pack[f])) != hipSuccess) return e;
+    if ((e = up_bits(m_bunpack[f], b.bit_unpack[f])) != hipSuccess) return e;
+  }
+  if (!bdesc.empty()) b.lone_bits = bdesc[0];
+  if (!bdesc.empty() && b.n > 1) {
+    if ((e = batch_alloc(b, (void**)&b.d_bits, sizeof(BitDesc) * b.n)) != hipSuccess) return e;
+    e = hipMemcpyAsync(b.d_bits, bdesc.data(), sizeof(BitDesc) * b.n, hipMemcpyHostToDevice, b.stream);
+    if (e != hipSuccess) return e;
+  }
   for (int g = 0; g < Batch::kGroups; ++g)
     if ((e = up(m_sweep[g], b.sweep[g])) != hipSuccess) return e;
   for (int g = 0; g < 4; ++g)
@@ -2569,6 +2733,15 @@ hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const
   if (const char* w = getenv("PAMC_TMMA_WAVES")) b.tmma_waves = atoi(w) == 8 ? 8 : 16;
   // the staging vectors are local: wait for the copies before they go
   return hipStreamSynchronize(b.stream);
+}
+
+hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const std::vector<Schedule>* scheds) {
+  const hipError_t e = build_batch(b, insts, scheds, true);
+  if (e != hipErrorOutOfMemory || !b.arena || !b.has_bits) return e;
+  // the fixed scratch holds the batch without the bit-packed launches' maps:
+  // the other sweep kernels give the same results
+  b.arena_used = 0;
+  return build_batch(b, insts, scheds, false);
 }
 
 using SweepKernel = void (*)(const Desc*, const uint64_t*, int, int);
@@ -2635,8 +2808,27 @@ static hipError_t batch_sweeps(Batch& b, int32_t nsweeps, int32_t commit = -1) {
       k_sweep_tmma<16><<<b.tile[3].grid, 16 * 64, b.tile_lds[3], b.stream>>>(b.d_desc, b.tile[3].map);
     ++launches;
   }
+  int max_ncls = b.max_ncls;
+  BitLaunch bl;
+  bl.D = b.d_bits;
+  if (b.n == 1) bl.lone = b.lone_bits;
+  auto bits_map = [&](const Batch::Launch& l) -> const BitLaunch& {
+    bl.map = b.n == 1 ? nullptr : l.map;
+    return bl;
+  };
+  for (int f = 0; f < Batch::kBitForms; ++f)
+    if (b.bit_pack[f].grid) {
+      launch_bits_pack(f, bits_map(b.bit_pack[f]), b.bit_pack[f].grid, true, b.stream);
+      for (int r = 0; r < 2; ++r) max_ncls = std::max(max_ncls, (int)b.bit_grid[r][f].size());
+    }
   for (int s = 0; s < nsweeps; ++s) {
-    for (int p = 0; p < b.max_ncls; ++p) {
+    for (int p = 0; p < max_ncls; ++p) {
+      for (int r = 0; r < 2; ++r)
+        for (int f = 0; f < Batch::kBitForms; ++f) {
+          if (p >= (int)b.bit_grid[r][f].size()) continue;
+          launch_bits_sweep(r, f, bits_map(b.bit_sweep[r][f]), b.bit_grid[r][f][p], s, p, b.stream);
+          ++launches;
+        }
       for (int g = 0; g < Batch::kGroups; ++g) {
         if (!b.sweep[g].grid || p >= b.group_ncls[g]) continue;  // no instance of the group has class p
         sweep_kernel_of_group(g)<<<b.sweep[g].grid, 256, 0, b.stream>>>(b.d_desc, b.sweep[g].map, s, p);
@@ -2644,6 +2836,8 @@ static hipError_t batch_sweeps(Batch& b, int32_t nsweeps, int32_t commit = -1) {
       }
     }
   }
+  for (int f = 0; f < Batch::kBitForms; ++f)
+    if (b.bit_unpack[f].grid) launch_bits_pack(f, bits_map(b.bit_unpack[f]), b.bit_unpack[f].grid, false, b.stream);
   if (prof) {
     hipEventRecord(next_event(P), b.stream);
     P->prof_launches += launches;
