@@ -905,6 +905,7 @@ pamc_status build_dense_common(pamc_instance* I, int32_t n) {
   HIP_TRY(dalloc(I, &I->rs_parent, I->R), "alloc");
   HIP_TRY(dalloc(I, &I->flip_ctr, 512), "alloc");
   HIP_TRY(pamc::prepare_kernel_lds(), "hipFuncSetAttribute");
+  HIP_TRY(pamc::prepare_dense_lds(), "hipFuncSetAttribute");
   const size_t gsz = (size_t)pamc::dense_field_buffers() * pamc::dense_superblock_rows() * I->R;
   HIP_TRY(dalloc(I, &I->Gd, gsz), "alloc fields");
   HIP_TRY(hipMemsetAsync(I->Gd, 0, sizeof(int32_t) * gsz, I->stream), "memset");
@@ -1142,7 +1143,6 @@ pamc_status pamc_create_instance_dense_i8(int32_t n, const int8_t* J, int64_t ld
     return fail(PAMC_ERR_INVALID_ARG, "bad memory kind");
   }
   int64_t W = 0, X = 0;
-  int32_t maxabs = 0;
   for (int32_t i = 0; i < n; ++i) {
     if (src[(size_t)i * ld + i] != 0) return fail(PAMC_ERR_INVALID_ARG, "nonzero diagonal");
     int64_t ab = 0;
@@ -1150,14 +1150,13 @@ pamc_status pamc_create_instance_dense_i8(int32_t n, const int8_t* J, int64_t ld
       const int8_t v = src[(size_t)i * ld + j];
       if (v == -128) return fail(PAMC_ERR_INVALID_ARG, "entries must lie in [-127, 127]");
       if (v != src[(size_t)j * ld + i]) return fail(PAMC_ERR_INVALID_ARG, "matrix is not symmetric");
-      maxabs = std::max(maxabs, (int32_t)(v < 0 ? -v : v));
       ab += v < 0 ? -v : v;
       if (j > i) W += objective == PAMC_OBJ_MAXCUT ? v : -v;
     }
     X = std::max(X, ab);
   }
   if (2 * X >= INT32_MAX) return fail(PAMC_ERR_INVALID_ARG, "local field range exceeds int32");
-  // the dense sweep sums a block's 64 energy changes in 32 bits
+  // the dense sweep sums 16 products of a flip and twice a field in 32 bits
   if (X >= (1 << 25)) return fail(PAMC_ERR_UNSUPPORTED, "dense couplings with max_v sum_j |J_vj| >= 2^25");
   pamc_instance* I = new (std::nothrow) pamc_instance();
   if (!I) return fail(PAMC_ERR_OUT_OF_MEMORY, "host allocation");
@@ -1166,17 +1165,18 @@ pamc_status pamc_create_instance_dense_i8(int32_t n, const int8_t* J, int64_t ld
   if (!st) {
     I->W = W;
     I->X = X;
-    I->dense_j4 = maxabs <= 7;  // stored couplings are v or -v
     const size_t np = (size_t)I->dn_pad;
-    std::vector<int8_t> row(np);
-    hipError_t e = hipMemsetAsync(I->Jd, 0, np * np, I->stream);
-    for (int32_t i = 0; i < n && e == hipSuccess; ++i) {
-      std::fill(row.begin(), row.end(), 0);
-      for (int32_t j = 0; j < n; ++j) {
-        const int8_t v = src[(size_t)i * ld + j];
-        row[j] = objective == PAMC_OBJ_MAXCUT ? (int8_t)-v : v;
-      }
-      e = hipMemcpy(I->Jd + (size_t)i * np, row.data(), np, hipMemcpyHostToDevice);
+    std::vector<int8_t> rows(16 * np), frags(16 * np);
+    hipError_t e = hipSuccess;
+    for (int32_t i0 = 0; i0 < (int32_t)np && e == hipSuccess; i0 += 16) {
+      std::fill(rows.begin(), rows.end(), 0);
+      for (int32_t i = i0; i < std::min(n, i0 + 16); ++i)
+        for (int32_t j = 0; j < n; ++j) {
+          const int8_t v = src[(size_t)i * ld + j];
+          rows[(size_t)(i - i0) * np + j] = objective == PAMC_OBJ_MAXCUT ? (int8_t)-v : v;
+        }
+      pamc::dense_fragments((int32_t)np, rows.data(), frags.data());
+      e = hipMemcpy(I->Jd + (size_t)i0 * np, frags.data(), 16 * np, hipMemcpyHostToDevice);
     }
     if (e != hipSuccess) st = dev_fail(e, "upload couplings");
   }
@@ -1203,7 +1203,6 @@ pamc_status pamc_create_instance_dense_random(int32_t n, uint64_t graph_seed, co
   if (!st) st = build_dense_common(I, n);
   if (!st) {
     I->X = n - 1;
-    I->dense_j4 = 1;  // +-1 couplings
     hipError_t e = pamc::launch_dense_generate(I, graph_seed);
     int64_t W = 0;
     if (e == hipSuccess) e = hipStreamSynchronize(I->stream);

@@ -2,20 +2,24 @@
 // Ising Problem"): int8 couplings J[n][n] in HBM, spins visited in the fixed
 // order 0..n-1.
 //
+// J is stored as matrix-core A fragments of 16 rows x 64 columns, 1 KB each
+// (lane l's 16 bytes: row l % 16, columns 16 (l / 16) .. + 15), a row block's
+// fragments one after another: the field product reads it as contiguous
+// streams straight into registers.
+//
 // A sweep runs over super-blocks of kSB = 1024 consecutive spins.  For each,
 // one matrix-core launch computes the local fields of Eq. 3 of all its rows
 // against the spins as they stand, G = J[sb, :] . S (int8 x int8 -> int32,
 // exact since |h| <= 127 n < 2^31; split over the K dimension and summed
-// atomically).  A sequential pass (one work-group per 64 replicas) then
+// atomically).  A sequential pass (one work-group per 16 replicas) then
 // walks the super-block in blocks of kDB = 64 spins: the couplings to spins
-// already flipped in earlier blocks of the super-block are added with a
-// small matrix-core product over the recorded changes dS, and the block's
-// spins are decided in order with h_k = G_k + C_k + sum_{k' < k in block}
-// J_kk' d_k' (d = 2 s_new for flipped spins; packed int8 with dot4, or four
-// bits with dot8 when every coupling fits), by the same threshold test as
-// the sparse path in the form x < c (each visit's critical field c, computed
-// for the whole sweep beforehand).  The pass and the next super-block's
-// product share one launch.
+// already flipped in earlier blocks of the super-block are added with small
+// matrix-core products over the recorded changes dS, and the block's spins
+// are decided in order with h_k = G_k + C_k + sum_{k' < k in block} J_kk' d_k'
+// (d = 2 s_new for flipped spins), by the same threshold test as the sparse
+// path in the form x < c (each visit's critical field c, computed for the
+// whole sweep beforehand).  The pass and the next super-block's product share
+// one launch.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
@@ -24,6 +28,7 @@
 #include <cmath>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/pamc.h"
@@ -35,32 +40,52 @@ namespace pamc {
 namespace {
 
 constexpr int kDB = 64;          // spins per sequential block
-static_assert(kDB / 4 == 6 + 6 + 4, "the helper waves' share of the critical-field groups assumes 16 groups");
 constexpr int kSB = 1024;        // rows per super-block: one field product, one sequential launch
-constexpr int kGM = 128, kGN = 128, kGK = 64;  // field-product tile: rows x replicas x K stage
-constexpr int kLdsRow = kGK + 16;              // bytes per staged row (padded)
-constexpr int kGStages = 3;                    // field-product K stages in flight per thread
-constexpr int kThrL = 2047;      // half-width of the LDS copy of the threshold table
+constexpr int kDenseThreads = 512;             // threads of the field-product and step work-groups
+constexpr int kGM = 128;                       // rows of a field-product tile
+constexpr int kStage = 128;                    // its columns per stage: two matrix-core steps of 64
+constexpr int kLdsRow = kStage + 16;           // bytes per staged row (padded)
+constexpr int kCritThreads = 1024;             // threads of a critical-field work-group
+constexpr int kCritLds = 32768;                // its threshold entries in LDS
 constexpr int32_t kCritInf = 1 << 30;  // critical field of a visit that flips (or not) at every x
 typedef int v4i __attribute__((ext_vector_type(4)));
 
+// Byte offset of J[row][col] in the fragment layout.
+__host__ __device__ __forceinline__ size_t frag_at(int32_t np, int32_t row, int32_t col) {
+  return (((size_t)(row >> 4) * (np >> 6) + (col >> 6)) * 64 + (row & 15) + 16 * ((col & 63) >> 4)) * 16 + (col & 15);
+}
+
 // J_ij = J_ji = +-1 from the low bit of Philox(key = seed; (i, j, 0, DENSE))
 // word 0 for i < j; zero diagonal and zero padding.  Also accumulates
-// W = sum_{i<j} (-J_ij).
-__global__ void __launch_bounds__(256) k_dense_generate(int8_t* J, int32_t n, int32_t np, uint32_t k0,
-                                                        uint32_t k1, int64_t* W) {
-  const int64_t total = (int64_t)np * np;
+// W = sum_{i<j} (-J_ij).  A thread makes a lane's 16 bytes of a fragment.
+__global__ void __launch_bounds__(256) k_dense_generate(v4i* J, int32_t n, int32_t np, uint32_t k0, uint32_t k1,
+                                                        int64_t* W) {
+  const int64_t total = (int64_t)np * np / 16;
+  const int nst = np >> 6;
   int64_t wsum = 0;
   for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
        idx += (int64_t)gridDim.x * blockDim.x) {
-    const int i = (int)(idx / np), j = (int)(idx % np);
-    int8_t v = 0;
-    if (i < n && j < n && i != j) {
-      const int a = i < j ? i : j, b = i < j ? j : i;
-      v = (philox10((uint32_t)a, (uint32_t)b, 0u, kTagDense, k0, k1).a & 1u) ? 1 : -1;
-      if (i < j) wsum -= v;
+    const int lane = (int)(idx & 63);
+    const int64_t f = idx >> 6;
+    const int i = 16 * (int)(f / nst) + (lane & 15), j0 = 64 * (int)(f % nst) + 16 * (lane >> 4);
+    v4i out;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      uint32_t word = 0;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const int j = j0 + 4 * w + b;
+        int32_t v = 0;
+        if (i < n && j < n && i != j) {
+          const int lo = i < j ? i : j, hi = i < j ? j : i;
+          v = (philox10((uint32_t)lo, (uint32_t)hi, 0u, kTagDense, k0, k1).a & 1u) ? 1 : -1;
+          if (i < j) wsum -= v;
+        }
+        word |= (uint32_t)(uint8_t)(int8_t)v << (8 * b);
+      }
+      out[w] = (int32_t)word;
     }
-    J[idx] = v;
+    J[idx] = out;
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) wsum += __shfl_xor(wsum, o, 64);
@@ -94,13 +119,13 @@ __global__ void __launch_bounds__(256) k_dense_init_spins(int8_t* S, int32_t* fa
 
 // G[m][r] += sum_{k in slice p} J[row0 + m][k] S[r][k] for the super-block's
 // rows m < rows and every replica r (the K slices meet by atomic addition in
-// G, which its reader clears).  Work-group = (128-row tile, 128-replica
-// tile, K slice); each 64-column K stage of both operands is staged through
-// LDS (double-buffered, rows padded by 16 bytes against bank conflicts) and
-// the four waves (2 x 2) each compute a 64 x 64 block as 4 x 4
-// v_mfma_i32_16x16x64_i8 tiles.  Operand fragments: lane l supplies 16
-// consecutive K bytes at 16*(l/16) of row (A) / replica (B) l % 16; the
-// result holds rows 4*(l/16)..+3 of column l % 16.
+// G, which its reader clears).  Work-group = (128-row tile, NT-replica tile, K
+// slice), eight waves, v_mfma_i32_16x16x64_i8 tiles.  The couplings go from
+// memory to registers, three stages of two 64-column steps ahead; the spins,
+// which all of the tile's rows share, through LDS (three buffers, rows padded
+// by 16 bytes against bank conflicts).  Operand fragments: lane l
+// supplies 16 consecutive K bytes at 16*(l/16) of row (A) / replica (B) l %
+// 16; the result holds rows 4*(l/16)..+3 of column l % 16.
 // The product runs over a K domain given as columns kbase .. kbase + kcount
 // + xlen with the xlen columns from kbase + x0 left out (x0, xlen, kbase and
 // kcount multiples of 64): compacted column k maps to kbase + k, plus xlen
@@ -115,138 +140,166 @@ struct GemmArgs {
   int32_t kbase, kcount, x0, xlen;
 };
 
+//
+// Reading J (102 MB a super-block at n = 100,000, 22 us at a copy's rate),
+// the fragments' way through LDS (64 KB per CU for 576 cycles of products)
+// and the atomic additions bound it: with R = 256, 24 slices of 4,224 columns
+// take 50 us, 39 of them without the additions; 61 with two buffers and the
+// compiler's own order.
+template <int NT>
 struct GemmLds {
-  __attribute__((aligned(16))) int8_t As[2][kGM * kLdsRow];
-  __attribute__((aligned(16))) int8_t Bs[2][kGN * kLdsRow];
+  __attribute__((aligned(16))) int8_t Bs[3][NT * kLdsRow];
 };
 
-__device__ __forceinline__ void gemm_body(const GemmArgs g, int bid, GemmLds& L) {
-  auto& As = L.As;
-  auto& Bs = L.Bs;
-  const int8_t* __restrict__ J = g.J;
+template <int NT>
+__device__ __forceinline__ void gemm_body(const GemmArgs& g, int bid, GemmLds<NT>& L) {
+  int8_t* Bs = L.Bs[0];
   int32_t* __restrict__ G = g.G;
-  const int32_t row0 = g.row0, rows = g.rows, np = g.np, R = g.R, kslice = g.kslice;
+  const int32_t row0 = g.row0, rows = g.rows, np = g.np, R = g.R;
   if (g.use_state == 1 && !g.st->active) return;
   const int8_t* __restrict__ S = (g.use_state ? g.st->cur : 0) ? g.S1 : g.S0;
   // XCD-aware order: work-groups are dealt to the 8 XCDs round-robin, so
-  // every output tile of K slice p lands on XCD p % 8 and the slice's J
-  // columns and spins are fetched into that XCD's L2 once, not once per
-  // tile row / column
-  const int MT = (rows + kGM - 1) / kGM, NT = (R + kGN - 1) / kGN;
+  // every output tile of K slice p lands on XCD p % 8 and the slice's
+  // spins are fetched into that XCD's L2 once, not once per row tile
+  const int MT = (rows + kGM - 1) / kGM, NTs = (R + NT - 1) / NT;
   const int xcd = bid & 7, q = bid >> 3;
-  const int tile = q % (MT * NT);
-  const int p = (q / (MT * NT)) * 8 + xcd;
+  const int tile = q % (MT * NTs);
+  const int p = (q / (MT * NTs)) * 8 + xcd;
   const int mt = tile % MT, ntile = tile / MT;
-  const int k_beg = p * kslice, k_end = min(g.kcount, k_beg + kslice);
+  const int k_beg = p * g.kslice, k_end = min(g.kcount, k_beg + g.kslice);
   if (k_beg >= k_end) return;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int wm = wave & 1, wn = wave >> 1;
-  // staging: 512 chunks of 16 bytes per operand tile, chunks t and t + 256
-  // per thread; chunk c = (row c / 4, bytes 16 (c % 4) ..).  Rows past the
-  // super-block or replicas past R re-read the last valid one; their results
-  // are dropped below.
-  const v4i zero = {0, 0, 0, 0};
-  const int8_t* ag[2];
-  const int8_t* bg[2];
-  int lofs[2];
+  // waves: 4 x 2 over the tile (32 rows x NT / 2 replicas each), or 8 x 1
+  constexpr int WN = NT >= 128 ? 2 : 1, WM = 8 / WN;
+  constexpr int FM = kGM / WM / 16, FN = NT / WN / 16;  // 16 x 16 tiles per wave
+  const int wm = wave % WM, wn = wave / WM;
+  const int steps = (k_end - k_beg) / 64, nst = (steps + 1) / 2;
+  auto column = [&](int step) {  // of a step of the slice, clamped to its last
+    const int kc = k_beg + 64 * min(step, steps - 1);
+    return g.kbase + kc + (kc >= g.x0 ? g.xlen : 0);
+  };
+  // A: the wave's row blocks (past the super-block: the last one again, its
+  // results are dropped below)
+  const int8_t* ag[FM];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int c = t + 256 * i, row = c >> 2, col = (c & 3) * 16;
-    const int m = min(mt * kGM + row, rows - 1), n = min(ntile * kGN + row, R - 1);
-    ag[i] = J + (size_t)(row0 + m) * np + col;
-    bg[i] = S + (size_t)n * np + col;
-    lofs[i] = row * kLdsRow + col;
+  for (int i = 0; i < FM; ++i) {
+    const int rb = min((row0 >> 4) + mt * (kGM / 16) + wm * FM + i, ((row0 + rows) >> 4) - 1);
+    ag[i] = g.J + (size_t)rb * (np >> 6) * 1024 + lane * 16;
   }
-  // kGStages K stages in flight in registers: the loads of stage s + D are
-  // issued while stage s is multiplied, so each load has D - 1 stages of
-  // matrix-core work to arrive in; stage s + 1 goes to the other LDS buffer
-  // at the end of stage s.  In the main loop every load and store is
-  // unconditional (a prefetch past the last stage re-reads the last stage
-  // and is never used), so the compiler waits for exactly the stage it
-  // stores, not for everything in flight.
-  constexpr int D = kGStages;
-  const int nst = (k_end - k_beg) / kGK;
-  v4i ra[D][2], rb[D][2];
-  auto load_stage = [&](int slot, int stage) {
-    const int kc = k_beg + stage * kGK;  // compacted column of the stage
-    const int k = g.kbase + kc + (kc >= g.x0 ? g.xlen : 0);
+  // B: chunks of 16 bytes, chunk c = (replica c / 8, bytes 16 (c % 8) ..)
+  constexpr int PB = NT * 8 / kDenseThreads;
+  const int8_t* bg[PB];
+  int lb[PB];
+  const int half = (t & 7) >> 2;  // the step of the stage that the thread's chunks belong to
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      ra[slot][i] = *reinterpret_cast<const v4i*>(ag[i] + k);
-      rb[slot][i] = *reinterpret_cast<const v4i*>(bg[i] + k);
-    }
+  for (int i = 0; i < PB; ++i) {
+    const int row = (t >> 3) + (kDenseThreads / 8) * i;
+    bg[i] = S + (size_t)min(ntile * NT + row, R - 1) * np + 16 * (t & 3);
+    lb[i] = row * kLdsRow + 16 * (t & 7);
+  }
+  constexpr int DA = 4;  // A register slots
+  static_assert(2 * FM <= FN && 2 * PB <= FN, "a half-stage issues these loads between its FN column tiles");
+  v4i ra[DA][2][FM], rb[2][PB], bf[2][FN], acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+  auto a_at = [&](int step) { return (size_t)(column(step) >> 6) * 1024; };
+  auto b_at = [&](int stage) {
+    const int k0 = column(2 * stage), k1 = column(2 * stage + 1);
+    return half ? k1 : k0;
   };
-  auto store_stage = [&](int slot, int buf) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      *reinterpret_cast<v4i*>(As[buf] + lofs[i]) = ra[slot][i];
-      *reinterpret_cast<v4i*>(Bs[buf] + lofs[i]) = rb[slot][i];
-    }
+  auto load_a = [&](int slot, int h, int i, size_t at) { ra[slot][h][i] = *reinterpret_cast<const v4i*>(ag[i] + at); };
+  auto load_b = [&](int slot, int i, int at) { rb[slot][i] = *reinterpret_cast<const v4i*>(bg[i] + at); };
+  auto write_b = [&](int slot, int buf, int i) { *reinterpret_cast<v4i*>(Bs + buf + lb[i]) = rb[slot][i]; };
+  const int frag = (wn * FN * 16 + (lane & 15)) * kLdsRow + 16 * (lane >> 4);
+  auto read_b = [&](int h, int buf, int j) {
+    bf[h][j] = *reinterpret_cast<const v4i*>(Bs + buf + frag + j * 16 * kLdsRow + 64 * h);
   };
-  v4i acc[4][4];
+  constexpr int kBuf = NT * kLdsRow;
+  // every load is unconditional (past the last step it reads the last one
+  // again), so the compiler waits for exactly the stage it uses
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int d = 0; d < DA - 1; ++d)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = zero;
-  const int frag = (lane & 15) * kLdsRow + 16 * (lane >> 4);
-  auto multiply = [&](int buf) {
-    v4i af[4], bf[4];
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      af[i] = *reinterpret_cast<const v4i*>(As[buf] + (wm * 64 + 16 * i) * kLdsRow + frag);
-      bf[i] = *reinterpret_cast<const v4i*>(Bs[buf] + (wn * 64 + 16 * i) * kLdsRow + frag);
-    }
+      for (int i = 0; i < FM; ++i) load_a(d, h, i, a_at(2 * d + h));
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+  for (int d = 0; d < 3; ++d) {
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj)
-        acc[i][jj] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[i], bf[jj], acc[i][jj], 0, 0, 0);
-  };
+    for (int i = 0; i < PB; ++i) load_b(d & 1, i, b_at(d));
+    if (d < 2)
 #pragma unroll
-  for (int d = 0; d < D; ++d) load_stage(d, min(d, nst - 1));
-  store_stage(0, 0);
+      for (int i = 0; i < PB; ++i) write_b(d & 1, d * kBuf, i);
+  }
   __syncthreads();
-  int s0 = 0;
-  for (; s0 + D <= nst; s0 += D) {
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-      const int st_ = s0 + j;  // in LDS buffer st_ & 1; register slot j is free
-      load_stage(j, min(st_ + D, nst - 1));
-      multiply(st_ & 1);
-      store_stage((j + 1) % D, (st_ + 1) & 1);
-      __syncthreads();
+  for (int j = 0; j < FN; ++j) read_b(0, 0, j);
+  // Stage st multiplies from A slot st % 4 and the fragments read from LDS
+  // half a stage before; between its matrix-core instructions it reads the
+  // next half's fragments, loads A of stage st + 3 and B of stage st + 3 and
+  // writes B of stage st + 2 to the third buffer, whose last reads ended
+  // before the previous barrier.  The scheduling barriers keep that order.
+  int st = 0, b0 = 0, b1 = kBuf, b2 = 2 * kBuf;
+  auto stage = [&](auto J) {
+    constexpr int sl = decltype(J)::value, nx = (sl + DA - 1) % DA, bs = sl & 1;
+    const size_t at[2] = {a_at(2 * (st + DA - 1)), a_at(2 * (st + DA - 1) + 1)};
+    const int kb = b_at(st + 3);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      read_b(1, b0, j);
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ra[sl][0][i], bf[0][j], acc[i][j], 0, 0, 0);
+      if (j < 2 * FM) load_a(nx, j / FM, j % FM, at[j / FM]);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    const bool two = 2 * st + 1 < steps;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      read_b(0, b1, j);
+      if (two) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+          acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ra[sl][1][i], bf[1][j], acc[i][j], 0, 0, 0);
+      }
+      if (j < PB) write_b(bs, b2, j);
+      else if (j < 2 * PB) load_b(bs ^ 1, j - PB, kb);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const int free = b0;
+    b0 = b1;
+    b1 = b2;
+    b2 = free;
+    __syncthreads();
+    return ++st < nst;
+  };
+  while (stage(std::integral_constant<int, 0>()) && stage(std::integral_constant<int, 1>()) &&
+         stage(std::integral_constant<int, 2>()) && stage(std::integral_constant<int, 3>())) {
   }
 #pragma unroll
-  for (int j = 0; j < D; ++j) {  // the last nst % D stages
-    const int st_ = s0 + j;
-    if (st_ < nst) {
-      multiply(st_ & 1);
-      if (st_ + 1 < nst) store_stage((j + 1) % D, (st_ + 1) & 1);
-      __syncthreads();
-    }
-  }
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < FN; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int m = mt * kGM + wm * 64 + 16 * i + 4 * (lane >> 4) + e;
-        const int n = ntile * kGN + wn * 64 + 16 * j + (lane & 15);
+        const int m = mt * kGM + (wm * FM + i) * 16 + 4 * (lane >> 4) + e;
+        const int n = ntile * NT + (wn * FN + j) * 16 + (lane & 15);
         const int32_t v = acc[i][j][e];
         if (v != 0 && m < rows && n < R)
           __hip_atomic_fetch_add(&G[(size_t)m * R + n], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
 }
 
-__global__ void __launch_bounds__(256) k_dense_gemm(GemmArgs g) {
-  __shared__ GemmLds L;
-  gemm_body(g, blockIdx.x, L);
+template <int NT>
+__global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) k_dense_gemm(GemmArgs g) {
+  __shared__ GemmLds<NT> L;
+  gemm_body<NT>(g, blockIdx.x, L);
 }
 
-// Sequential visit of one super-block's spins for one 64-replica tile.
+// Sequential visit of one super-block's spins for one group of 16 replicas.
 struct SeqArgs {
   const int8_t* J;
   int8_t* S0;
@@ -255,58 +308,77 @@ struct SeqArgs {
   int64_t* E1;
   int32_t* G;   // [kSB][R] fields of the super-block rows against its starting spins
   const uint32_t* thr;
-  const v4i* C;  // [n_pad / 4][R] critical fields of the sweep (k_dense_crit)
+  const v4i* C;  // [n_pad / 4][R] negated critical fields of the sweep (k_dense_crit)
+  const int32_t* not_monotone;  // nonzero: the thresholds rise somewhere, so critical fields do not exist
   RunState* st;
   int32_t n, np, R;
-  int32_t j4;  // every coupling in [-8, 7]: the sequential pass uses four-bit dot products
   uint32_t k0, k1;
   int64_t* flip_ctr;
 };
 
-
-// Critical fields of one sweep's visits.  The thresholds T[x + Xl] (|x| <=
-// Xl) do not increase with x, so the test u < T[x + Xl] holds exactly for
-// x < c - Xl, c = the number of leading entries of T[0 .. 2Xl] above u.  The
-// stored value is c - Xl, with c = 0 stored as -2^30 and c = 2Xl + 1 as
-// +2^30, so that a field beyond the table (|x| > Xl, when the table is
-// saturated) meets the decision of the clamped lookup (|x| < 2^30 - 2^12);
-// Metropolis then raises it to 1 (x <= 0 always flips).  C[q][r] holds the
-// four spins of quad q for replica r, from the same Philox words (q, sweep,
-// r, SWEEP) as the visits.  The table lives in LDS; the search is a
-// fixed-step binary lifting over it.
+// Critical fields of one sweep's visits.  The thresholds T[x + Xt] (|x| <=
+// Xt) do not increase with x, so the test u < T[x + Xt] holds exactly for
+// x < c - Xt, c = the number of leading entries of T above u.  The stored
+// value is -(c - Xt), with c = 0 stored as +2^30 (no field flips) and c =
+// 2Xt + 1 as -2^30, so that a field beyond the table (|x| > Xt, where the
+// table is saturated) meets the decision of the clamped lookup (|x| < 2^30 -
+// 2^12); Metropolis raises c - Xt to 1 (x <= 0 always flips), and padding
+// vertices never flip.  C[q][r] holds the four spins of quad q for replica r,
+// from the same Philox words (q, sweep, r, SWEEP) as the visits.  The search
+// is a fixed-step binary lifting: over every 2^shift-th entry, held in LDS,
+// then over the entries between two of them, read through the caches (at
+// most three steps while the table has fewer than 2^18 entries).  Should the
+// table rise anywhere (a negative beta), *not_monotone is set.
 template <int RULE>
-__global__ void __launch_bounds__(256) k_dense_crit(const uint32_t* thr, const RunState* st, v4i* C,
-                                                    int32_t sweep_idx, int32_t nq, int32_t R, uint32_t k0,
-                                                    uint32_t k1) {
-  __shared__ uint32_t thr_s[2 * kThrL + 1];
+__global__ void __launch_bounds__(kCritThreads) k_dense_crit(const uint32_t* __restrict__ thr, const RunState* st,
+                                                             v4i* C, int32_t* not_monotone, int32_t sweep_idx,
+                                                             int32_t n, int32_t nq, int32_t R, uint32_t k0,
+                                                             uint32_t k1) {
+  extern __shared__ uint32_t thr_s[];
   if (!st->active) return;
-  const int32_t Xt = (int32_t)st->table_x, Xl = min(Xt, kThrL), L = 2 * Xl + 1;
+  const int32_t Xt = (int32_t)st->table_x, L = 2 * Xt + 1;
   const uint32_t gs = st->gs + (uint32_t)sweep_idx;
-  for (int i = threadIdx.x; i < L; i += blockDim.x) thr_s[i] = thr[Xt - Xl + i];
+  int shift = 0;
+  while ((L >> shift) > kCritLds) ++shift;
+  const int32_t coarse = L >> shift;  // entries (m << shift) - 1, m = 1 .. coarse
+  for (int i = threadIdx.x; i < coarse; i += blockDim.x) thr_s[i] = thr[((i + 1) << shift) - 1];
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+  bool rises = false;
+  for (int64_t i = first; i + 1 < L; i += stride) rises = rises || thr[i] < thr[i + 1];
+  if (rises) *not_monotone = 1;
+  int top = 1;
+  while (2 * top <= coarse) top *= 2;
   __syncthreads();
-  const int64_t total = (int64_t)nq * R, stride = (int64_t)gridDim.x * blockDim.x;
-  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t total = (int64_t)nq * R;
   int32_t q = (int32_t)(first / R), r = (int32_t)(first % R);
   const int32_t dq = (int32_t)(stride / R), dr = (int32_t)(stride % R);
   for (int64_t it = first; it < total; it += stride) {
     const u32x4 w = philox10((uint32_t)q, gs, (uint32_t)r, kTagSweep, k0, k1);
     int32_t pos[4] = {0, 0, 0, 0};
-    // pos + step <= 4096 - step before each step, so every read is inside
-    // the table's 2 kThrL + 1 entries (entries at or past L are never taken)
-#pragma unroll
-    for (int step = 2048; step > 0; step >>= 1)
+    for (int step = top; step > 0; step >>= 1)
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         const int32_t p = pos[kk] + step;
-        const uint32_t tv = thr_s[p - 1];
-        pos[kk] = (p <= L && tv > pick(w, kk)) ? p : pos[kk];
+        const uint32_t tv = thr_s[min(p, coarse) - 1];
+        pos[kk] = (p <= coarse && tv > pick(w, kk)) ? p : pos[kk];
       }
+    if (shift) {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) pos[kk] <<= shift;
+      for (int step = 1 << (shift - 1); step > 0; step >>= 1)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          const int32_t p = pos[kk] + step;
+          const uint32_t tv = thr[min(p, L) - 1];
+          pos[kk] = (p <= L && tv > pick(w, kk)) ? p : pos[kk];
+        }
+    }
     v4i c;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      int32_t v = pos[kk] == 0 ? -kCritInf : pos[kk] == L ? kCritInf : pos[kk] - Xl;
+      int32_t v = pos[kk] == 0 ? -kCritInf : pos[kk] == L ? kCritInf : pos[kk] - Xt;
       if (RULE == 1) v = max(v, 1);
-      c[kk] = v;
+      c[kk] = 4 * q + kk < n ? -v : kCritInf;
     }
     C[it] = c;
     q += dq;
@@ -318,571 +390,407 @@ __global__ void __launch_bounds__(256) k_dense_crit(const uint32_t* thr, const R
   }
 }
 
-// One pass over the 64 spins of one block for one replica per lane (wave 0):
-// h_k = gsum_k + sum_{k' < k in block} J_kk' d_k' (d = 2 s_new of flipped
-// spins, packed int8, dot4), x = s h, flip iff x < cc (the visit's critical
-// field, from LDS); every spin of the block is below n.  sw: the block's 16
-// starting spin words; d: the block's d words.  With WIDE the pass also
-// returns whether any lane met |x| > Xl (needed only when the LDS table is
-// narrower than the full one).  The sign is applied as a mask, m = 0 or -1:
-// x < cc is (h ^ m) < cc + m, since h ^ -1 = -h - 1.  The pass has no
-// branches, so the compiler can move the independent work (the couplings to
-// earlier groups, LDS reads) into the latency of the decision chain, which
-// per spin is dot4, xor, compare, select.
-template <int RULE, bool WIDE>
-__device__ __forceinline__ bool decide_pass(const uint32_t (*jd)[kDB / 4], const int32_t (*gsum)[64],
-                                            const v4i (*crit)[64], int32_t Xl, const uint32_t (&sw)[kDB / 4],
-                                            int lane, uint32_t (&d)[kDB / 4], int32_t& dE32, int32_t& nflip) {
-  uint32_t wide = 0;
-  int32_t xsum = 0, nf = 0;
-#pragma unroll
-  for (int g = 0; g < kDB / 4; ++g) d[g] = 0;
-#pragma unroll
-  for (int g = 0; g < kDB / 4; ++g) {
-    const v4i cc = crit[g][lane];
-    // couplings to the flips of the earlier groups of the block: four
-    // independent accumulations, in group order, so only the last one
-    // (the previous group's flips) waits for the decision chain
-    int32_t base[4];
-    uint32_t jg[4];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int k = 4 * g + kk;
-      int32_t p = gsum[k][lane];
-#pragma unroll
-      for (int g2 = 0; g2 < g; ++g2) p = __builtin_amdgcn_sdot4((int)jd[k][g2], (int)d[g2], p, false);
-      base[kk] = p;
-      jg[kk] = jd[k][g];
-    }
-    const uint32_t w = sw[g];
-    // the d byte of a flip, -2 s: 0xFE for s = +1 (0x01), 0x02 for s = -1 (0xFF)
-    const uint32_t bw = 0xFEFEFEFEu ^ (((w >> 7) & 0x01010101u) * 0xFCu);
-    uint32_t dg = 0;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      // m = -1 for s = -1 (its own spin has not changed yet), else 0
-      const int32_t m = (int32_t)(w << (24 - 8 * kk)) >> 31;
-      const int32_t h = __builtin_amdgcn_sdot4((int)jg[kk], (int)dg, base[kk], false);
-      const int32_t y = h ^ m;  // x = y - m
-      if (WIDE) wide |= (uint32_t)(h + Xl) > (uint32_t)(2 * Xl);
-      const bool flip = y < cc[kk] + m;
-      dg = flip ? dg | (bw & (0xFFu << (8 * kk))) : dg;
-      xsum += flip ? y : 0;
-    }
-    d[g] = dg;
-  }
-  // a flipped byte is 0xFE (s = +1) or 0x02 (s = -1): bit 1 counts the
-  // flips, bit 2 those of s = +1; sum x = sum y + the flips of s = -1
-  int32_t npos = 0;
-#pragma unroll
-  for (int g = 0; g < kDB / 4; ++g) {
-    nf += __builtin_popcount(d[g] & 0x02020202u);
-    npos += __builtin_popcount(d[g] & 0x04040404u);
-  }
-  dE32 += xsum + (nf - npos);
-  nflip += nf;
-  return wide != 0;
-}
-
-// The same pass for couplings in [-8, 7], four bits each.  jd8 packs a
-// row's couplings to eight spins of the block per word and the flips are
-// kept in the same layout -- of the eight spins 8G + j, nibble 2j holds
-// spin j < 4 and nibble 2 (j - 4) + 1 spin j >= 4 -- so that one dot8 covers
-// eight couplings; a flip is the nibble 0xE (s = +1) or 0x2 (s = -1).  The
-// d words go out as bytes, unpacked at the end.
-template <int RULE, bool WIDE>
-__device__ __forceinline__ bool decide_pass8(const uint32_t (*jd8)[kDB / 8], const int32_t (*gsum)[64],
-                                             const v4i (*crit)[64], int32_t Xl, const uint32_t (&sw)[kDB / 4],
-                                             int lane, uint32_t (&d)[kDB / 4], int32_t& dE32, int32_t& nflip) {
-  uint32_t wide = 0, d8[kDB / 8];
-  int32_t xsum = 0, nf = 0, npos = 0;
-#pragma unroll
-  for (int G = 0; G < kDB / 8; ++G) d8[G] = 0;
-#pragma unroll
-  for (int G = 0; G < kDB / 8; ++G) {
-    const v4i cc0 = crit[2 * G][lane], cc1 = crit[2 * G + 1][lane];
-    int32_t base[8];
-    uint32_t jg[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int k = 8 * G + j;
-      int32_t p = gsum[k][lane];
-#pragma unroll
-      for (int G2 = 0; G2 < G; ++G2) p = __builtin_amdgcn_sdot8((int)jd8[k][G2], (int)d8[G2], p, false);
-      base[j] = p;
-      jg[j] = jd8[k][G];
-    }
-    const uint32_t w0 = sw[2 * G], w1 = sw[2 * G + 1];
-    // the flip nibbles, 0xE, or 0x2 where the spin is -1
-    const uint32_t negn = ((w0 >> 7) & 0x01010101u) | ((w1 >> 3) & 0x10101010u);
-    const uint32_t bw = 0xEEEEEEEEu ^ (negn * 0xCu);
-    uint32_t dg = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int jb = j & 3, sh = j < 4 ? 8 * jb : 8 * jb + 4;
-      const int32_t m = (int32_t)((j < 4 ? w0 : w1) << (24 - 8 * jb)) >> 31;
-      const int32_t h = __builtin_amdgcn_sdot8((int)jg[j], (int)dg, base[j], false);
-      const int32_t y = h ^ m;  // x = y - m
-      if (WIDE) wide |= (uint32_t)(h + Xl) > (uint32_t)(2 * Xl);
-      const bool flip = y < (j < 4 ? cc0[jb] : cc1[jb]) + m;
-      dg = flip ? dg | (bw & (0xFu << sh)) : dg;
-      xsum += flip ? y : 0;
-    }
-    d8[G] = dg;
-  }
-#pragma unroll
-  for (int G = 0; G < kDB / 8; ++G) {
-    // bit 1 of a flip nibble counts the flips, bit 2 those of s = +1
-    nf += __builtin_popcount(d8[G] & 0x22222222u);
-    npos += __builtin_popcount(d8[G] & 0x44444444u);
-    // nibbles 0, 2, 4, 6 are spins 0..3, nibbles 1, 3, 5, 7 spins 4..7;
-    // 0x0E becomes the byte 0xFE
-    const uint32_t lo = d8[G] & 0x0F0F0F0Fu, hi = (d8[G] >> 4) & 0x0F0F0F0Fu;
-    d[2 * G] = lo | ((lo & 0x08080808u) * 0x1Eu);
-    d[2 * G + 1] = hi | ((hi & 0x08080808u) * 0x1Eu);
-  }
-  dE32 += xsum + (nf - npos);
-  nflip += nf;
-  return wide != 0;
-}
-
-struct BlockTally {
-  int32_t dE32, nflip;
-};
-
-// The same decisions with every threshold exact (fields beyond the LDS
-// table recomputed by the function that fills it), from the block's
-// starting spin words sw0 (LDS); the d words go to dout (LDS).  Out of line
-// and unoptimised for speed: only reached when a lane met |x| > Xl.
-template <int RULE>
-__device__ __noinline__ BlockTally decide_block_exact(const uint32_t (*jd)[kDB / 4], const int32_t (*gsum)[64],
-                                                      const uint32_t* thr_s, double beta, int32_t Xl, int32_t Xt,
-                                                      const uint32_t* sw0, uint32_t* dout, int rb0, int n,
-                                                      uint32_t gs, uint32_t r, uint32_t k0, uint32_t k1, int lane) {
-  BlockTally t = {0, 0};
-  for (int g = 0; g < kDB / 4; ++g) {
-    const int vq = rb0 + 4 * g;
-    const u32x4 rnd = philox10((uint32_t)(vq >> 2), gs, r, kTagSweep, k0, k1);
-    uint32_t w = sw0[g], dg = 0;
-    for (int kk = 0; kk < 4; ++kk) {
-      const int k = 4 * g + kk;
-      int32_t h = gsum[k][lane];
-      for (int g2 = 0; g2 < g; ++g2) h = __builtin_amdgcn_sdot4((int)jd[k][g2], (int)dout[g2], h, false);
-      h = __builtin_amdgcn_sdot4((int)jd[k][g], (int)dg, h, false);
-      const int32_t sm = -(int32_t)((w >> (8 * kk + 7)) & 1u);
-      const int32_t x = (h ^ sm) - sm;
-      const int32_t xl = min(max(x, -Xl), Xl);
-      const uint32_t thr = x == xl ? thr_s[xl + Xl] : flip_threshold(beta, RULE, min(max(x, -Xt), Xt));
-      const uint32_t u = kk == 0 ? rnd.a : kk == 1 ? rnd.b : kk == 2 ? rnd.c : rnd.d;
-      bool flip = u < thr;
-      if (RULE == 1) flip = flip || x <= 0;
-      flip = flip && vq + kk < n;
-      if (flip) {
-        t.dE32 += x;
-        w ^= 0xFEu << (8 * kk);
-        dg |= (uint32_t)(uint8_t)(int8_t)(sm == 0 ? -2 : 2) << (8 * kk);
-        t.nflip += 1;
-      }
-    }
-    dout[g] = dg;
-  }
-  return t;
-}
-
-// Decides the 64 spins of one block; d words into dout (LDS).  The critical
-// fields cover |x| <= Xl; when the LDS table is narrower than the full one
-// (Xl < Xt) and some lane met a field beyond it, the block is decided
-// again, exactly, from its starting spins (one uniform branch per block
-// keeps the common pass free of control flow).  The last block of the
-// matrix, which holds spins at or beyond n, takes the exact path directly,
-// and so does every block when the table is not monotone (all_exact).
-template <int RULE, bool WIDE, bool J4>
-__device__ __forceinline__ void decide_block(const uint32_t (*jd)[kDB / 4], const uint32_t (*jd8)[kDB / 8],
-                                             const int32_t (*gsum)[64],
-                                             const v4i (*crit)[64], const uint32_t* thr_s, double beta,
-                                             int32_t Xl, int32_t Xt, bool all_exact, const uint32_t* sw0,
-                                             uint32_t* dout, int rb0, int n, uint32_t gs, uint32_t r, uint32_t k0,
-                                             uint32_t k1, int lane, int64_t& dE, int32_t& nflip) {
-  int32_t dE32 = 0, nf = 0;  // |dE32| <= 64 X < 2^31 (X < 2^25)
-  bool exact = all_exact || rb0 + kDB > n;
-  if (!exact) {
-    uint32_t sw[kDB / 4], d[kDB / 4];
-#pragma unroll
-    for (int g = 0; g < kDB / 4; ++g) sw[g] = sw0[g];
-    const bool wide = J4 ? decide_pass8<RULE, WIDE>(jd8, gsum, crit, Xl, sw, lane, d, dE32, nf)
-                         : decide_pass<RULE, WIDE>(jd, gsum, crit, Xl, sw, lane, d, dE32, nf);
-    exact = WIDE && __builtin_amdgcn_ballot_w64(wide) != 0;
-    if (!exact) {
-#pragma unroll
-      for (int g = 0; g < kDB / 4; ++g) dout[g] = d[g];
-    }
-  }
-  if (exact) {
-    const BlockTally t = decide_block_exact<RULE>(jd, gsum, thr_s, beta, Xl, Xt, sw0, dout, rb0, n, gs, r, k0, k1,
-                                                  lane);
-    dE32 = t.dE32;
-    nf = t.nflip;
-  }
-  dE += 2 * (int64_t)dE32;
-  nflip += nf;
-}
-
-// One work-group per tile walks the super-block's 64-spin blocks in order,
-// pipelined: while wave 0 decides block b (and writes its replica's new spin
-// words back), waves 1-3 prepare block b + 1 -- its fields G (taken from the
-// field product, which is cleared for the next super-block), plus the
-// couplings to the spins flipped in blocks 0..b-1 of the super-block, C =
-// J[blk b+1, blocks 0..b-1] . dS (matrix cores; the spin changes dS of the
-// super-block are kept in LDS, replica-major), its diagonal block of J and
-// its critical fields.  After wave 0 is done, the four waves add block b's
-// own contribution to block b + 1 (one 64-column matrix-core step, its J
-// fragments loaded before the decisions).
+// LDS of the sequential pass; buffers are taken in turn by the block's
+// number.  Fragments are those of v_mfma_i32_16x16x64_i8, [strip of 16
+// rows][lane].
 struct SeqLds {
-  uint32_t jd[2][kDB][kDB / 4];   // J[rb0 + k][rb0 + 4g .. 4g+3], packed int8
-  uint32_t jd8[2][kDB][kDB / 8];  // the same, eight four-bit couplings per word (order of decide_pass8)
-  int32_t gsum[2][kDB][64];       // fields of this tile before the block's own flips
-  uint32_t thr_s[2 * kThrL + 1];  // thresholds for |x| <= Xl
-  __attribute__((aligned(16))) int8_t dsl[64][kSB + 16];  // spin changes d, [replica][row - row0]
-  uint32_t swl[2][64][kDB / 4 + 1];                       // the block's spin words, [replica][word]
-  int32_t part[16][64];  // wave 2's part of strip 3, fragment rows x replicas
-  __attribute__((aligned(16))) v4i crit[kDB / 4][64];     // the block's critical fields, [group][replica]
+  v4i field[2][4][64];  // fields of the block from everything but the block before it and itself
+  v4i h0[2][4][64];     // fields at the block's start
+  v4i ain[4][4][64];    // J of the block against itself, columns permuted (see seq_body)
+  v4i anx[3][4][64];    // J of the block against the block before it, columns permuted
+  v4i crit[3][4][64];   // negated critical fields
+  v4i sw[4][64];        // spin words, one per strip
+  v4i jin[3][4][4][2];  // [strip][lane / 16]: twice J within a lane's four spins, pairs 10, 20, 21, 30, 31, 32
+  __attribute__((aligned(16))) int8_t dsl[16][kSB + 16];  // spin changes d, [replica][row - row0]
+  __attribute__((aligned(16))) int8_t spl[16][kSB + 16];  // the super-block before's spins, final
 };
 
 // Barrier for work-groups whose waves exchange data through LDS only: the
 // waves' LDS writes complete before it, and their global loads and stores
-// in flight stay in flight (a full __syncthreads would wait for those too,
-// e.g. for the deciding wave's spin write-back).
+// in flight stay in flight (a full __syncthreads would wait for those too).
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int RULE, bool WIDE, bool J4>
-__device__ __forceinline__ void seq_body(const SeqArgs a, int tile, int32_t sweep_idx, int32_t row0, int32_t rows,
+// One work-group per 16 replicas walks the super-block's 64-spin blocks in
+// order.  Wave 0 decides block b from registers while the others prepare
+// block b + 1 and finish block b - 1; one LDS barrier per block.
+//
+// The deciding wave.  Its lane l = 16 g + c keeps, for replica c, the fields
+// of spins 16 s + 4 g + j (strip s, j < 4) where the matrix cores leave them:
+// element j of accumulator s.  Groups of four spins are decided in order (s,
+// then g): every lane decides its four spins, one after another, with the
+// couplings inside the four (dot4), and the lanes whose turn it is keep the
+// result, one word d (bytes 0, 2 or -2).  A product J . d then brings the
+// change to the fields of the spins to come.  The order of its K dimension is
+// free: lane group g supplies K bytes 16 g .. 16 g + 15, and as byte 4 s + j
+// of them it supplies spin 16 s + 4 g + j, so its operand is the four words
+// it decided itself and no data moves between lanes; the couplings are stored
+// with their columns in that order (ain, anx).
+//
+// Decision: with m = 0 or -1 for s = +1 or -1, s h < c is (h ^ m) < c + m (h ^
+// -1 = -h - 1), i.e. the sign of t = (h ^ m) - (c + m).  Inside the four, a
+// flip of j' (f = t >> 31 = -1) adds f times 2 s_j s_j' J_jj' to t_j, products
+// taken beforehand, so the chain per spin is one multiply-add and one shift
+// (a dot4 instead costs three wait states more).  That chain bounds a block:
+// 16 groups of four, each eight dependent operations and a matrix-core
+// product whose result the next group waits for, 1.8 us a block and 29 us a
+// super-block of 1,024 spins.  One work-group per 64 replicas with the
+// couplings applied by dot products took 5.6 us a block, and 24 where the
+// threshold table outgrew LDS.
+//
+// Energy: flips change it by -d.h, summed over the block as -d.(h0 + J d /
+// 2) by another wave, from the fields h0 at the block's start.
+template <int RULE, bool EXACT>
+__device__ __forceinline__ void seq_body(const SeqArgs& a, int group, int32_t sweep_idx, int32_t row0, int32_t rows,
                                          SeqLds& L) {
-  auto& jd = L.jd;
-  auto& jd8 = L.jd8;
-  auto& gsum = L.gsum;
-  auto& thr_s = L.thr_s;
-  auto& dsl = L.dsl;
-  auto& swl = L.swl;
-  auto& crit = L.crit;
-  auto& part = L.part;
   RunState* st = a.st;
   if (!st->active) return;
   const int cur = st->cur;
   int8_t* S = cur ? a.S1 : a.S0;
-  int64_t* E = cur ? a.E1 : a.E0;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int r = tile * 64 + lane;
-  const uint32_t gs = st->gs + (uint32_t)sweep_idx;
-  const int32_t Xt = (int32_t)st->table_x;
-  const double beta = st->sweep_beta;
-  // The central part of the table lives in LDS, for the exact path (which
-  // recomputes it for |x| > Xl) and the monotonicity check below.
-  const int32_t Xl = min(Xt, kThrL);
-  for (int i = threadIdx.x; i <= 2 * Xl; i += blockDim.x) thr_s[i] = a.thr[Xt - Xl + i];
+  const int c = lane & 15, g = lane >> 4;
+  const int r = group * 16 + c;
   const int nb = min(rows, a.n - row0 + kDB - 1) / kDB;  // blocks holding real spins
-  // fields of block bb (rows row0 + 64 bb ..) from G, cleared behind for
-  // the next super-block's product; the diagonal J block
-  auto load_fields = [&](int bb, int buf) {
-    for (int i = threadIdx.x; i < kDB * 64; i += blockDim.x) {
-      const int k = i >> 6, c = i & 63;
-      int32_t* gp = a.G + (size_t)(bb * kDB + k) * a.R + tile * 64 + c;
-      gsum[buf][k][c] = *gp;
-      *gp = 0;
-    }
-  };
-  // words 2 gp and 2 gp + 1 of row k of the diagonal J block, in bytes and
-  // in four-bit couplings (nibble 2 b from the first word's byte b, nibble
-  // 2 b + 1 from the second's)
-  auto put_jd = [&](int buf, int k, int gp, uint32_t lo, uint32_t hi) {
-    jd[buf][k][2 * gp] = lo;
-    jd[buf][k][2 * gp + 1] = hi;
-    jd8[buf][k][gp] = (lo & 0x0F0F0F0Fu) | ((hi & 0x0F0F0F0Fu) << 4);
-  };
-  auto load_diag = [&](int bb, int buf, int t, int nt) {
-    const int rb0 = row0 + bb * kDB;
-    for (int i = t; i < kDB * kDB / 8; i += nt) {
-      const int k = i / (kDB / 8), gp = i % (kDB / 8);
-      const uint2 w = *reinterpret_cast<const uint2*>(a.J + (size_t)(rb0 + k) * a.np + rb0 + 8 * gp);
-      put_jd(buf, k, gp, w.x, w.y);
-    }
-    for (int i = t; i < kDB * kDB / 4; i += nt) {
-      const int k = i / (kDB / 4), g = i % (kDB / 4);
-      // the block's spin words of the tile (replica k, word g)
-      swl[buf][k][g] = *reinterpret_cast<const uint32_t*>(S + (size_t)(tile * 64 + k) * a.np + rb0 + 4 * g);
-    }
-  };
-  // the diagonal block of bb into registers (lane t of wave 3) and from
-  // there into LDS
-  constexpr int kDiagPer = kDB * kDB / 4 / 64;  // spin words per thread of wave 3
-  constexpr int kPairPer = kDB * kDB / 8 / 64;  // J word pairs per thread of wave 3
-  auto fetch_diag = [&](int bb, int t, uint2 (&dj)[kPairPer], uint32_t (&dsw)[kDiagPer]) {
-    const int rb0 = row0 + bb * kDB;
-#pragma unroll
-    for (int it = 0; it < kPairPer; ++it) {
-      const int i = t + 64 * it, k = i / (kDB / 8), gp = i % (kDB / 8);
-      dj[it] = *reinterpret_cast<const uint2*>(a.J + (size_t)(rb0 + k) * a.np + rb0 + 8 * gp);
-    }
-#pragma unroll
-    for (int it = 0; it < kDiagPer; ++it) {
-      const int i = t + 64 * it, k = i / (kDB / 4), g = i % (kDB / 4);
-      dsw[it] = *reinterpret_cast<const uint32_t*>(S + (size_t)(tile * 64 + k) * a.np + rb0 + 4 * g);
-    }
-  };
-  auto put_diag = [&](int buf, int t, const uint2 (&dj)[kPairPer], const uint32_t (&dsw)[kDiagPer]) {
-#pragma unroll
-    for (int it = 0; it < kPairPer; ++it) {
-      const int i = t + 64 * it;
-      put_jd(buf, i / (kDB / 8), i % (kDB / 8), dj[it].x, dj[it].y);
-    }
-#pragma unroll
-    for (int it = 0; it < kDiagPer; ++it) {
-      const int i = t + 64 * it, k = i / (kDB / 4), g = i % (kDB / 4);
-      swl[buf][k][g] = dsw[it];
-    }
-  };
-  // the 16-row strip sr of block bb against the column steps kbeg .. kend
-  // of the super-block (64 columns each): its J fragments (step kbeg + i in
-  // av[i]), and its fields from G (fragment layout: row 4 (lane / 16) + j
-  // of the strip, replica 16 nt + lane % 16)
-  auto load_frags = [&](int bb, int sr, int kbeg, int kend, auto& av) {
-    constexpr int N = sizeof(av) / sizeof(av[0]);
-    const int8_t* arow = a.J + (size_t)(row0 + bb * kDB + 16 * sr + (lane & 15)) * a.np + row0 + 16 * (lane >> 4);
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-      av[i] = kbeg + i < kend ? *reinterpret_cast<const v4i*>(arow + 64 * (kbeg + i)) : v4i{0, 0, 0, 0};
-  };
-  auto load_g = [&](int bb, int sr, int32_t (&gv)[16]) {
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        gv[4 * nt + j] = a.G[(size_t)(bb * kDB + 16 * sr + 4 * (lane >> 4) + j) * a.R + tile * 64 + nt * 16 +
-                             (lane & 15)];
-  };
-  // acc += J[strip rows][steps kbeg .. kend) . dsl[:, those columns] on
-  // the matrix cores
-  auto strip_product = [&](int kbeg, int kend, const auto& av, v4i (&acc)[4]) {
-    constexpr int N = sizeof(av) / sizeof(av[0]);
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      if (kbeg + i < kend) {
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-          const v4i bv =
-              *reinterpret_cast<const v4i*>(&dsl[nt * 16 + (lane & 15)][64 * (kbeg + i) + 16 * (lane >> 4)]);
-          acc[nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[i], bv, acc[nt], 0, 0, 0);
-        }
-      }
-    }
-  };
-  // result fragment of strip sr into gsum[buf]: with G, the fields gv
-  // taken from the field product plus the product (G is cleared behind for
-  // the next super-block's product), else added to gsum
-  auto add_strip = [&](int bb, int buf, int sr, const v4i (&acc)[4], const int32_t* gv) {
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int k = 16 * sr + 4 * (lane >> 4) + j, c = nt * 16 + (lane & 15);
-        if (gv) {
-          gsum[buf][k][c] = gv[4 * nt + j] + acc[nt][j];
-          a.G[(size_t)(bb * kDB + k) * a.R + tile * 64 + c] = 0;
-        } else {
-          gsum[buf][k][c] += acc[nt][j];
-        }
-      }
-  };
-  // critical fields of block bb, group g (four spins), this lane's replica
-  auto crit_group = [&](int bb, int g) { return a.C[(size_t)(((row0 + bb * kDB) >> 2) + g) * a.R + r]; };
-  if (nb > 0) {
-    load_fields(0, 0);
-    load_diag(0, 0, threadIdx.x, blockDim.x);
-    for (int g = wave; g < kDB / 4; g += 4) crit[g][lane] = crit_group(0, g);
-  }
-  __syncthreads();
-  // the critical fields assume thresholds that do not increase with x;
-  // should the table ever break that, every block takes the exact path
-  bool mono = true;
-  for (int i = threadIdx.x; i < 2 * Xl; i += blockDim.x) mono = mono && thr_s[i] >= thr_s[i + 1];
-  const bool all_exact = !__syncthreads_and(mono);
-  int64_t dE = 0;
-  int32_t nflip = 0;
   const v4i zero = {0, 0, 0, 0};
-  for (int b = 0; b < nb; ++b) {
-    const int cb = b & 1;
-    const int rb0 = row0 + b * kDB;
-    const bool next = b + 1 < nb;
-    // J fragment of block b+1, strip `wave`, against block b's columns
-    v4i a_next = zero;
-    if (next)
-      a_next = *reinterpret_cast<const v4i*>(a.J + (size_t)(rb0 + kDB + 16 * wave + (lane & 15)) * a.np + rb0 +
-                                             16 * (lane >> 4));
-    // waves 1..3: the critical fields of block b+1 (held in registers
-    // until wave 0 is done with block b's); wave 3, which also takes the
-    // diagonal block, loads 4 of the 16 groups, waves 1 and 2 six each
-    constexpr int kCritPerHelper = 6;
-    const int crit_g0 = wave == 1 ? 0 : wave == 2 ? 6 : 12;
-    const int crit_cnt = wave == 3 ? 4 : 6;
-    v4i crit_next[kCritPerHelper];
-    if (wave == 0) {
-      // the d words go to the super-block's spin changes (dsl)
-      decide_block<RULE, WIDE, J4>(jd[cb], jd8[cb], gsum[cb], crit, thr_s, beta, Xl, Xt, all_exact, swl[cb][lane],
-                                   reinterpret_cast<uint32_t*>(&dsl[lane][b * kDB]), rb0, a.n, gs, (uint32_t)r,
-                                   a.k0, a.k1, lane, dE, nflip);
-      // the lane's new spin words of the block go straight back: a byte of
-      // d is 0 (no flip), 2 or -2, and a flip turns 0x01 <-> 0xFF, i.e. xor
-      // 0xFE
-      {
-        const uint32_t* dw = reinterpret_cast<const uint32_t*>(&dsl[lane][b * kDB]);
-        const uint32_t* sw = swl[cb][lane];
-        uint4* dst = reinterpret_cast<uint4*>(S + (size_t)r * a.np + rb0);
+  if (nb <= 0) return;
+  // fragment (row block, step) of the super-block's rows and any columns
+  auto frag = [&](int row, int col) {
+    return a.J + ((size_t)((row0 + row) >> 4) * (a.np >> 6) + (col >> 6)) * 1024;
+  };
+  auto word = [&](const int8_t* p) { return *reinterpret_cast<const int32_t*>(p); };
+  // The passes over blocks -1, 0, 1, .. between barriers: what block b + 1
+  // needs last (its fields) is made while block b is decided, everything else
+  // one block earlier.
+  if (wave == 0) {
+    __builtin_amdgcn_s_setprio(3);
+    const uint32_t gs = st->gs + (uint32_t)sweep_idx;
+    const int32_t Xt = (int32_t)st->table_x;
+    struct Inputs {
+      v4i ain[4], anx[4], ncc[4], jin[4][2], sw;
+    };
+    auto fetch = [&](int b, Inputs& x) {
 #pragma unroll
-        for (int q = 0; q < kDB / 16; ++q) {
-          uint4 v;
-          v.x = sw[4 * q] ^ ((dw[4 * q] & 0x02020202u) * 0x7Fu);
-          v.y = sw[4 * q + 1] ^ ((dw[4 * q + 1] & 0x02020202u) * 0x7Fu);
-          v.z = sw[4 * q + 2] ^ ((dw[4 * q + 2] & 0x02020202u) * 0x7Fu);
-          v.w = sw[4 * q + 3] ^ ((dw[4 * q + 3] & 0x02020202u) * 0x7Fu);
-          dst[q] = v;
-        }
+      for (int s = 0; s < 4; ++s) {
+        x.ain[s] = L.ain[b & 3][s][lane];
+        x.ncc[s] = L.crit[b % 3][s][lane];
+        x.jin[s][0] = L.jin[b % 3][s][g][0];
+        x.jin[s][1] = L.jin[b % 3][s][g][1];
+        if (b > 0) x.anx[s] = L.anx[b % 3][s][lane];
       }
-    } else {
-      // Helper wave w takes strip w - 1 of block b+1 over all b column
-      // steps; strip 3 is split at step h = b / 2, steps [0, h) to wave 1
-      // (with its fields G) and [h, b) to wave 2 (into an LDS partial that
-      // wave 3 adds after the barrier); wave 3 also takes the diagonal
-      // block.  The global reads of a part are issued before any of them
-      // is used, so that their latencies overlap.
-      const int h = b / 2;
-      if (next) {
+      x.sw = L.sw[b & 3][lane];
+    };
+    v4i dprev = zero;
+    auto decide = [&](int b, const Inputs& x) {
+      v4i acc[4];
 #pragma unroll
-        for (int i = 0; i < kCritPerHelper; ++i)
-          if (i < crit_cnt) crit_next[i] = crit_group(b + 1, crit_g0 + i);
-        v4i acc[4] = {zero, zero, zero, zero};
-        v4i av[kSB / kDB - 2];  // b <= kSB / kDB - 2 when there is a next block
-        int32_t gv[16];
-        if (wave == 3) {
-          // every read of the wave for block b+1 (diagonal block, strip,
-          // fields) in flight together
-          uint2 dj[kPairPer];
-          uint32_t dsw[kDiagPer];
-          fetch_diag(b + 1, lane, dj, dsw);
-          load_frags(b + 1, 2, 0, b, av);
-          load_g(b + 1, 2, gv);
-          put_diag(cb ^ 1, lane, dj, dsw);
-          strip_product(0, b, av, acc);
-          add_strip(b + 1, cb ^ 1, 2, acc, gv);
-        } else {
-          // the wave's strip and its part of strip 3, read together
-          v4i a3[(kSB / kDB - 1) / 2];
-          int32_t gv3[16];
-          const int kb = wave == 1 ? 0 : h, ke = wave == 1 ? h : b;
-          load_frags(b + 1, wave - 1, 0, b, av);
-          load_g(b + 1, wave - 1, gv);
-          load_frags(b + 1, 3, kb, ke, a3);
-          if (wave == 1) load_g(b + 1, 3, gv3);
-          strip_product(0, b, av, acc);
-          add_strip(b + 1, cb ^ 1, wave - 1, acc, gv);
-          v4i acc3[4] = {zero, zero, zero, zero};
-          strip_product(kb, ke, a3, acc3);
-          if (wave == 1) {
-            add_strip(b + 1, cb ^ 1, 3, acc3, gv3);
-          } else {
+      for (int s = 0; s < 4; ++s) acc[s] = L.field[b & 1][s][lane];
+      if (b > 0) {
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
+        for (int s = 0; s < 4; ++s) acc[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(x.anx[s], dprev, acc[s], 0, 0, 0);
+      }
 #pragma unroll
-              for (int j = 0; j < 4; ++j) part[4 * (lane >> 4) + j][nt * 16 + (lane & 15)] = acc3[nt][j];
+      for (int s = 0; s < 4; ++s) L.h0[b & 1][s][lane] = acc[s];
+      v4i dw = zero;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const uint32_t w = (uint32_t)x.sw[s];
+        u32x4 rnd;
+        if constexpr (EXACT)
+          rnd = philox10((uint32_t)((row0 + b * kDB + 16 * s + 4 * g) >> 2), gs, (uint32_t)r, kTagSweep, a.k0, a.k1);
+        int32_t m[4], nt[4], pr[6];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          m[j] = __builtin_amdgcn_sbfe((int32_t)w, 8u * j + 7u, 1u);
+          nt[j] = EXACT ? -m[j] : x.ncc[s][j] - m[j];
+        }
+#pragma unroll
+        for (int j = 1, k = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < j; ++i, ++k) pr[k] = __mul24((m[j] ^ m[i]) | 1, x.jin[s][k >> 2][k & 3]);
+        // the change of a flip, -2 s: 0xFE for s = +1 (0x01), 0x02 for s = -1 (0xFF)
+        const uint32_t bw = 0xFEFEFEFEu ^ (((w >> 7) & 0x01010101u) * 0xFCu);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          uint32_t dg = 0;
+          int32_t f[4];  // all ones: flip
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            int32_t t = (acc[s][j] ^ m[j]) + nt[j];  // EXACT: x = s h
+#pragma unroll
+            for (int i = 0; i < j; ++i) t = __mul24(f[i], pr[j * (j - 1) / 2 + i]) + t;
+            if constexpr (EXACT) {
+              const uint32_t T = a.thr[min(max(t, -Xt), Xt) + Xt];
+              bool fl = pick(rnd, j) < T;
+              if (RULE == 1) fl = fl || t <= 0;
+              f[j] = fl && row0 + b * kDB + 16 * s + 4 * g + j < a.n ? -1 : 0;
+            } else {
+              f[j] = t >> 31;
+            }
+            dg |= (uint32_t)f[j] & (bw & (0xFFu << (8 * j)));
+          }
+          const int32_t mine = g == q ? (int32_t)dg : 0;
+          dw[s] |= mine;
+          if (q < 3) {
+            v4i bv = zero;
+            bv[s] = mine;
+            acc[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(x.ain[s], bv, acc[s], 0, 0, 0);
           }
         }
+        v4i bv = zero;
+        bv[s] = dw[s];
+#pragma unroll
+        for (int s2 = s + 1; s2 < 4; ++s2)
+          acc[s2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(x.ain[s2], bv, acc[s2], 0, 0, 0);
+        *reinterpret_cast<int32_t*>(&L.dsl[c][b * kDB + 16 * s + 4 * g]) = dw[s];
+      }
+      dprev = dw;
+    };
+    Inputs xa, xb;
+    lds_barrier();
+    fetch(0, xa);
+    lds_barrier();
+    for (int b = 0; b < nb; b += 2) {
+      if (b + 1 < nb) fetch(b + 1, xb);
+      decide(b, xa);
+      lds_barrier();
+      if (b + 1 < nb) {
+        if (b + 2 < nb) fetch(b + 2, xa);
+        decide(b + 1, xb);
+        lds_barrier();
       }
     }
     lds_barrier();
-    if (next) {
-      if (wave != 0) {
+  } else if (wave <= 4) {
+    // strip sr of block x: its fields from the field product (cleared behind
+    // for the next super-block's), from the super-block before (whose
+    // columns that product left out) and from the flips of blocks 0 .. x - 2;
+    // read two blocks ahead (the super-block before's couplings one), multiplied
+    // one ahead
+    const int sr = wave - 1;
+    constexpr int kMaxSteps = kSB / kDB - 2, kPrev = kSB / kDB;
+    const int prev = row0 > 0 ? row0 - kSB : -1;  // first column of the super-block before
+    v4i av[2][kMaxSteps], pv[kPrev];
+    int32_t gv[2][4];
+    auto load_prev = [&](int x) {
+      if (x >= nb || prev < 0) return;
+      const int8_t* p = frag(x * kDB + 16 * sr, prev) + lane * 16;
 #pragma unroll
-        for (int i = 0; i < kCritPerHelper; ++i)
-          if (i < crit_cnt) crit[crit_g0 + i][lane] = crit_next[i];
+      for (int k = 0; k < kPrev; ++k) pv[k] = *reinterpret_cast<const v4i*>(p + 1024 * k);
+    };
+    auto load = [&](int x, v4i(&v)[kMaxSteps], int32_t(&f)[4]) {
+      if (x >= nb) return;
+      int32_t* gp = a.G + (size_t)(x * kDB + 16 * sr + 4 * g) * a.R + r;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[j] = gp[(size_t)j * a.R];
+      const int8_t* p = frag(x * kDB + 16 * sr, row0) + lane * 16;
+#pragma unroll
+      for (int k = 0; k < kMaxSteps; ++k)
+        if (k < x - 1) v[k] = *reinterpret_cast<const v4i*>(p + 1024 * k);
+    };
+    auto prepare = [&](int x, const v4i(&v)[kMaxSteps], const int32_t(&f)[4]) {
+      if (x >= nb) return;
+      v4i s0 = {f[0], f[1], f[2], f[3]}, s1 = zero;
+      if (prev >= 0) {
+#pragma unroll
+        for (int k = 0; k < kPrev; k += 2) {
+          s0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+              pv[k], *reinterpret_cast<const v4i*>(&L.spl[c][64 * k + 16 * g]), s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+              pv[k + 1], *reinterpret_cast<const v4i*>(&L.spl[c][64 * (k + 1) + 16 * g]), s1, 0, 0, 0);
+        }
       }
-      // block b's own flips, strip `wave` of block b+1
-      v4i acc[4] = {zero, zero, zero, zero};
+      load_prev(x + 1);
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        const v4i bv = *reinterpret_cast<const v4i*>(&dsl[nt * 16 + (lane & 15)][b * kDB + 16 * (lane >> 4)]);
-        acc[nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a_next, bv, acc[nt], 0, 0, 0);
+      for (int k = 0; k < kMaxSteps; ++k)
+        if (k < x - 1) {
+          const v4i bv = *reinterpret_cast<const v4i*>(&L.dsl[c][64 * k + 16 * g]);
+          if (k & 1)
+            s1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(v[k], bv, s1, 0, 0, 0);
+          else
+            s0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(v[k], bv, s0, 0, 0, 0);
+        }
+      L.field[x & 1][sr][lane] = s0 + s1;
+      int32_t* gp = a.G + (size_t)(x * kDB + 16 * sr + 4 * g) * a.R + r;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) gp[(size_t)j * a.R] = 0;
+    };
+    load(0, av[0], gv[0]);
+    load_prev(0);
+    load(1, av[1], gv[1]);
+    lds_barrier();  // the spins of the super-block before are in
+    prepare(0, av[0], gv[0]);
+    lds_barrier();
+    for (int b = 0; b < nb; b += 2) {
+      // while block b is decided: block b + 1; then b + 2 while b + 1 is
+      load(b + 2, av[0], gv[0]);
+      prepare(b + 1, av[1], gv[1]);
+      lds_barrier();
+      if (b + 1 < nb) {
+        load(b + 3, av[1], gv[1]);
+        prepare(b + 2, av[0], gv[0]);
+        lds_barrier();
       }
-      if (wave == 3) {
-        // wave 2's part of strip 3
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[nt][j] += part[4 * (lane >> 4) + j][nt * 16 + (lane & 15)];
-      }
-      add_strip(b + 1, cb ^ 1, wave, acc, nullptr);
     }
     lds_barrier();
-  }
-  if (wave != 0) return;
-  if (dE != 0)
-    __hip_atomic_fetch_add((unsigned long long*)&E[r], (unsigned long long)dE, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-  if (a.flip_ctr) {
+  } else if (wave <= 6) {
+    // wave 5: the couplings of block x to itself, those inside a lane's four
+    // spins, its critical fields and spin words; wave 6: its couplings to the
+    // block before it
+    const bool self = wave == 5;
+    v4i fa[4], cr[4], ji[2], sw;
+    auto load = [&](int x) {
+      if (x >= nb) return;
+      if (self || x > 0) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) nflip += __shfl_xor(nflip, o, 64);
-    if (lane == 0)
-      __hip_atomic_fetch_add((unsigned long long*)&a.flip_ctr[tile & 255],
-                             (unsigned long long)nflip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int s = 0; s < 4; ++s) {
+          const int8_t* f = frag(x * kDB + 16 * s, row0 + (self ? x : x - 1) * kDB) + 16 * c + 4 * g;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) fa[s][e] = word(f + 256 * e);
+        }
+      }
+      if (!self) return;
+      const int rb0 = row0 + x * kDB;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        cr[s] = a.C[(size_t)((rb0 >> 2) + 4 * s + g) * a.R + r];
+        sw[s] = word(S + (size_t)r * a.np + rb0 + 16 * s + 4 * g);
+      }
+      // lane = (strip c / 4, group c % 4): its four rows against its four columns
+      const int8_t* f = frag(x * kDB + 16 * (c >> 2), rb0) + 256 * (c >> 2) + 4 * (c & 3);
+#pragma unroll
+      for (int j = 1, k = 0; j < 4; ++j) {
+        const int32_t w = word(f + 16 * (4 * (c & 3) + j));
+#pragma unroll
+        for (int i = 0; i < j; ++i, ++k) ji[k >> 2][k & 3] = 2 * __builtin_amdgcn_sbfe(w, 8u * i, 8u);
+      }
+    };
+    auto put = [&](int x) {
+      if (x >= nb) return;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        if (self) {
+          L.ain[x & 3][s][lane] = fa[s];
+          L.crit[x % 3][s][lane] = cr[s];
+        } else if (x > 0) {
+          L.anx[x % 3][s][lane] = fa[s];
+        }
+      }
+      if (!self) return;
+      L.sw[x & 3][lane] = sw;
+      if (lane < 16) {
+        L.jin[x % 3][lane >> 2][lane & 3][0] = ji[0];
+        L.jin[x % 3][lane >> 2][lane & 3][1] = ji[1];
+      }
+    };
+    load(0);
+    put(0);
+    load(1);
+    lds_barrier();
+    put(1);
+    load(2);
+    lds_barrier();
+    for (int b = 0; b < nb; ++b) {
+      put(b + 2);
+      load(b + 3);
+      lds_barrier();
+    }
+    lds_barrier();
+  } else {
+    // wave 7: first the spins of the super-block before; then the energy
+    // change and the new spin words of block x
+    if (row0 > 0) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        *reinterpret_cast<v4i*>(&L.spl[i][16 * lane]) =
+            *reinterpret_cast<const v4i*>(S + (size_t)(group * 16 + i) * a.np + row0 - kSB + 16 * lane);
+    }
+    int64_t dE = 0;
+    int32_t nflip = 0;
+    auto finish = [&](int x) {
+      v4i d, sw = L.sw[x & 3][lane];
+      int32_t e = 0;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) d[s] = *reinterpret_cast<const int32_t*>(&L.dsl[c][x * kDB + 16 * s + 4 * g]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        v4i p = L.h0[x & 1][s][lane];
+        p = __builtin_amdgcn_mfma_i32_16x16x64_i8(L.ain[x & 3][s][lane], d, p + p, 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) e += __builtin_amdgcn_sbfe(d[s], 8u * j + 1u, 7u) * p[j];  // d / 2
+        // a flip turns 0x01 <-> 0xFF, i.e. xor 0xFE
+        const uint32_t f = (uint32_t)d[s] & 0x02020202u;
+        *reinterpret_cast<uint32_t*>(S + (size_t)r * a.np + row0 + x * kDB + 16 * s + 4 * g) = (uint32_t)sw[s] ^ (f * 0x7Fu);
+        nflip += __builtin_popcount(f);
+      }
+      dE -= e;  // |e| < 2^31: |p| <= 2 X + 2^14, X < 2^25, 16 spins per lane
+    };
+    lds_barrier();
+    lds_barrier();
+    for (int b = 0; b < nb; ++b) {
+      if (b > 0) finish(b - 1);
+      lds_barrier();
+    }
+    finish(nb - 1);
+    lds_barrier();
+    // the four lanes of a replica
+    dE += __shfl_xor(dE, 16, 64);
+    dE += __shfl_xor(dE, 32, 64);
+    if (g == 0 && dE != 0)
+      __hip_atomic_fetch_add((unsigned long long*)&(cur ? a.E1 : a.E0)[r], (unsigned long long)dE, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+    if (a.flip_ctr) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) nflip += __shfl_xor(nflip, o, 64);
+      if (lane == 0)
+        __hip_atomic_fetch_add((unsigned long long*)&a.flip_ctr[group & 255], (unsigned long long)nflip,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
 }
 
-// One super-block step: work-groups 0..T-1 run the sequential pass of this
-// super-block (one per replica tile); with gemm_on the others compute the
+// One super-block step: work-groups 0 .. NG-1 run the sequential pass of this
+// super-block (one per 16 replicas); with gemm_on the others compute the
 // field product of the next super-block over every column except this
-// super-block's own (which the pass is changing), into the other field
-// buffer.  The two parts share no data, so the product runs on the compute
-// units the pass leaves idle; the missing columns are added by a small
-// product once the pass is done.
-template <int RULE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-k_dense_step(SeqArgs a, GemmArgs g, int32_t sweep_idx, int32_t row0, int32_t rows, int32_t T, int32_t gemm_on) {
+// super-block's own (which the pass is changing; the next pass adds them),
+// into the other field buffer.  The two parts share no data, so the product
+// runs on the compute units the pass leaves idle: 61 us a
+// super-block at n = 100,000, R = 256, where the product is the longer part (90
+// with the former layout and pass), and 32 us at n = 2,047, R = 64, where the
+// pass is (757).
+template <int RULE, int NT>
+__global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_dense_step(SeqArgs a, GemmArgs g, int32_t sweep_idx, int32_t row0, int32_t rows, int32_t NG, int32_t gemm_on) {
   __shared__ union {
     SeqLds seq;
-    GemmLds gemm;
+    GemmLds<NT> gemm;
   } L;
-  if ((int)blockIdx.x < T) {
-    // fields beyond the LDS table need checking only when it is narrower
-    // than the full one
-    const int32_t Xt = (int32_t)a.st->table_x;
-    if (a.j4) {
-      if (Xt > kThrL)
-        seq_body<RULE, true, true>(a, blockIdx.x, sweep_idx, row0, rows, L.seq);
-      else
-        seq_body<RULE, false, true>(a, blockIdx.x, sweep_idx, row0, rows, L.seq);
-    } else {
-      if (Xt > kThrL)
-        seq_body<RULE, true, false>(a, blockIdx.x, sweep_idx, row0, rows, L.seq);
-      else
-        seq_body<RULE, false, false>(a, blockIdx.x, sweep_idx, row0, rows, L.seq);
-    }
+  if ((int)blockIdx.x < NG) {
+    if (*a.not_monotone)
+      seq_body<RULE, true>(a, blockIdx.x, sweep_idx, row0, rows, L.seq);
+    else
+      seq_body<RULE, false>(a, blockIdx.x, sweep_idx, row0, rows, L.seq);
+  } else if (gemm_on) {
+    gemm_body<NT>(g, blockIdx.x - NG, L.gemm);
   }
-  else if (gemm_on)
-    gemm_body(g, blockIdx.x - T, L.gemm);
 }
 
 // Energy of the population from super-block fields: E_r += sum_k s_rk G_kr
 // (the caller negates and halves at the end); clears G.  Work-group =
-// (tile, 64-row block), wave 0 lanes = replicas.
+// (tile, kEnergyRows-row block), lanes = replicas.
+constexpr int kEnergyRows = 8;
 __global__ void __launch_bounds__(64) k_dense_energy_sb(const int8_t* S, int32_t* G, int64_t* E, int32_t row0,
                                                         int32_t rows, int32_t n, int32_t np, int32_t R) {
   const int T = R / 64;
   const int tile = blockIdx.x % T, rb = blockIdx.x / T;
   const int r = tile * 64 + threadIdx.x;
   int64_t acc = 0;
-  for (int k = 64 * rb; k < 64 * rb + 64 && row0 + k < n; ++k) {
+#pragma unroll
+  for (int k = kEnergyRows * rb; k < kEnergyRows * (rb + 1); ++k) {
+    if (row0 + k >= n) break;
     int32_t* gp = G + (size_t)k * R + r;
     acc += (int64_t)*gp * S[(size_t)r * np + row0 + k];
     *gp = 0;
@@ -954,38 +862,61 @@ __global__ void __launch_bounds__(256) k_dense_collect_sb(int32_t* G, int32_t* H
 // ---------------------------------------------------------------------------
 static inline uint32_t key0(const pamc_instance* I) { return (uint32_t)I->seed; }
 static inline uint32_t key1(const pamc_instance* I) { return (uint32_t)(I->seed >> 32); }
+// Set by k_dense_crit where the thresholds rise; cleared with each table.
+static inline int32_t* dense_monotone_flag(const pamc_instance* I) {
+  return reinterpret_cast<int32_t*>(I->flip_ctr + kMonotoneSlot);
+}
+
+// Kernels whose dynamic LDS may exceed the default limit.
+hipError_t prepare_dense_lds() {
+  for (const void* k : {(const void*)k_dense_crit<0>, (const void*)k_dense_crit<1>}) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (kCritLds + 1));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 hipError_t launch_dense_generate(pamc_instance* I, uint64_t graph_seed) {
   int64_t* W = I->flip_ctr + 400;
   hipMemsetAsync(W, 0, sizeof(int64_t), I->stream);
-  const int64_t total = (int64_t)I->dn_pad * I->dn_pad;
+  const int64_t total = (int64_t)I->dn_pad * I->dn_pad / 16;
   const int grid = (int)std::min<int64_t>((total + 255) / 256, 1 << 16);
-  k_dense_generate<<<grid, 256, 0, I->stream>>>(I->Jd, I->n, I->dn_pad, (uint32_t)graph_seed,
+  k_dense_generate<<<grid, 256, 0, I->stream>>>(reinterpret_cast<v4i*>(I->Jd), I->n, I->dn_pad, (uint32_t)graph_seed,
                                                 (uint32_t)(graph_seed >> 32), W);
   return hipGetLastError();
+}
+
+void dense_fragments(int32_t np, const int8_t* rows, int8_t* out) {
+  for (int32_t i = 0; i < 16; ++i)
+    for (int32_t j = 0; j < np; j += 16) memcpy(out + frag_at(np, i, j), rows + (size_t)i * np + j, 16);
 }
 
 // rows of the super-block starting at row0 (a multiple of 64)
 static inline int sb_rows(const pamc_instance* I, int row0) { return std::min(kSB, I->dn_pad - row0); }
 
+// Replicas per tile of the field product: all of them up to 256, so that the
+// couplings are read once.
+static inline int gemm_nt(const pamc_instance* I) { return I->R <= 64 ? 64 : (I->R <= 128 ? 128 : 256); }
+
 // K slices of the field product, each a multiple of the 64-column stage.
 struct GemmShape {
   int grid, kslice;
 };
-// About 192 working work-groups: the K range is cut into P slices of whole
-// stages; the grid covers the slices in groups of 8 (one per XCD;
-// work-groups of slices past the end return at once).  The product shares
-// the device with the sequential pass, and fewer, longer work-groups leave
-// it more of the memory system: C3 sweeps timed at 128, 192, 256, 384, 512,
-// 768 and 1,024 were fastest at 192.
+// About kGemmWorkGroups working work-groups: the K range is cut into P
+// slices of whole stages; the grid covers the slices in groups of 8 (one per
+// XCD; work-groups of slices past the end return at once).  P above 8 is a
+// multiple of 8, or some XCDs would get a slice more than others and, beside
+// the pass's work-groups, more work-groups than CUs: n = 100,000, R = 256
+// takes 82 ms a run of 12 sweeps with 128 + 64 of them, 99 with 128 (16
+// slices) and 124 with 224 (28 slices).
+constexpr int kGemmWorkGroups = 192;
 static inline GemmShape gemm_shape(const pamc_instance* I, int rows, int kcount) {
-  const int tiles = ((rows + kGM - 1) / kGM) * ((I->R + kGN - 1) / kGN);
-  const int stages = std::max(1, kcount / kGK);
-  // at least 4 stages per work-group: a short K range (the previous
-  // super-block's columns, 16 stages) splits in 4 slices (timed against
-  // 1, 2, 8 and 16 stages per work-group)
-  const int P = std::max(1, std::min(stages / 4, (192 + tiles - 1) / tiles));
-  const int kslice = ((stages + P - 1) / P) * kGK;
+  const int nt = gemm_nt(I);
+  const int tiles = ((rows + kGM - 1) / kGM) * ((I->R + nt - 1) / nt);
+  const int stages = std::max(1, (kcount + kStage - 1) / kStage);
+  int P = std::max(1, std::min(stages / 2, kGemmWorkGroups / tiles));  // at least two stages per work-group
+  if (P > 8) P -= P % 8;
+  const int kslice = ((stages + P - 1) / P) * kStage;
   const int slices = (kcount + kslice - 1) / kslice;
   return {tiles * ((slices + 7) / 8) * 8, kslice};
 }
@@ -1017,6 +948,13 @@ static GemmLaunch gemm_launch(const pamc_instance* I, int32_t row0, int32_t rows
   g.xlen = xlen;
   return {g, gsh.grid};
 }
+static void launch_gemm(const pamc_instance* I, const GemmLaunch& gl) {
+  switch (gemm_nt(I)) {
+    case 64: k_dense_gemm<64><<<gl.grid, kDenseThreads, 0, I->stream>>>(gl.g); break;
+    case 128: k_dense_gemm<128><<<gl.grid, kDenseThreads, 0, I->stream>>>(gl.g); break;
+    default: k_dense_gemm<256><<<gl.grid, kDenseThreads, 0, I->stream>>>(gl.g); break;
+  }
+}
 static GemmLaunch gemm_full(const pamc_instance* I, int32_t row0, int32_t rows, int32_t use_state, int32_t* G) {
   return gemm_launch(I, row0, rows, use_state, G, 0, I->dn_pad, I->dn_pad, 0);
 }
@@ -1027,8 +965,8 @@ static hipError_t dense_full_energy(pamc_instance* I, int buf) {
   for (int row0 = 0; row0 < I->n; row0 += kSB) {
     const int rows = sb_rows(I, row0);
     const GemmLaunch gl = gemm_full(I, row0, rows, 0, I->Gd);
-    k_dense_gemm<<<gl.grid, 256, 0, I->stream>>>(gl.g);
-    k_dense_energy_sb<<<T * (rows / 64), 64, 0, I->stream>>>(buf ? I->Sd2 : I->Sd, I->Gd, I->pop.E[buf], row0,
+    launch_gemm(I, gl);
+    k_dense_energy_sb<<<T * (rows / kEnergyRows), 64, 0, I->stream>>>(buf ? I->Sd2 : I->Sd, I->Gd, I->pop.E[buf], row0,
                                                              rows, I->n, I->dn_pad, I->R);
   }
   return hipGetLastError();
@@ -1056,13 +994,18 @@ hipError_t launch_dense_load(pamc_instance* I) {
 // with its critical fields (every visit's, one launch); super-block 0 of a
 // sweep gets its full product first; then, for each super-block i, the
 // launch that runs its sequential pass also computes the product of i+1
-// over every column except i's, and a small product adds i's (now final)
-// columns to i+1 before its pass.  With profiling, one event pair brackets
-// each super-block step (the completing product and the pass with the
-// overlapped product).
+// over every column except i's, which (final by then) the pass of i+1 adds
+// itself.  With profiling, one event pair brackets each super-block step (the
+// pass with the overlapped product).
 static hipError_t dense_sweeps(Batch& b, int32_t nsweeps) {
   pamc_instance* I = b.I[0];
-  const int T = I->R / 64;
+  const int NG = I->R / 16;
+  using StepKernel = void (*)(SeqArgs, GemmArgs, int32_t, int32_t, int32_t, int32_t, int32_t);
+  static const StepKernel step_kernels[2][3] = {{k_dense_step<0, 64>, k_dense_step<0, 128>, k_dense_step<0, 256>},
+                                                {k_dense_step<1, 64>, k_dense_step<1, 128>, k_dense_step<1, 256>}};
+  const int nt = gemm_nt(I);
+  const StepKernel step = step_kernels[I->rule == 1][nt == 64 ? 0 : (nt == 128 ? 1 : 2)];
+  int32_t* const not_monotone = dense_monotone_flag(I);
   SeqArgs a;
   a.J = I->Jd;
   a.S0 = I->Sd;
@@ -1071,11 +1014,11 @@ static hipError_t dense_sweeps(Batch& b, int32_t nsweeps) {
   a.E1 = I->pop.E[1];
   a.thr = I->thr;
   a.C = reinterpret_cast<const v4i*>(I->Cd);
+  a.not_monotone = not_monotone;
   a.st = I->st;
   a.n = I->n;
   a.np = I->dn_pad;
   a.R = I->R;
-  a.j4 = I->dense_j4;
   a.k0 = key0(I);
   a.k1 = key1(I);
   a.flip_ctr = I->prof ? I->flip_ctr : nullptr;
@@ -1093,19 +1036,17 @@ static hipError_t dense_sweeps(Batch& b, int32_t nsweeps) {
       if (i == 0) {
         // the sweep's critical fields, then super-block 0's full product
         const int64_t items = (int64_t)(I->dn_pad / 4) * I->R;
-        const int cgrid = (int)std::min<int64_t>((items + 255) / 256, 2048);
+        const int cgrid = (int)std::min<int64_t>((items + kCritThreads - 1) / kCritThreads, 256);
+        // LDS for the table at its widest, 2 X + 1 entries
+        const size_t lds = sizeof(uint32_t) * (size_t)std::min<int64_t>(2 * I->X + 1, kCritLds + 1);
         v4i* C = reinterpret_cast<v4i*>(I->Cd);
         if (I->rule == 1)
-          k_dense_crit<1><<<cgrid, 256, 0, I->stream>>>(I->thr, I->st, C, s, I->dn_pad / 4, I->R, a.k0, a.k1);
+          k_dense_crit<1><<<cgrid, kCritThreads, lds, I->stream>>>(I->thr, I->st, C, not_monotone, s, I->n,
+                                                                   I->dn_pad / 4, I->R, a.k0, a.k1);
         else
-          k_dense_crit<0><<<cgrid, 256, 0, I->stream>>>(I->thr, I->st, C, s, I->dn_pad / 4, I->R, a.k0, a.k1);
-        const GemmLaunch gl = gemm_full(I, row0, rows, 1, gbuf(0));
-        k_dense_gemm<<<gl.grid, 256, 0, I->stream>>>(gl.g);
-      } else {
-        // the previous super-block's columns, final now
-        const int p0 = row0 - kSB;
-        const GemmLaunch gl = gemm_launch(I, row0, rows, 1, gbuf(i), p0, sb_rows(I, p0), 0, 0);
-        k_dense_gemm<<<gl.grid, 256, 0, I->stream>>>(gl.g);
+          k_dense_crit<0><<<cgrid, kCritThreads, lds, I->stream>>>(I->thr, I->st, C, not_monotone, s, I->n,
+                                                                   I->dn_pad / 4, I->R, a.k0, a.k1);
+        launch_gemm(I, gemm_full(I, row0, rows, 1, gbuf(0)));
       }
       a.G = gbuf(i);
       const bool next = i + 1 < nsb;
@@ -1114,11 +1055,7 @@ static hipError_t dense_sweeps(Batch& b, int32_t nsweeps) {
         const int n0 = row0 + kSB;
         nx = gemm_launch(I, n0, sb_rows(I, n0), 1, gbuf(i + 1), 0, I->dn_pad - rows, row0, rows);
       }
-      const int grid = T + (next ? nx.grid : 0);
-      if (I->rule == 1)
-        k_dense_step<1><<<grid, 256, 0, I->stream>>>(a, nx.g, s, row0, rows, T, next ? 1 : 0);
-      else
-        k_dense_step<0><<<grid, 256, 0, I->stream>>>(a, nx.g, s, row0, rows, T, next ? 1 : 0);
+      step<<<NG + (next ? nx.grid : 0), kDenseThreads, 0, I->stream>>>(a, nx.g, s, row0, rows, NG, next ? 1 : 0);
       if (I->prof) {
         hipEvent_t e1 = ctl_event(I);
         hipEventRecord(e1, I->stream);
@@ -1179,7 +1116,7 @@ hipError_t launch_dense_fields(pamc_instance* I, int32_t* H_rmajor) {
   for (int row0 = 0; row0 < I->n; row0 += kSB) {
     const int rows = sb_rows(I, row0);
     const GemmLaunch gl = gemm_full(I, row0, rows, 2, I->Gd);
-    k_dense_gemm<<<gl.grid, 256, 0, I->stream>>>(gl.g);
+    launch_gemm(I, gl);
     k_dense_collect_sb<<<std::min(1024, (rows * I->R + 255) / 256), 256, 0, I->stream>>>(
         I->Gd, H_rmajor, row0, rows, I->n, I->dn_pad, I->R);
   }

@@ -131,10 +131,9 @@ struct pamc_instance {
   int32_t* m3_labels = nullptr;
   int64_t* m3_cut = nullptr;
   // dense instance
-  int8_t* Jd = nullptr;  // [np_pad][ld] row-major
+  int8_t* Jd = nullptr;  // couplings as matrix-core fragments (dense_fragments), n padded to 64
   int64_t ldj = 0;
   int32_t dn_pad = 0;    // padded dimension of the dense matrix
-  int32_t dense_j4 = 0;  // every dense coupling in [-8, 7] (four-bit dot products)
   int8_t* Sd = nullptr;  // [R][dn_pad] replica-major spins (dense)
   int8_t* Sd2 = nullptr; // resampling buffer
   int32_t* Gd = nullptr; // super-block field buffers [2][rows][R]
@@ -215,6 +214,7 @@ struct Desc {
   uint32_t* btab;
   int32_t* bphases;
   int32_t bits, bcoup, bmaxdeg, bpad;
+  int32_t* not_monotone;  // dense instances: cleared with each threshold table
 };
 
 // What the bit-packed sweep kernels read of an instance.  Masks: a group of
@@ -362,6 +362,14 @@ hipError_t ctl_deactivate(Batch& b);
 hipEvent_t ctl_event(pamc_instance* I);
 
 // dense path launchers (dense.hip); b is the instance's batch of one
+// The slot of an instance's counters (flip_ctr) that tells whether the
+// current threshold table rises anywhere.
+constexpr int kMonotoneSlot = 404;
+hipError_t prepare_dense_lds();
+// 16 rows of np int8 couplings as matrix-core A fragments (the layout of Jd:
+// [row block of 16][step of 64 columns][lane][16 bytes], lane l holding
+// columns 16 (l / 16) .. of row l % 16); out: 16 np bytes.
+void dense_fragments(int32_t np, const int8_t* rows, int8_t* out);
 int32_t dense_superblock_rows();
 int32_t dense_field_buffers();  // super-block field buffers (the next one is filled during a pass)
 hipError_t launch_dense_fields(pamc_instance* I, int32_t* H_rmajor);

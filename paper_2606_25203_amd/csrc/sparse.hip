@@ -1354,6 +1354,7 @@ __global__ void __launch_bounds__(256) k_thresholds(const Desc* __restrict__ D,
     if (threadIdx.x == 0) commit_step(d, commit);
     __syncthreads();  // the phase records below name the buffer it makes current
   }
+  if (d.not_monotone && lb == 0 && threadIdx.x == 0) *d.not_monotone = 0;
   const int64_t Xt = st->table_x;
   const double beta = st->sweep_beta;
   if (d.potts_K) {  // e^{beta (syn_k - max syn)} for max syn - syn_k = i
@@ -2352,6 +2353,7 @@ Desc make_desc(const pamc_instance* I) {
   d.bits = I->bits;
   d.bcoup = I->bcoup;
   d.bmaxdeg = I->bmaxdeg;
+  d.not_monotone = I->dense ? reinterpret_cast<int32_t*>(I->flip_ctr + kMonotoneSlot) : nullptr;
   return d;
 }
 
