@@ -93,6 +93,7 @@ void free_instance(pamc_instance* I) {
   delete I->self;
   I->self = nullptr;
   dev_free(I, I->d_sched);
+  dev_free(I, I->pair_out);
   void* ptrs[] = {I->g.row_ptr, I->g.col, I->g.J, I->g.grow, I->g.gcol, I->g.gJ, I->g.class_ptr, I->pop.S[0], I->pop.S[1],
                   I->pop.H[0], I->pop.H[1], I->pop.E[0], I->pop.E[1], I->pop.fam[0],
                   I->pop.fam[1], I->best, I->to_internal_dev, I->st, I->thr, I->order,
@@ -1717,17 +1718,22 @@ pamc_status pamc_max3cut_decode(pamc_instance* I, const int8_t* spins, int32_t* 
   return PAMC_OK;
 }
 
+// Mean of min(d, n - d) / n over all pairs from the sum over them.
+static double mean_pair_distance(const pamc_instance* I, int64_t sum) {
+  return I->R > 1 ? (double)sum / ((double)I->n * (0.5 * (double)I->R * (double)(I->R - 1))) : 0.0;
+}
+
 pamc_status pamc_pair_distance(pamc_instance* I, double* mean) {
   if (!I || !mean) return fail(PAMC_ERR_INVALID_ARG, "NULL argument");
   if (I->dense) return fail(PAMC_ERR_UNSUPPORTED, "pair distance on dense instances");
   if (I->potts_K) return fail(PAMC_ERR_UNSUPPORTED, "pair distance on Potts labels");
   hipSetDevice(I->device);
-  double* d = (double*)(I->flip_ctr + 300);
-  HIP_TRY(pamc::launch_pair_distance(I, d), "pair distance");
-  double v = 0.0;
+  int64_t* d = I->flip_ctr + 300;
+  HIP_TRY(pamc::launch_pair_hist(I, 0, d), "pair distance");
+  int64_t sum = 0;
   HIP_TRY(hipStreamSynchronize(I->stream), "pair distance");
-  HIP_TRY(hipMemcpy(&v, d, sizeof(double), hipMemcpyDeviceToHost), "readback");
-  *mean = I->R > 1 ? v / ((double)I->R * (I->R - 1) / 2.0) : 0.0;
+  HIP_TRY(hipMemcpy(&sum, d, sizeof(int64_t), hipMemcpyDeviceToHost), "readback");
+  *mean = mean_pair_distance(I, sum);
   return PAMC_OK;
 }
 
@@ -2047,20 +2053,20 @@ pamc_status pamc_autotune(pamc_instance* I, double beta, int32_t sweeps, int32_t
 
 pamc_status pamc_pair_distance_hist(pamc_instance* I, int32_t nbins, int64_t* counts, double* mean) {
   if (!I || !counts) return fail(PAMC_ERR_INVALID_ARG, "NULL argument");
-  if (nbins < 1 || nbins > 4096) return fail(PAMC_ERR_INVALID_ARG, "nbins must lie in [1, 4096]");
+  constexpr int32_t kMaxPairBins = 4096;
+  if (nbins < 1 || nbins > kMaxPairBins) return fail(PAMC_ERR_INVALID_ARG, "nbins must lie in [1, 4096]");
   if (I->dense) return fail(PAMC_ERR_UNSUPPORTED, "pair distance on dense instances");
   if (I->potts_K) return fail(PAMC_ERR_UNSUPPORTED, "pair distance on Potts labels");
   hipSetDevice(I->device);
-  int64_t* d = nullptr;
-  HIP_TRY(dev_alloc(I, (void**)&d, sizeof(int64_t) * (nbins + 1)), "alloc");
-  hipError_t e = pamc::launch_pair_hist(I, nbins, d, d + nbins);
-  int64_t sum = 0;
+  // kept with the instance: an allocation and its release cost more than the kernel
+  if (!I->pair_out) HIP_TRY(dev_alloc(I, (void**)&I->pair_out, sizeof(int64_t) * (kMaxPairBins + 1)), "alloc");
+  int64_t out[kMaxPairBins + 1];
+  hipError_t e = pamc::launch_pair_hist(I, nbins, I->pair_out);
   if (e == hipSuccess) e = hipStreamSynchronize(I->stream);
-  if (e == hipSuccess) e = hipMemcpy(counts, d, sizeof(int64_t) * nbins, hipMemcpyDeviceToHost);
-  if (e == hipSuccess) e = hipMemcpy(&sum, d + nbins, sizeof(int64_t), hipMemcpyDeviceToHost);
-  dev_free(I, d);
+  if (e == hipSuccess) e = hipMemcpy(out, I->pair_out, sizeof(int64_t) * (nbins + 1), hipMemcpyDeviceToHost);
   if (e != hipSuccess) return dev_fail(e, "pair distance histogram");
-  if (mean) *mean = I->R > 1 ? (double)sum / ((double)I->n * (0.5 * (double)I->R * (double)(I->R - 1))) : 0.0;
+  std::copy(out, out + nbins, counts);
+  if (mean) *mean = mean_pair_distance(I, out[nbins]);
   return PAMC_OK;
 }
 

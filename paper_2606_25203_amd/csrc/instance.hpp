@@ -152,6 +152,7 @@ struct pamc_instance {
   pamc::Batch* self = nullptr;
   bool self_dirty = true;
   void* d_sched = nullptr;  // device copy of the run's schedule
+  int64_t* pair_out = nullptr;  // pair-distance histogram and sum (allocated at its first call)
 };
 
 namespace pamc {
@@ -328,11 +329,11 @@ hipError_t launch_fields(Batch& b, int32_t buf, int32_t* H);
 // (spins uploaded by the host); the current buffer becomes 0.
 hipError_t launch_load_population(Batch& b);
 hipError_t launch_m3_decode(pamc_instance* I, const int8_t* spins_internal_dev);
-hipError_t launch_pair_distance(pamc_instance* I, double* out_dev);
-// histogram of min(d, n - d) over all replica pairs into nbins bins of
-// [0, 1/2] (bin = floor(2 nbins min(d, n-d) / n), capped) plus its sum
 hipError_t launch_refresh_fields(Batch& b);
-hipError_t launch_pair_hist(pamc_instance* I, int32_t nbins, int64_t* hist_dev, int64_t* sum_dev);
+// histogram of min(d, n - d) over all replica pairs into nbins >= 0
+// bins of [0, 1/2] (bin = floor(2 nbins min(d, n-d) / n), capped) in out_dev[0 ..
+// nbins), their sum after them
+hipError_t launch_pair_hist(pamc_instance* I, int32_t nbins, int64_t* out_dev);
 int32_t cluster_max_n();
 int32_t sweep_waves();  // wavefronts per sweep work-group
 int32_t tile_max_quads();  // vertex quads a tile-resident sweep holds in LDS
