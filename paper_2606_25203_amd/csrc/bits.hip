@@ -39,13 +39,6 @@ constexpr int kBitTab = 2 * (2 * kBitsMaxDegree + 2);  // threshold entries, sta
 typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-// Read-only memory of a launch: uniform reads of it are scalar loads.
-#define PAMC_CONST __attribute__((address_space(4)))
-template <typename T>
-__device__ __forceinline__ const PAMC_CONST T* cmem(const T* p) {
-  return (const PAMC_CONST T*)p;
-}
-
 // a + (bit of this lane in m); m comes from a scalar load (inline asm: no wait
 // states are kept between a vector instruction that writes m and this one).
 __device__ __forceinline__ uint32_t add_bit(uint32_t a, uint64_t m) {

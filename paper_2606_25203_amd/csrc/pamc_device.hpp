@@ -22,6 +22,14 @@ __device__ __forceinline__ PAMC_GLOBAL T* gmem(T* p) {
   return (PAMC_GLOBAL T*)p;
 }
 
+// Memory that no work-group of a launch writes: uniform reads of it are scalar
+// loads, also where a store or an atomic might alias an ordinary pointer.
+#define PAMC_CONST __attribute__((address_space(4)))
+template <typename T>
+__device__ __forceinline__ const PAMC_CONST T* cmem(const T* p) {
+  return (const PAMC_CONST T*)p;
+}
+
 constexpr int kLanes = 64;      // replicas per tile = wavefront width
 constexpr int kMaxHubs = 2;     // hub vertices with incrementally kept fields in the gathered-field mode
 constexpr int kHistCap = 64;    // controller history capacity (>= win_long)

@@ -93,22 +93,20 @@ __device__ __forceinline__ void group_chunk(int G, int lb, int& group, int& chun
 // of its spin word, so one 4 x int8 dot product adds J s_j.
 // ---------------------------------------------------------------------------
 template <int JM, int TPW>
-__device__ __forceinline__ void gather_fields(const PAMC_GLOBAL int32_t* __restrict__ gcol,
-                                              const PAMC_GLOBAL int32_t* __restrict__ gJ, int e0, int e1,
+__device__ __forceinline__ void gather_fields(const PAMC_CONST int32_t* __restrict__ gcol,
+                                              const PAMC_CONST int32_t* __restrict__ gJ, int e0, int e1,
                                               __amdgpu_buffer_rsrc_t Sr, const int (&voff)[TPW],
                                               int32_t (&h)[TPW]) {
 #pragma unroll
   for (int t = 0; t < TPW; ++t) h[t] = 0;
   for (int e = e0; e < e1; e += 4) {
     // rows start at multiples of 4 entries: one 16-byte scalar load each
-    const i32x4 cj = *reinterpret_cast<const PAMC_GLOBAL i32x4*>(gcol + e);
-    const i32x4 cJ = *reinterpret_cast<const PAMC_GLOBAL i32x4*>(gJ + e);
-    // uniform by construction; stated so that a vector load of them can
-    // never turn the buffer offsets below into per-lane values
-    const int j[4] = {__builtin_amdgcn_readfirstlane(cj.x), __builtin_amdgcn_readfirstlane(cj.y),
-                      __builtin_amdgcn_readfirstlane(cj.z), __builtin_amdgcn_readfirstlane(cj.w)};
-    const int32_t c[4] = {__builtin_amdgcn_readfirstlane(cJ.x), __builtin_amdgcn_readfirstlane(cJ.y),
-                          __builtin_amdgcn_readfirstlane(cJ.z), __builtin_amdgcn_readfirstlane(cJ.w)};
+    const i32x4 cj = *reinterpret_cast<const PAMC_CONST i32x4*>(gcol + e);
+    const i32x4 cJ = *reinterpret_cast<const PAMC_CONST i32x4*>(gJ + e);
+    const int j[4] = {cj.x, cj.y,
+                      cj.z, cj.w};
+    const int32_t c[4] = {cJ.x, cJ.y,
+                          cJ.z, cJ.w};
     uint32_t w[TPW][4];
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
@@ -171,9 +169,9 @@ __device__ __forceinline__ void reduce_energy_and_flips(int64_t (*red)[kLanes], 
 // vertices), so it is summed in 32 bits.
 // ---------------------------------------------------------------------------
 template <int JM, int TPW, bool THR_LDS, bool HUB>
-__device__ __forceinline__ void sweep_pull_body(const PAMC_GLOBAL int32_t* __restrict__ row_ptr,
-                                                const PAMC_GLOBAL int32_t* __restrict__ col,
-                                                const PAMC_GLOBAL int32_t* __restrict__ Jc,
+__device__ __forceinline__ void sweep_pull_body(const PAMC_CONST int32_t* __restrict__ row_ptr,
+                                                const PAMC_CONST int32_t* __restrict__ col,
+                                                const PAMC_CONST int32_t* __restrict__ Jc,
                                                 const PAMC_GLOBAL uint32_t* __restrict__ thr_g,
                                                 uint32_t* thr_s, PAMC_GLOBAL uint32_t* __restrict__ S,
                                                 PAMC_GLOBAL int64_t* __restrict__ E, const Desc& d,
@@ -222,7 +220,7 @@ __device__ __forceinline__ void sweep_pull_body(const PAMC_GLOBAL int32_t* __res
       const int v = 4 * q + k;
       const bool in = v >= v0 && v < v1;
 #pragma unroll
-      for (int hk = 0; hk < kMaxHubs; ++hk) hj[k][hk] = (HUB && in) ? gmem(d.hubJ)[v * kMaxHubs + hk] : 0;
+      for (int hk = 0; hk < kMaxHubs; ++hk) hj[k][hk] = (HUB && in) ? cmem(d.hubJ)[v * kMaxHubs + hk] : 0;
       if (HUB && in && (v == d.hub_v0 || v == d.hub_v1)) {
         const int hk = v == d.hub_v0 ? 0 : 1;
 #pragma unroll
@@ -303,8 +301,8 @@ __global__ void __launch_bounds__(256) k_sweep_pull(const Desc* __restrict__ D,
   const PAMC_GLOBAL RunState* __restrict__ st = gmem((const RunState*)d.st);
   if (!st->active || sweep_idx >= st->nsweeps_now || phase >= d.ncls) return;
   const int cur = st->cur;
-  const PAMC_GLOBAL int32_t* __restrict__ order = gmem((const int32_t*)d.order);
-  const PAMC_GLOBAL int32_t* __restrict__ class_ptr = gmem(d.class_ptr);
+  const PAMC_CONST int32_t* __restrict__ order = cmem((const int32_t*)d.order);
+  const PAMC_CONST int32_t* __restrict__ class_ptr = cmem(d.class_ptr);
   const int cls = order[sweep_idx * d.ncls + phase];
   const int v0 = class_ptr[cls], v1 = class_ptr[cls + 1];
   const int nqc = ((v1 + 3) >> 2) - (v0 >> 2);
@@ -316,16 +314,16 @@ __global__ void __launch_bounds__(256) k_sweep_pull(const Desc* __restrict__ D,
   const PAMC_GLOBAL uint32_t* __restrict__ thr_g = gmem((const uint32_t*)d.thr);
   PAMC_GLOBAL uint32_t* __restrict__ S = gmem(cur ? d.S1 : d.S0);
   PAMC_GLOBAL int64_t* __restrict__ E = gmem(cur ? d.E1 : d.E0);
-  const PAMC_GLOBAL int32_t* __restrict__ Jc = gmem(d.gJ);
+  const PAMC_CONST int32_t* __restrict__ Jc = cmem(d.gJ);
   // the step's table (2 Xt + 1 entries) goes to LDS whenever it fits, also
   // for instances whose full range (WIDE: 2X + 1) would not
   if (!WIDE || 2 * Xt + 1 <= kThrLds) {
     for (int i = threadIdx.x; i <= 2 * Xt; i += blockDim.x) thr_s[i] = thr_g[i];
     __syncthreads();
-    sweep_pull_body<JM, TPW, true, HUB>(gmem(d.grow), gmem(d.gcol), Jc, thr_g, thr_s, S, E, d, group, chunk, v0,
+    sweep_pull_body<JM, TPW, true, HUB>(cmem(d.grow), cmem(d.gcol), Jc, thr_g, thr_s, S, E, d, group, chunk, v0,
                                         v1, gs, Xt);
   } else {
-    sweep_pull_body<JM, TPW, false, HUB>(gmem(d.grow), gmem(d.gcol), Jc, thr_g, thr_s, S, E, d, group, chunk, v0,
+    sweep_pull_body<JM, TPW, false, HUB>(cmem(d.grow), cmem(d.gcol), Jc, thr_g, thr_s, S, E, d, group, chunk, v0,
                                          v1, gs, Xt);
   }
 }
@@ -720,11 +718,11 @@ __global__ void __launch_bounds__(NW * 64) k_sweep_tmma_g(const Desc* __restrict
 // coalesced no-return atomic.  Used where gathering is dearer (high degree,
 // hub vertices).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void sweep_push_body(const PAMC_GLOBAL int32_t* __restrict__ row_ptr,
-                                                const PAMC_GLOBAL int32_t* __restrict__ col,
-                                                const PAMC_GLOBAL int32_t* __restrict__ Jc,
-                                                const PAMC_GLOBAL int32_t* __restrict__ class_ptr,
-                                                const PAMC_GLOBAL int32_t* __restrict__ order,
+__device__ __forceinline__ void sweep_push_body(const PAMC_CONST int32_t* __restrict__ row_ptr,
+                                                const PAMC_CONST int32_t* __restrict__ col,
+                                                const PAMC_CONST int32_t* __restrict__ Jc,
+                                                const PAMC_CONST int32_t* __restrict__ class_ptr,
+                                                const PAMC_CONST int32_t* __restrict__ order,
                                                 const PAMC_GLOBAL uint32_t* __restrict__ thr_g, const Desc& d,
                                                 int lb, int sweep_idx, int phase) {
   __shared__ int64_t red[kSweepWaves][kLanes];
@@ -753,7 +751,6 @@ __device__ __forceinline__ void sweep_push_body(const PAMC_GLOBAL int32_t* __res
   if (thr_lds)
     for (int i = threadIdx.x; i <= 2 * Xt; i += blockDim.x) thr_s[i] = thr_g[i];
   __syncthreads();
-  const uint32_t* __restrict__ thr = thr_lds ? thr_s : (const uint32_t*)thr_g;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t r = (uint32_t)(tile * kLanes + lane);
@@ -798,7 +795,7 @@ __device__ __forceinline__ void sweep_push_body(const PAMC_GLOBAL int32_t* __res
         const int32_t s = (int32_t)(int8_t)(sw >> (8 * k));
         const int32_t x = s * h;
         const int32_t xi = x < -Xt ? -Xt : (x > Xt ? Xt : x);
-        const uint32_t T = thr[xi + Xt];
+        const uint32_t T = thr_lds ? thr_s[xi + Xt] : thr_g[xi + Xt];
         const bool flip = (rule == 1 && x <= 0) || (pick(rnd, k) < T);
         const int32_t snew = -s;
         if (flip) {
@@ -839,7 +836,7 @@ __global__ void __launch_bounds__(256) k_sweep_push(const Desc* __restrict__ D,
   const Desc& d = D[inst];
   const PAMC_GLOBAL RunState* __restrict__ st = gmem((const RunState*)d.st);
   if (!st->active || sweep_idx >= st->nsweeps_now || phase >= d.ncls) return;
-  sweep_push_body(gmem(d.row_ptr), gmem(d.col), gmem(d.J), gmem(d.class_ptr), gmem((const int32_t*)d.order),
+  sweep_push_body(cmem(d.row_ptr), cmem(d.col), cmem(d.J), cmem(d.class_ptr), cmem((const int32_t*)d.order),
                   gmem((const uint32_t*)d.thr), d, lb, sweep_idx, phase);
 }
 
@@ -863,9 +860,9 @@ __global__ void __launch_bounds__(256) k_sweep_push(const Desc* __restrict__ D,
 // ---------------------------------------------------------------------------
 template <int K>
 __device__ __forceinline__ int32_t syn_of(const int32_t (&syn)[K], int k) {
-  int32_t x = syn[0];
+  int32_t x = 0;  // every entry is read, none indexed by k (see the uniform words in k_sweep_potts)
 #pragma unroll
-  for (int i = 1; i < K; ++i) x = k == i ? syn[i] : x;
+  for (int i = 0; i < K; ++i) x |= syn[i] & -(int32_t)(k == i);
   return x;
 }
 
@@ -908,73 +905,94 @@ __device__ __forceinline__ int potts_choose(const int32_t (&syn)[K], const uint3
 
 constexpr int kPottsTabLds = 1024;  // doubles of the weight table kept in LDS (8 KB: occupancy)
 
-// K-label field of one vertex from the gathered CSR (rows padded to
-// multiples of 4 entries with coupling 0; columns as the byte offset of the
-// neighbour's label word in a tile plus its byte index), four neighbours per
-// step: two 16-byte scalar loads and four buffer loads.
-template <int K>
-__device__ __forceinline__ void gather_labels(const PAMC_GLOBAL int32_t* __restrict__ gcol,
-                                              const PAMC_GLOBAL int32_t* __restrict__ gJ, int e0, int e1,
-                                              __amdgpu_buffer_rsrc_t Sr, int voff, int32_t (&syn)[K]) {
-#pragma unroll
-  for (int c = 0; c < K; ++c) syn[c] = 0;
-  for (int e = e0; e < e1; e += 4) {
-    const i32x4 cj = *reinterpret_cast<const PAMC_GLOBAL i32x4*>(gcol + e);
-    const i32x4 cJ = *reinterpret_cast<const PAMC_GLOBAL i32x4*>(gJ + e);
-    const int j[4] = {__builtin_amdgcn_readfirstlane(cj.x), __builtin_amdgcn_readfirstlane(cj.y),
-                      __builtin_amdgcn_readfirstlane(cj.z), __builtin_amdgcn_readfirstlane(cj.w)};
-    const int32_t c4[4] = {__builtin_amdgcn_readfirstlane(cJ.x), __builtin_amdgcn_readfirstlane(cJ.y),
-                           __builtin_amdgcn_readfirstlane(cJ.z), __builtin_amdgcn_readfirstlane(cJ.w)};
-    uint32_t w[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) w[u] = __builtin_amdgcn_raw_buffer_load_b32(Sr, voff, j[u] & ~3, 0);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint32_t lab = __builtin_amdgcn_ubfe(w[u], 8u * (uint32_t)(j[u] & 3), 8u);
-#pragma unroll
-      for (int c = 0; c < K; ++c) syn[c] += lab == (uint32_t)c ? c4[u] : 0;
-    }
-  }
-}
-
-// The same field when every |syn_k| fits W = 32 / K bits less one (X <
-// 2^(W-1)): the K sums are kept as W-bit fields of one 32-bit integer, sum_j
-// J_vj 2^(W label_j), so a neighbour costs a shift and an add instead of K
+// K-label fields of the vertices of a quad from the gathered CSR (rows padded
+// to multiples of 4 entries with coupling 0; columns as the byte offset of the
+// neighbour's label word in a tile plus its byte index).  The four rows lie
+// one after another (vertex k's from entry row[k] to row[k + 1]; empty outside
+// the class), so the walk takes kAhead groups of four entries together
+// wherever the rows meet, with all their label words in flight, and notes the
+// running sum at each row's end.
+//
+// PACKED, when every |syn_k| fits W = 32 / K bits less one (X < 2^(W-1)): the
+// K sums are kept as W-bit fields of one 32-bit integer, sum_j J_vj 2^(W
+// label_j), so a neighbour costs a shift and an add instead of K
 // compare-select-adds; the fields are taken apart at the end, each as the
-// sign-extended low W bits of what remains (exact: the integer is
-// sum_k syn_k 2^(W k) with every |syn_k| < 2^(W-1), which fits 32 bits).
-template <int K>
-__device__ __forceinline__ void gather_labels_packed(const PAMC_GLOBAL int32_t* __restrict__ gcol,
-                                                     const PAMC_GLOBAL int32_t* __restrict__ gJ, int e0, int e1,
-                                                     __amdgpu_buffer_rsrc_t Sr, int voff, int32_t (&syn)[K]) {
-  constexpr int W = 32 / K;
-  uint32_t acc = 0;
-  for (int e = e0; e < e1; e += 4) {
-    const i32x4 cj = *reinterpret_cast<const PAMC_GLOBAL i32x4*>(gcol + e);
-    const i32x4 cJ = *reinterpret_cast<const PAMC_GLOBAL i32x4*>(gJ + e);
-    const int j[4] = {__builtin_amdgcn_readfirstlane(cj.x), __builtin_amdgcn_readfirstlane(cj.y),
-                      __builtin_amdgcn_readfirstlane(cj.z), __builtin_amdgcn_readfirstlane(cj.w)};
-    const uint32_t c4[4] = {(uint32_t)__builtin_amdgcn_readfirstlane(cJ.x),
-                            (uint32_t)__builtin_amdgcn_readfirstlane(cJ.y),
-                            (uint32_t)__builtin_amdgcn_readfirstlane(cJ.z),
-                            (uint32_t)__builtin_amdgcn_readfirstlane(cJ.w)};
-    uint32_t w[4];
+// sign-extended low W bits of what remains (exact: a row's integer is sum_k
+// syn_k 2^(W k) with every |syn_k| < 2^(W-1), which fits 32 bits, and
+// differences of the running sums hold modulo 2^32).
+//
+// A wave's chain of reads bounds it (one quad per wave: n = 7,000, degree 6,
+// R = 2,048 is 13 waves a SIMD).  With one row after another, through vector
+// loads of its entries, a phase took 38 us; the four rows together with the
+// entries from scalar loads, and no array in LDS (see the uniform words
+// below), take 22.
+template <int K, bool PACKED>
+__device__ __forceinline__ void gather_labels(const PAMC_CONST int32_t* __restrict__ gcol,
+                                              const PAMC_CONST int32_t* __restrict__ gJ, const int (&row)[5],
+                                              __amdgpu_buffer_rsrc_t Sr, int voff, int32_t (&syn)[4][K]) {
+  constexpr int kAhead = 4, W = 32 / K, N = PACKED ? 1 : K;
+  uint32_t run[N], at_end[4][N];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) w[u] = __builtin_amdgcn_raw_buffer_load_b32(Sr, voff, j[u] & ~3, 0);
+  for (int n = 0; n < N; ++n) {
+    run[n] = 0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint32_t lab = __builtin_amdgcn_ubfe(w[u], 8u * (uint32_t)(j[u] & 3), 8u);
-      acc += c4[u] << (W * lab);
+    for (int k = 0; k < 4; ++k) at_end[k][n] = 0;
+  }
+  for (int e = row[0]; e < row[4]; e += 4 * kAhead) {
+    int j[kAhead][4];
+    uint32_t c[kAhead][4], w[kAhead][4];
+#pragma unroll
+    for (int g = 0; g < kAhead; ++g) {
+      const int at = min(e + 4 * g, row[4] - 4);  // past the last row: its last group again, not counted
+      const i32x4 cj = *reinterpret_cast<const PAMC_CONST i32x4*>(gcol + at);
+      const i32x4 cJ = *reinterpret_cast<const PAMC_CONST i32x4*>(gJ + at);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        j[g][u] = cj[u];
+        c[g][u] = (uint32_t)cJ[u];
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < kAhead; ++g)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) w[g][u] = __builtin_amdgcn_raw_buffer_load_b32(Sr, voff, j[g][u] & ~3, 0);
+#pragma unroll
+    for (int g = 0; g < kAhead; ++g) {
+      const int p = e + 4 * g + 4;
+      if (p > row[4]) break;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t lab = __builtin_amdgcn_ubfe(w[g][u], 8u * (uint32_t)(j[g][u] & 3), 8u);
+        if constexpr (PACKED) {
+          run[0] += c[g][u] << (W * lab);
+        } else {
+#pragma unroll
+          for (int n = 0; n < K; ++n) run[n] += lab == (uint32_t)n ? c[g][u] : 0u;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (p == row[k + 1])
+#pragma unroll
+          for (int n = 0; n < N; ++n) at_end[k][n] = run[n];
     }
   }
-  int32_t rest = (int32_t)acc;
 #pragma unroll
-  for (int k = 0; k < K - 1; ++k) {
-    const int32_t f = (int32_t)((uint32_t)rest << (32 - W)) >> (32 - W);
-    syn[k] = f;
-    rest = (rest - f) >> W;
+  for (int k = 0; k < 4; ++k) {
+    if constexpr (PACKED) {
+      int32_t rest = (int32_t)(at_end[k][0] - (k ? at_end[k - 1][0] : 0u));
+#pragma unroll
+      for (int n = 0; n < K - 1; ++n) {
+        const int32_t f = (int32_t)((uint32_t)rest << (32 - W)) >> (32 - W);
+        syn[k][n] = f;
+        rest = (rest - f) >> W;
+      }
+      syn[k][K - 1] = rest;
+    } else {
+#pragma unroll
+      for (int n = 0; n < K; ++n) syn[k][n] = (int32_t)(at_end[k][n] - (k ? at_end[k - 1][n] : 0u));
+    }
   }
-  syn[K - 1] = rest;
 }
 
 template <int K>
@@ -989,9 +1007,9 @@ __global__ void __launch_bounds__(256) k_sweep_potts(const Desc* __restrict__ D,
   const Desc& d = D[inst];
   const PAMC_GLOBAL RunState* __restrict__ st = gmem((const RunState*)d.st);
   if (!st->active || sweep_idx >= st->nsweeps_now || phase >= d.ncls) return;
-  const PAMC_GLOBAL int32_t* __restrict__ grow = gmem(d.grow);
-  const PAMC_GLOBAL int32_t* __restrict__ gcol = gmem(d.gcol);
-  const PAMC_GLOBAL int32_t* __restrict__ gJ = gmem(d.gJ);
+  const PAMC_CONST int32_t* __restrict__ grow = cmem(d.grow);
+  const PAMC_CONST int32_t* __restrict__ gcol = cmem(d.gcol);
+  const PAMC_CONST int32_t* __restrict__ gJ = cmem(d.gJ);
   const PAMC_GLOBAL int32_t* __restrict__ class_ptr = gmem(d.class_ptr);
   const int cur = st->cur;
   PAMC_GLOBAL uint32_t* __restrict__ S = gmem(cur ? d.S1 : d.S0);
@@ -1030,29 +1048,29 @@ __global__ void __launch_bounds__(256) k_sweep_potts(const Desc* __restrict__ D,
     const uint32_t sw0 = sw;
     // the four fields first (the class's vertices do not see each other)
     int32_t synq[4][K];
+    int row[5];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int v = 4 * q + k;
-      const bool in = v >= v0 && v < v1;
-      if (packed)
-        gather_labels_packed<K>(gcol, gJ, in ? grow[v] : 0, in ? grow[v + 1] : 0, Sr, voff, synq[k]);
-      else
-        gather_labels<K>(gcol, gJ, in ? grow[v] : 0, in ? grow[v + 1] : 0, Sr, voff, synq[k]);
-    }
+    for (int k = 0; k < 5; ++k) row[k] = grow[min(max(4 * q + k, v0), v1)];
+    if (packed)
+      gather_labels<K, true>(gcol, gJ, row, Sr, voff, synq);
+    else
+      gather_labels<K, false>(gcol, gJ, row, Sr, voff, synq);
     // uniform words: W per visit (K, or 2 for the cascade); the quad's
     // visits share W Philox blocks (quad, sweep, replica, POTTS | b << 8),
     // read as one sequence, vertex k of the quad taking words k W .. k W + W-1
+    // (both sequences' words are read before the choice between them: an
+    // array indexed by the rule would be moved to LDS, with every work-group
+    // reading its shape from the dispatch packet in host memory, 7 to 12 us)
     uint32_t uw[4 * K];
     const bool cascade = K == 3 && rule == 1;
 #pragma unroll
     for (int b = 0; b < K; ++b) {
-      if (b < 2 || !cascade) {
-        const u32x4 w = philox10((uint32_t)q, gs, r, kTagPotts | ((uint32_t)b << 8), d.k0, d.k1);
-        uw[4 * b] = w.a;
-        uw[4 * b + 1] = w.b;
-        uw[4 * b + 2] = w.c;
-        uw[4 * b + 3] = w.d;
-      }
+      u32x4 w = {0, 0, 0, 0};
+      if (b < 2 || !cascade) w = philox10((uint32_t)q, gs, r, kTagPotts | ((uint32_t)b << 8), d.k0, d.k1);
+      uw[4 * b] = w.a;
+      uw[4 * b + 1] = w.b;
+      uw[4 * b + 2] = w.c;
+      uw[4 * b + 3] = w.d;
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -1063,7 +1081,10 @@ __global__ void __launch_bounds__(256) k_sweep_potts(const Desc* __restrict__ D,
         for (int c = 0; c < K; ++c) syn[c] = synq[k][c];
         uint32_t u[K];
 #pragma unroll
-        for (int c = 0; c < K; ++c) u[c] = cascade ? (c < 2 ? uw[2 * k + c] : 0u) : uw[K * k + c];
+        for (int c = 0; c < K; ++c) {
+          const uint32_t own = uw[K * k + c], two = c < 2 ? uw[2 * k + c] : 0u;
+          u[c] = cascade ? two : own;
+        }
         const int old = (int)((sw >> (8 * k)) & 0xFFu);
         const int nw = potts_choose<K>(syn, u, tab, last, rule, gamma);
         if (nw != old) {
