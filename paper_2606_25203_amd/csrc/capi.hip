@@ -200,6 +200,20 @@ pamc::Batch* self_batch(pamc_instance* I, hipError_t* err) {
   return I->self;
 }
 
+// Before a run (or, for several calls alike, a sweep call) of this many sweeps
+// per step: the batch is rebuilt where that changes its launches.
+void self_for_sweeps(pamc_instance* I, int32_t sweeps, bool run) {
+  if (I->dense || I->bits != 1 || I->bits_always) return;
+  const int32_t least = pamc::bits_min_sweeps(std::vector<pamc_instance*>{I});
+  if ((sweeps >= least) == (I->self_sweeps >= least)) {
+    I->self_other = 0;
+  } else if (run || I->self_dirty || ++I->self_other >= 3) {
+    I->self_sweeps = sweeps;
+    I->self_other = 0;
+    I->self_dirty = true;
+  }
+}
+
 #define SELF_BATCH(I, var)                                  \
   hipError_t var##_err;                                     \
   pamc::Batch* var = self_batch(I, &var##_err);             \
@@ -224,6 +238,7 @@ struct HostSparse {
   int64_t nnz = 0, W = 0, X = 0;
   std::vector<int32_t> class_ptr, to_internal, to_input, rp2, col2, J2, grow, gcol, gJ, hubJ;
   int32_t bits_ok = 0, bits = 0, bcoup = 0, bcopies = 1, bmaxdeg = 0, bstride = 0;  // bit-packed sweeps
+  bool bits_always = false;
   int32_t allow_bits = 1;  // set by the caller
   std::vector<int32_t> brows, bent;
 };
@@ -564,7 +579,10 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
   // Bit-packed sweeps leave the matrix-core tile form to lone instances and
   // small batches, whose step it makes in one launch (PAMC_BITS = 1: not even
   // that).
-  if (h.bits_ok) h.bits = h.tile == 2 && !(be && atoi(be) == 1) ? 2 : 1;
+  if (h.bits_ok) {
+    h.bits_always = be && atoi(be) == 1;
+    h.bits = h.tile == 2 && !h.bits_always ? 2 : 1;
+  }
   // Tiles per wavefront: share the per-vertex scalar work among up to 4
   // tiles while keeping enough work-groups (one quad per wave) to fill the
   // chip.  Then quads per wave: the most (fewer partial energy sums) that
@@ -622,6 +640,7 @@ std::string tune_key(const pamc_instance* I) {
 void apply_shape(pamc_instance* I, const TuneShape& t) {
   I->tile = t.tile;
   I->bits = t.bits;
+  I->bits_always = t.bits == 1;
   I->tpw = t.tpw;
   I->qpw = t.qpw;
   if (I->dual && !I->pull) {  // the incremental-field form's shape
@@ -669,6 +688,7 @@ pamc_status upload_sparse(pamc_instance* I, HostSparse& h) {
   I->push_qpw = h.push_qpw;
   I->bits_ok = h.bits_ok;
   I->bits = h.bits;
+  I->bits_always = h.bits_always;
   I->bcoup = h.bcoup;
   I->bcopies = h.bcopies;
   I->bmaxdeg = h.bmaxdeg;
@@ -1262,6 +1282,7 @@ pamc_status pamc_sweep(pamc_instance* I, double beta, int32_t nsweeps) {
   if (I->potts_K && beta < 0) return fail(PAMC_ERR_INVALID_ARG, "negative beta on Potts labels");
   if (nsweeps == 0) return PAMC_OK;
   hipSetDevice(I->device);
+  self_for_sweeps(I, nsweeps, false);
   SELF_BATCH(I, b);
   if (I->dense) {
     HIP_TRY(pamc::launch_dense_prim_sweep(*b, beta, nsweeps), "dense sweep");
@@ -1453,6 +1474,7 @@ pamc_status pamc_anneal(pamc_instance* I, const pamc_schedule* sched, pamc_resul
     st = set_field_mode(I, true);
     if (st) return st;
   }
+  self_for_sweeps(I, s.sweeps, true);
   SELF_BATCH(I, b);
   auto run_flags = [&](pamc::Batch* x) {
     x->max_sweeps = std::max(s.sweeps, 1);

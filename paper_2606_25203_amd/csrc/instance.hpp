@@ -101,7 +101,8 @@ struct pamc_instance {
   int32_t order_cap = 0;
   // bit-packed sweeps: every coupling is +-|bcoup| (bits.hip)
   int32_t bits_ok = 0;      // possible
-  int32_t bits = 0;         // taken for the sweeps: 1 always, 2 in large batches
+  int32_t bits = 0;         // taken for the sweeps: 1 by bits_min_sweeps, 2 in large batches
+  bool bits_always = false; // bits == 1 whatever the sweeps per step
   int32_t bcoup = 0;        // the coupling's magnitude; negative when every coupling is
   int32_t bcopies = 1;      // 2: couplings of both signs, masks kept with their complements
   int32_t bmaxdeg = 0;      // the longest row
@@ -151,6 +152,8 @@ struct pamc_instance {
   // the instance as a batch of one (rebuilt when a buffer it names changes)
   pamc::Batch* self = nullptr;
   bool self_dirty = true;
+  int32_t self_sweeps = 1 << 30;  // sweeps per step that its launches were chosen for
+  int32_t self_other = 0;         // sweep calls in a row that other launches would suit
   void* d_sched = nullptr;  // device copy of the run's schedule
   int64_t* pair_out = nullptr;  // pair-distance histogram and sum (allocated at its first call)
 };
@@ -335,6 +338,9 @@ hipError_t launch_refresh_fields(Batch& b);
 // nbins), their sum after them
 hipError_t launch_pair_hist(pamc_instance* I, int32_t nbins, int64_t* out_dev);
 int32_t cluster_max_n();
+// The fewest sweeps per step from which instances of bits == 1 sweep
+// bit-packed as one batch.
+int32_t bits_min_sweeps(const std::vector<pamc_instance*>& insts);
 int32_t sweep_waves();  // wavefronts per sweep work-group
 int32_t tile_max_quads();  // vertex quads a tile-resident sweep holds in LDS
 int64_t tile_lds_bytes(int32_t nq, int32_t rows);  // its LDS: spins, table, a class's gathered rows

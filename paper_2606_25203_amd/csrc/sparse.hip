@@ -37,6 +37,7 @@ constexpr int kClusterMaxN = 26000;        // LDS: 5 bytes per vertex
 constexpr int kRsMaxR = 16384;
 constexpr int kThrLds = 2048;              // threshold entries staged in LDS when they fit
 constexpr int kThrBlocks = 16;             // threshold work-groups per instance
+constexpr int kOrderLds = 2048;            // class-order entries shuffled in LDS at a time
 constexpr int kInitBlocks = 64;            // spin-init work-groups per instance
 constexpr int kApplyChunks = 16;           // cluster-apply work-groups per target
 constexpr int kFieldBlocks = 1024;         // max field-init work-groups per instance
@@ -1396,24 +1397,61 @@ __global__ void __launch_bounds__(256) k_thresholds(const Desc* __restrict__ D,
       d.thr[i] = flip_threshold(beta, d.rule, i - Xt);
   }
   if (lb == 0 && d.ncls > 0) {
-    const int nsw = min(st->nsweeps_now, d.order_cap);
-    for (int s = threadIdx.x; s < nsw; s += blockDim.x) {
-      int32_t* o = d.order + (size_t)s * d.ncls;
-      for (int k = 0; k < d.ncls; ++k) o[k] = k;
-      if (d.shuffle) {
+    const int nsw = min(st->nsweeps_now, d.order_cap), ncls = d.ncls;
+    if (ncls <= kOrderLds) {
+      // as many sweeps at a time as LDS holds: their draws and results by all
+      // threads, each sweep's exchanges by one (a chain of reads and writes
+      // that took a microsecond a class in memory)
+      __shared__ int32_t perm[kOrderLds], with[kOrderLds];
+      const int per = kOrderLds / ncls;
+      for (int s0 = 0; s0 < nsw; s0 += per) {
+        const int ns = min(per, nsw - s0);
+        for (int i = threadIdx.x; i < ns * ncls; i += blockDim.x) {
+          const int k = i % ncls;
+          perm[i] = k;
+          if (d.shuffle) {
+            const u32x4 w = philox10((uint32_t)k, st->gs + (uint32_t)(s0 + i / ncls), 0u, kTagOrder, d.k0, d.k1);
+            with[i] = (int)(((uint64_t)w.a * (uint64_t)(k + 1)) >> 32);
+          }
+        }
+        __syncthreads();
+        if (d.shuffle)
+          for (int s = threadIdx.x; s < ns; s += blockDim.x) {
+            int32_t* o = perm + s * ncls;
+            for (int i = ncls - 1; i >= 1; --i) {
+              const int j = with[s * ncls + i];
+              const int32_t t = o[i];
+              o[i] = o[j];
+              o[j] = t;
+            }
+          }
+        __syncthreads();
+        for (int i = threadIdx.x; i < ns * ncls; i += blockDim.x) {
+          const int32_t c = perm[i];
+          d.order[s0 * ncls + i] = c;
+          if (d.bits)  // the phases in visiting order
+            reinterpret_cast<int4*>(d.bphases)[s0 * ncls + i] =
+                make_int4(d.class_ptr[c], d.class_ptr[c + 1], (int32_t)(st->gs + (uint32_t)(s0 + i / ncls)), st->cur);
+        }
+        __syncthreads();
+      }
+    } else {
+      for (int s = threadIdx.x; s < nsw; s += blockDim.x) {
+        int32_t* o = d.order + (size_t)s * ncls;
+        for (int k = 0; k < ncls; ++k) o[k] = k;
         const uint32_t gs = st->gs + (uint32_t)s;
-        for (int i = d.ncls - 1; i >= 1; --i) {
+        for (int i = d.shuffle ? ncls - 1 : 0; i >= 1; --i) {
           const u32x4 w = philox10((uint32_t)i, gs, 0u, kTagOrder, d.k0, d.k1);
           const int j = (int)(((uint64_t)w.a * (uint64_t)(i + 1)) >> 32);
           const int32_t t = o[i];
           o[i] = o[j];
           o[j] = t;
         }
+        if (d.bits)
+          for (int k = 0; k < ncls; ++k)
+            reinterpret_cast<int4*>(d.bphases)[(size_t)s * ncls + k] =
+                make_int4(d.class_ptr[o[k]], d.class_ptr[o[k] + 1], (int32_t)gs, st->cur);
       }
-      if (d.bits)  // the phases in visiting order
-        for (int k = 0; k < d.ncls; ++k)
-          reinterpret_cast<int4*>(d.bphases)[(size_t)s * d.ncls + k] =
-              make_int4(d.class_ptr[o[k]], d.class_ptr[o[k] + 1], (int32_t)(st->gs + (uint32_t)s), st->cur);
     }
     if (d.bits)  // sweeps that other instances of a batch still make
       for (int i = nsw * d.ncls + threadIdx.x; i < d.order_cap * d.ncls; i += blockDim.x)
@@ -2584,6 +2622,44 @@ static int64_t field_blocks(const pamc_instance* I) {
   return std::min<int64_t>((int64_t)I->T * ((I->n + 63) / 64), kFieldBlocks);
 }
 
+// A step pays for packing the spins and for unpacking them with their
+// energies (11 us for small instances, about two sweeps' gain for large ones),
+// each sweep of it gains.  Times of 20 steps without and with bit-packed
+// sweeps, one instance:
+// - against the gathered per-class launches (each phase gains with the length
+//   of the rows): G(5000, degree 5), R = 1024, 1, 2, 3, 5 sweeps a step: 1.75 and
+//   2.02, 2.35 and 2.42, 2.91 and 2.86, 4.10 and 3.79 ms; G(20000, degree 9), R =
+//   1024: 3.53 and 3.97, 5.51 and 5.27, 7.46 and 6.57, 11.3 and 9.2; G(2000, degree
+//   30), R = 256, 1 and 5: 3.64 and 2.63, 13.0 and 7.3 ms;
+// - against a work-group per tile for the whole step, whose sweep takes about n
+//   (0.02 + 0.0023 degree) + classes us where a bit-packed one takes 4.3 us a
+//   class: G(300, degree 7), R = 256, 1 and 5: 1.36 and 1.59, 2.49 and 3.04 ms;
+//   G(600, degree 7): 1.53 and 1.65, 3.43 and 3.15; G(1200, degree 7): 1.94 and
+//   1.55, 5.24 and 2.84 ms.
+int32_t bits_min_sweeps(const std::vector<pamc_instance*>& insts) {
+  constexpr int32_t kNever = INT32_MAX;
+  bool tiles = true;  // every one could sweep in tiles
+  double tile_us = 0, degree = 0;
+  int64_t all_tiles = 0;
+  int32_t ncls = 0, count = 0;
+  for (const pamc_instance* I : insts) {
+    if (I->dense || I->bits != 1) continue;
+    const double deg = I->n > 0 ? (double)I->nnz / I->n : 0.0;
+    tiles = tiles && I->tile == 1;
+    tile_us = std::max(tile_us, I->n * (0.02 + 0.0023 * deg) + I->ncls);
+    degree = std::max(degree, deg);
+    ncls = std::max(ncls, I->ncls);
+    all_tiles += I->T;
+    ++count;
+  }
+  if (!count) return kNever;
+  if (tiles) {
+    const double gain = tile_us * (double)((all_tiles + kComputeUnits - 1) / kComputeUnits) - 4.3 * ncls;
+    return gain > 0.05 ? (int32_t)std::ceil(11.0 / gain) : kNever;
+  }
+  return degree >= 20.0 ? 1 : (degree >= 8.0 ? 2 : 3);
+}
+
 static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts, const std::vector<Schedule>* scheds,
                               bool allow_bits) {
   // the old maps may still be read by queued kernels
@@ -2603,9 +2679,14 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
   int64_t mfma_tiles = 0;
   for (const pamc_instance* I : insts)
     if (!I->dense && I->tile == 2) mfma_tiles += I->T;
+  int32_t most_sweeps = b.n == 1 && !scheds ? insts[0]->self_sweeps : 1;
+  if (scheds)
+    for (const Schedule& s : *scheds) most_sweeps = std::max(most_sweeps, s.sweeps);
+  const bool enough = most_sweeps >= bits_min_sweeps(insts);
   auto sweeps_bits = [&](int i) {
     const pamc_instance* I = insts[i];
-    return allow_bits && !I->dense && (I->bits == 1 || (I->bits == 2 && mfma_tiles > kMfmaGroupTiles));
+    return allow_bits && !I->dense &&
+           ((I->bits == 1 && (enough || I->bits_always)) || (I->bits == 2 && mfma_tiles > kMfmaGroupTiles));
   };
   bool any_bits = false;
   for (int i = 0; i < b.n; ++i) {
@@ -2709,36 +2790,40 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
                      [&](int x, int y) { return insts[x]->ncls > insts[y]->ncls; });
     int64_t quads = 0;  // quads x tiles of a phase, over the batch
     for (int i : bit_insts) quads += (int64_t)insts[i]->T * insts[i]->max_class_quads;
-    // Rows of at most four entries that fill the chip: a quad per wave, else
-    // a quad per work-group.  A scalar load costs a compute unit about 8
-    // cycles whatever its width, so wide tile groups pay once there are
-    // enough quads to go round.  Runs timed with groups of 1, 2 and 4 tiles:
-    // 100 x 200 torus, R = 4096 (160,000 quads x tiles a phase), 120 steps x
-    // 10 sweeps: 200, 107 and 89 ms with a quad per wave, 190 ms with a quad
-    // per work-group of 4 tiles; G(11999, degree 34), R = 512 (2,000): 37.6,
-    // 30.6 and 31.7 ms; G(5003, degree 9), R = 512: 15.2, 13.6 and 14.1 ms; 32
-    // served requests at once: 378, 287 and 248 ms.  Quads per wave on the
-    // torus: 1 90.6, 2 89.2, 3 88.5, 4 91.1, 5 92.9 ms.
-    int form = quads >= 8192 ? 5 : 1;
-    int qpw = quads >= 65536 ? 2 : 1;
+    // Rows of at most four entries: a quad per wave, else a quad per
+    // work-group.  A scalar load costs a compute unit about 8 cycles whatever its
+    // width, so wide tile groups pay once there are enough quads to go round.
+    // Runs timed with groups of 1, 2 and 4 tiles, a quad per wave: torus 60 x 60,
+    // R = 512 (3,600 quads x tiles a phase): 1.95, 2.13 and 2.35 ms; R = 4096
+    // (28,800): 4.68, 3.95 and 3.71; 100 x 200, R = 4096 (160,000): 200, 107 and 89.
+    // A quad per work-group: G(2000, degree 7), R = 256 (500): 2.65, 2.86 and
+    // 3.16 ms; G(11999, degree 34), R = 512 (2,000): 37.6, 30.6 and 31.7; G(5000,
+    // degree 5), R = 1024 (4,000): 5.78, 4.25 and 3.79.  Quads per wave or
+    // work-group, 1 and 2: the last 3.79 and 4.04 ms; G(20000, degree 5), R = 1024
+    // (16,000) 8.15 and 7.77; the large torus 90.6 and 89.2 (3: 88.5, 4: 91.1).
+    int qpw = 0, form = -1;
     if (const char* e = getenv("PAMC_BITS_FORM")) form = std::min(5, std::max(0, atoi(e)));
     if (const char* e = getenv("PAMC_BITS_QPW")) qpw = std::max(1, atoi(e));
-    int uq = 4;
+    int uq = 0;
     if (const char* e = getenv("PAMC_BITS_UQ")) uq = std::max(1, atoi(e));
     for (int i : bit_insts) {
       const pamc_instance* I = insts[i];
-      int f = form;
+      int f = form, qw = qpw, u = uq;
+      if (f < 0 && I->bstride == 4) f = quads < 8192 ? 3 : 5;
+      if (f < 0) f = quads < 1000 ? 0 : (quads < 2500 ? 1 : 2);
       if (f >= 3 && I->bstride != 4) f -= 3;
+      if (!qw) qw = quads >= (I->bstride == 4 ? 65536 : 12000) ? 2 : 1;
+      if (!u) u = I->nq >= 4096 ? 8 : 4;  // G(20000, degree 9), R = 64: 2.24 and 2.03 ms; n = 5,000: 2.05 and 2.11
       while (f % 3 > 0 && I->T % (f % 3 == 2 ? 4 : 2) != 0) --f;
       const int G = 1 << (f % 3);
       std::vector<uint64_t>& m = m_bits[I->rule * Batch::kBitForms + f];
       std::vector<int32_t>& grid = b.bit_grid[I->rule][f];
-      add_blocks(m, i, (int64_t)(I->T / G) * bits_work_groups(I->max_class_quads, qpw, f < 3), true);
+      add_blocks(m, i, (int64_t)(I->T / G) * bits_work_groups(I->max_class_quads, qw, f < 3), true);
       if ((int)grid.size() < I->ncls) grid.resize(I->ncls);
       for (int p = 0; p < I->ncls; ++p) grid[p] = (int32_t)m.size();
       add_blocks(m_bpack[f], i, (int64_t)(I->T / G) * bits_pack_chunks(I->nq), true);
-      add_blocks(m_bunpack[f], i, (int64_t)(I->T / G) * bits_work_groups(I->nq, uq, f < 3), true);
-      bdesc[i] = make_bit_desc(I, desc[i], qpw, uq);
+      add_blocks(m_bunpack[f], i, (int64_t)(I->T / G) * bits_work_groups(I->nq, u, f < 3), true);
+      bdesc[i] = make_bit_desc(I, desc[i], qw, u);
     }
   }
   // diversity samples: one work-group per replica.  A batch without
