@@ -557,7 +557,7 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
     h.tmma_ok = 1;
     h.nks = (h.np + 63) / 64;
     const int32_t nrt = (h.np + 15) / 16;
-    h.Jt.assign((size_t)nrt * h.nks * 1024, 0);
+    h.Jt.assign(((size_t)nrt * h.nks + 1) * 1024, 0);  // an odd number of columns is read as the next even one
     for (int32_t iv = 0; iv < n; ++iv)
       for (int32_t e = h.rp2[iv]; e < h.rp2[iv + 1]; ++e) {
         const int32_t c = h.col2[e], t = iv >> 4, ks = c >> 6, lane = (iv & 15) + 16 * ((c & 63) >> 4);

@@ -405,15 +405,6 @@ struct SeqLds {
   __attribute__((aligned(16))) int8_t spl[16][kSB + 16];  // the super-block before's spins, final
 };
 
-// Barrier for work-groups whose waves exchange data through LDS only: the
-// waves' LDS writes complete before it, and their global loads and stores
-// in flight stay in flight (a full __syncthreads would wait for those too).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // One work-group per 16 replicas walks the super-block's 64-spin blocks in
 // order.  Wave 0 decides block b from registers while the others prepare
 // block b + 1 and finish block b - 1; one LDS barrier per block.

@@ -30,6 +30,15 @@ __device__ __forceinline__ const PAMC_CONST T* cmem(const T* p) {
   return (const PAMC_CONST T*)p;
 }
 
+// Barrier for work-groups whose waves exchange data through LDS only: the
+// waves' LDS writes complete before it, and their global loads and stores
+// in flight stay in flight (a full __syncthreads would wait for those too).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 constexpr int kLanes = 64;      // replicas per tile = wavefront width
 constexpr int kMaxHubs = 2;     // hub vertices with incrementally kept fields in the gathered-field mode
 constexpr int kHistCap = 64;    // controller history capacity (>= win_long)

@@ -608,90 +608,197 @@ __global__ void __launch_bounds__(NW * 64) k_sweep_tmma(const Desc* __restrict__
 // each holding a quarter of the tile's spins.  Wave w takes the class's
 // 16-row tiles w, w + NW, ...; lane l's replica is 16 g + l % 16 and its
 // quad 4 t + l / 16, as above.
-template <int NW>
-__global__ void __launch_bounds__(NW * 64) k_sweep_tmma_g(const Desc* __restrict__ D,
-                                                          const uint64_t* __restrict__ map) {
-  extern __shared__ uint32_t tl[];  // int8 spins [16][rowb], then the threshold table
-  __shared__ int64_t red[NW][kLanes];
-  __shared__ int32_t fred[NW];
-  int inst, lb;
-  if (!resolve(map, inst, lb)) return;
-  const Desc& d = D[inst];
+//
+// The chain from one class's barrier to the next bounds it, and a unit's rate
+// of reading J (64 bytes a cycle, every work-group all of J in a sweep).  A wave
+// keeps its replicas' spins as B operands in registers and after a barrier
+// reads again only the 64-vertex columns that hold the class just visited; the
+// roles of the waves rotate by half from class to class, so that while some
+// decide a class the others read their couplings, draw their words and
+// multiply the columns that are final for the next.  Row tiles start at the
+// class's first quad, so a class of 64 vertices is four of them.  G(800,
+// 19176), R = 256, 15 classes x 5 sweeps: 84 us, where it took 137 with the
+// loads, words and products of a class all behind its barrier; G(300, 2400), R =
+// 128, 15 x 3: 21 and 33 us.  A quarter, half, three quarters and all of the
+// couplings read by the deciding waves for their next turn: 6.44, 6.28, 6.65 and
+// 6.78 ms a run.
+template <int NW, int NKP, bool METRO>  // NKP: 64-vertex columns, rounded up to even
+__device__ __forceinline__ void sweep_tmma_group(const Desc& d, int lb, uint32_t* tl, int64_t (*red)[kLanes],
+                                                 int32_t* fred) {
   const PAMC_GLOBAL RunState* __restrict__ st = gmem((const RunState*)d.st);
   const int nsw = st->nsweeps_now;
-  if (!st->active || nsw <= 0) return;
   const int tile = lb >> 2, grp = lb & 3;
   const int cur = st->cur;
-  const int nq = d.nq, nks = d.nks;
-  const int rowb = 64 * nks + 16;  // bytes per replica row (padded against bank conflicts)
+  const int nq = d.nq, nks = d.nks, ncls = d.ncls;
+  constexpr int rowb = 64 * NKP + 16;  // bytes per replica row (padded against bank conflicts)
   const int32_t Xt = (int32_t)st->table_x;
   PAMC_GLOBAL uint32_t* __restrict__ S = gmem(cur ? d.S1 : d.S0) + (size_t)tile * nq * kLanes + 16 * grp;
   PAMC_GLOBAL int64_t* __restrict__ E = gmem(cur ? d.E1 : d.E0);
   const PAMC_GLOBAL uint32_t* __restrict__ thr_g = gmem((const uint32_t*)d.thr);
-  const PAMC_GLOBAL int32_t* __restrict__ order = gmem((const int32_t*)d.order);
-  const PAMC_GLOBAL int32_t* __restrict__ class_ptr = gmem(d.class_ptr);
+  const PAMC_CONST int32_t* __restrict__ order = cmem((const int32_t*)d.order);
+  const PAMC_CONST int32_t* __restrict__ class_ptr = cmem(d.class_ptr);
   const PAMC_GLOBAL int8_t* __restrict__ Jt = gmem(d.Jt);
   int8_t* Sb = reinterpret_cast<int8_t*>(tl);
   uint32_t* thr_s = tl + 4 * rowb;  // 16 rowb bytes
-  // the group's spin words (q, 16 grp + c) into replica-major rows
-  for (int i = threadIdx.x; i < nq * 16; i += blockDim.x)
-    *reinterpret_cast<uint32_t*>(Sb + (i & 15) * rowb + 4 * (i >> 4)) = S[(i >> 4) * kLanes + (i & 15)];
-  for (int i = threadIdx.x; i <= 2 * Xt; i += blockDim.x) thr_s[i] = thr_g[i];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15;                  // the lane's replica in the group
   const uint32_t r = (uint32_t)(tile * kLanes + 16 * grp + c);
-  const int kq = lane >> 4;                 // the lane's quad within a 16-row tile
+  const int kq = lane >> 4;                 // the lane's quad within a row tile
   const int8_t* brow = Sb + c * rowb + 16 * kq;  // B operand: replica c, bytes 16 kq ..
-  const bool metropolis = d.rule == 1;
+  const uint32_t k0 = d.k0, k1 = d.k1;
+  const int phases = nsw * ncls;
   int64_t dE = 0;
-  int32_t nflip = 0;
-  for (int sw_i = 0; sw_i < nsw; ++sw_i) {
-    const uint32_t gs = st->gs + (uint32_t)sw_i;
-    for (int p = 0; p < d.ncls; ++p) {
-      const int cls = order[sw_i * d.ncls + p];
-      const int v0 = class_ptr[cls], v1 = class_ptr[cls + 1];
-      const int q0 = v0 >> 2, q1 = (v1 + 3) >> 2;  // the class's quads
-      const int t0 = q0 >> 2, t1 = (q1 + 3) >> 2;  // its 16-row tiles
-      __syncthreads();  // the previous class's spins are in
-      for (int t = t0 + wave; t < t1; t += NW) {
-        const PAMC_GLOBAL int8_t* arow = Jt + ((size_t)t * nks * 64 + lane) * 16;
-        i32x4 av[kTmmaMaxKs];
+  int32_t dEs = 0, nflip = 0;  // dEs: of the sweep, |x| < 2^10 and at most n / 4 spins a lane
+  // a phase's class (empty past the last)
+  struct Class {
+    int v0, v1;
+    __device__ int tiles() const { return (v1 - (v0 & ~3) + 15) >> 4; }
+  };
+  auto class_of = [&](int i) -> Class {
+    if (i >= phases) return {0, 0};
+    const int cls = order[i];
+    return {class_ptr[cls], class_ptr[cls + 1]};
+  };
+  i32x4 av[NKP], bv[NKP];
+  // fragments lo .. hi - 1 of row tile u of a class (rows of other classes are
+  // left as they are: no result of them is used; an odd last column is followed
+  // by other couplings, against spins of 0)
+  auto load_a = [&](const Class& x, int u, int lo, int hi) {
+    const int row = (x.v0 & ~3) + 16 * u + c;
+    const uint32_t at = ((uint32_t)(row >> 4) * nks * 64 + (row & 15) + 16 * kq) * 16;
+    if (row < x.v1)
 #pragma unroll
-        for (int ks = 0; ks < kTmmaMaxKs; ++ks)
-          if (ks < nks) av[ks] = *reinterpret_cast<const PAMC_GLOBAL i32x4*>(arow + (size_t)ks * 1024);
-        const int q = 4 * t + kq;
-        const u32x4 rnd = philox10((uint32_t)q, gs, r, kTagSweep, d.k0, d.k1);
-        __builtin_amdgcn_sched_barrier(0);
-        i32x4 acc = {0, 0, 0, 0};
+      for (int ks = 0; ks < NKP; ++ks)
+        if (ks >= lo && ks < hi)
+          av[ks] = *reinterpret_cast<const PAMC_GLOBAL i32x4*>(Jt + at + 1024 * ks);
+  };
+  auto quad_of = [&](const Class& x, int u) { return (x.v0 >> 2) + 4 * u + kq; };
+  auto word_at = [&](int q) { return reinterpret_cast<uint32_t*>(Sb + c * rowb + 4 * q); };
+  // products over the columns not in the mask
+  auto multiply_rest = [&](uint32_t mask) {
+    i32x4 a0 = {0, 0, 0, 0}, a1 = {0, 0, 0, 0};
 #pragma unroll
-        for (int ks = 0; ks < kTmmaMaxKs; ++ks)
-          if (ks < nks)
-            acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[ks], *reinterpret_cast<const i32x4*>(brow + 64 * ks),
-                                                        acc, 0, 0, 0);
-        if (q < q0 || q >= q1) continue;
-        uint32_t* wp = reinterpret_cast<uint32_t*>(Sb + c * rowb + 4 * q);
-        const uint32_t sw = *wp;
-        uint32_t flipmask = 0;
+    for (int ks = 0; ks < NKP; ++ks)
+      if (!(mask >> ks & 1u)) {
+        if (ks & 1)
+          a1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[ks], bv[ks], a1, 0, 0, 0);
+        else
+          a0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[ks], bv[ks], a0, 0, 0, 0);
+      }
+    return a0 + a1;
+  };
+  // What a visit of a quad needs beside its fields: its spins (after the barrier
+  // of the phase before: they may share a word with, or be, the class visited
+  // there), its words, and which of its vertices are of the class.
+  struct Quad {
+    int q;
+    uint32_t sw, in;
+    u32x4 rnd;
+  };
+  auto quad_ready = [&](const Class& x, int u, uint32_t gs) {
+    Quad z;
+    z.q = quad_of(x, u);
+    z.in = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int v = 4 * q + k;
-          if (v < v0 || v >= v1) continue;
-          const int32_t s = __builtin_amdgcn_sbfe((int32_t)sw, 8u * k, 8u);
-          const int32_t x = __mul24(s, acc[k]);
-          const int32_t xi = min(max(x, -Xt), Xt) + Xt;
-          const bool flip = (pick(rnd, k) < thr_s[xi]) || (metropolis && x <= 0);
-          dE += flip ? (int64_t)x : 0;
-          flipmask |= flip ? (0xFEu << (8 * k)) : 0u;
-          nflip += flip ? 1 : 0;
-        }
-        if (flipmask) *wp = sw ^ flipmask;
+    for (int k = 0; k < 4; ++k) z.in |= (uint32_t)(4 * z.q + k - x.v0) < (uint32_t)(x.v1 - x.v0) ? 0xFEu << (8 * k) : 0u;
+    z.rnd = philox10((uint32_t)z.q, gs, r, kTagSweep, k0, k1);
+    return z;
+  };
+  const uint32_t* thr_mid = thr_s + Xt;
+  auto decide = [&](const Quad& z, const i32x4& h) {
+    uint32_t flipmask = 0;
+    int32_t x[4];
+    uint32_t T[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      x[k] = __mul24(__builtin_amdgcn_sbfe((int32_t)z.sw, 8u * k, 8u), h[k]);
+      T[k] = thr_mid[min(max(x[k], -Xt), Xt)];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      bool flip = pick(z.rnd, k) < T[k];
+      if constexpr (METRO) flip |= x[k] <= 0;
+      const uint32_t m = flip ? z.in & (0xFEu << (8 * k)) : 0u;  // +1 (0x01) <-> -1 (0xFF)
+      dEs += m ? x[k] : 0;
+      flipmask |= m;
+    }
+    nflip += __builtin_popcount(flipmask & 0x02020202u);
+    if (flipmask) *word_at(z.q) = z.sw ^ flipmask;
+  };
+  Class x0 = class_of(0), x1 = class_of(1), x2 = class_of(2);
+  // the group's spin words (q, 16 grp + c) into replica-major rows, 0 past the last
+  for (int i = threadIdx.x; i < 16 * NKP * 16; i += blockDim.x)
+    *reinterpret_cast<uint32_t*>(Sb + (i & 15) * rowb + 4 * (i >> 4)) =
+        (i >> 4) < nq ? S[(i >> 4) * kLanes + (i & 15)] : 0u;
+  for (int i = threadIdx.x; i <= 2 * Xt; i += blockDim.x) thr_s[i] = thr_g[i];
+  // wave w's row tile (if the class has that many; then also every NW-th
+  // after it) in even and odd phases
+  const int j0 = wave, j1 = (wave + NW / 2) % NW;
+  if (j0 < x0.tiles()) load_a(x0, j0, 0, NKP);
+  __syncthreads();
+#pragma unroll
+  for (int ks = 0; ks < NKP; ++ks) bv[ks] = *reinterpret_cast<const i32x4*>(brow + 64 * ks);
+  uint32_t gs = st->gs;
+  int left = ncls;  // phases left in the sweep
+  i32x4 h = {0, 0, 0, 0};
+  Quad z{};
+  bool now = j0 < x0.tiles(), early = false;  // early: the next class's first half is on its way
+  if (now) {
+    z = quad_ready(x0, j0, gs);
+    z.sw = *word_at(z.q);
+    h = multiply_rest(0u);
+  }
+  constexpr int kEarly = NKP / 2;
+  int i = 0;
+  auto phase = [&](int jc, int jn) {  // the wave's row tiles in this phase and the next
+    const Class x3 = class_of(i + 3);
+    const bool next = jn < x1.tiles();
+    if (now) {
+      decide(z, h);
+      for (int u = jc + NW; u < x0.tiles(); u += NW) {  // further row tiles of a large class
+        load_a(x0, u, 0, NKP);
+        z = quad_ready(x0, u, gs);
+        z.sw = *word_at(z.q);
+        decide(z, multiply_rest(0u));
       }
     }
-  }
+    if (--left == 0) {
+      left = ncls;
+      ++gs;
+      dE += dEs;
+      dEs = 0;
+    }
+    // the columns that hold the class (if it has a vertex)
+    const uint32_t mask = x0.v1 > x0.v0 ? (2u << ((x0.v1 - 1) >> 6)) - (1u << (x0.v0 >> 6)) : 0u;
+    if (next) {
+      if (!early) load_a(x1, jn, 0, kEarly);
+      load_a(x1, jn, kEarly, NKP);
+      z = quad_ready(x1, jn, gs);
+      h = multiply_rest(mask);
+    }
+    early = !next && jc < x2.tiles();
+    if (early) load_a(x2, jc, 0, kEarly);
+    lds_barrier();  // the class's spins are in
+    if (next) z.sw = *word_at(z.q);
+#pragma unroll
+    for (int ks = 0; ks < NKP; ++ks)
+      if (mask >> ks & 1u) {
+        bv[ks] = *reinterpret_cast<const i32x4*>(brow + 64 * ks);
+        if (next) h = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[ks], bv[ks], h, 0, 0, 0);
+      }
+    now = next;
+    x0 = x1;
+    x1 = x2;
+    x2 = x3;
+    return ++i < phases;
+  };
+  if (phases > 0)
+    while (phase(j0, j1) && phase(j1, j0)) {
+    }
   __syncthreads();
-  for (int i = threadIdx.x; i < nq * 16; i += blockDim.x)
-    S[(i >> 4) * kLanes + (i & 15)] = *reinterpret_cast<const uint32_t*>(Sb + (i & 15) * rowb + 4 * (i >> 4));
+  for (int j = threadIdx.x; j < nq * 16; j += blockDim.x)
+    S[(j >> 4) * kLanes + (j & 15)] = *reinterpret_cast<const uint32_t*>(Sb + (j & 15) * rowb + 4 * (j >> 4));
   red[wave][lane] = dE;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) nflip += __shfl_xor(nflip, o, 64);
@@ -711,6 +818,38 @@ __global__ void __launch_bounds__(NW * 64) k_sweep_tmma_g(const Desc* __restrict
                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
+}
+
+template <int NW, bool METRO>
+__device__ __forceinline__ void sweep_tmma_groups(const Desc& d, int lb, uint32_t* tl, int64_t (*red)[kLanes],
+                                                  int32_t* fred) {
+  switch ((d.nks + 1) / 2) {
+    case 1: sweep_tmma_group<NW, 2, METRO>(d, lb, tl, red, fred); break;
+    case 2: sweep_tmma_group<NW, 4, METRO>(d, lb, tl, red, fred); break;
+    case 3: sweep_tmma_group<NW, 6, METRO>(d, lb, tl, red, fred); break;
+    case 4: sweep_tmma_group<NW, 8, METRO>(d, lb, tl, red, fred); break;
+    case 5: sweep_tmma_group<NW, 10, METRO>(d, lb, tl, red, fred); break;
+    case 6: sweep_tmma_group<NW, 12, METRO>(d, lb, tl, red, fred); break;
+    case 7: sweep_tmma_group<NW, 14, METRO>(d, lb, tl, red, fred); break;
+    default: sweep_tmma_group<NW, 16, METRO>(d, lb, tl, red, fred); break;
+  }
+}
+
+template <int NW>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_sweep_tmma_g(const Desc* __restrict__ D, const uint64_t* __restrict__ map) {
+  extern __shared__ uint32_t tl[];  // int8 spins [16][rowb], then the threshold table
+  __shared__ int64_t red[NW][kLanes];
+  __shared__ int32_t fred[NW];
+  int inst, lb;
+  if (!resolve(map, inst, lb)) return;
+  const Desc& d = D[inst];
+  const PAMC_GLOBAL RunState* __restrict__ st = gmem((const RunState*)d.st);
+  if (!st->active || st->nsweeps_now <= 0) return;
+  if (d.rule == 1)
+    sweep_tmma_groups<NW, true>(d, lb, tl, red, fred);
+  else
+    sweep_tmma_groups<NW, false>(d, lb, tl, red, fred);
 }
 
 // ---------------------------------------------------------------------------
@@ -2342,7 +2481,10 @@ int32_t tile_max_quads() { return kTileMaxQuads; }
 int64_t tile_lds_bytes(int32_t nq, int32_t rows) { return (int64_t)nq * kLanes * 4 + kThrLds * 4 + 8 * (int64_t)rows; }
 int64_t tile_lds_limit() { return kTileLdsBytes; }
 int32_t tmma_max_n() { return kTmmaMaxN; }
-int64_t tmma_lds_bytes(int32_t nks, int32_t rows) { return rows * (64 * (int64_t)nks + 16) + kThrLds * 4; }
+// (16-row work-groups take an even number of 64-vertex columns)
+int64_t tmma_lds_bytes(int32_t nks, int32_t rows) {
+  return rows * (64 * (int64_t)(rows == 16 ? (nks + 1) / 2 * 2 : nks) + 16) + kThrLds * 4;
+}
 
 // Kernels whose dynamic LDS may exceed the default limit.
 hipError_t prepare_kernel_lds() {
