@@ -152,6 +152,11 @@ struct pamc_instance {
   // the instance as a batch of one (rebuilt when a buffer it names changes)
   pamc::Batch* self = nullptr;
   bool self_dirty = true;
+  // memory of the small buffers made with the instance: pieces of blocks that
+  // are released with it (not with a provider of its own, see dev_alloc)
+  std::vector<char*> blocks;
+  size_t block_used = 0;
+  bool blocking = false;
   int32_t self_sweeps = 1 << 30;  // sweeps per step that its launches were chosen for
   int32_t self_other = 0;         // sweep calls in a row that other launches would suit
   void* d_sched = nullptr;  // device copy of the run's schedule
@@ -296,10 +301,17 @@ struct Batch {
   // hipMalloc); it must outlive the batch
   const pamc_allocator* al = nullptr;
   void free_device();
+  // outside arena mode and without a provider: one block whose pieces the
+  // descriptors and maps take, kept over rebuilds
+  char* block = nullptr;
+  size_t block_used = 0;
   Batch() = default;
   Batch(const Batch&) = delete;
   Batch& operator=(const Batch&) = delete;
-  ~Batch() { free_device(); }
+  ~Batch() {
+    free_device();
+    if (block) hipFree(block);
+  }
 };
 
 Desc make_desc(const pamc_instance* I);

@@ -2657,17 +2657,21 @@ int Batch::group_of(const pamc_instance* I) {
   return 1 + 18 * (I->nhub ? 1 : 0) + 9 * wide + 3 * I->jmode + ti;
 }
 
+constexpr size_t kBatchBlock = 256 << 10;  // bytes of a batch's own block
+static void batch_free(Batch& b, void* p) {
+  // pieces of an arena or of the batch's block are not freed by themselves
+  if (!p || b.arena || (b.block && (char*)p >= b.block && (char*)p < b.block + kBatchBlock)) return;
+  if (b.al)
+    b.al->free(b.al->ctx, p, (void*)b.stream);
+  else
+    hipFree(p);
+}
+
 void Batch::free_device() {
-  const bool own = arena == nullptr;  // arena pieces are not the batch's to free
-  auto release = [&](void* p) {
-    if (!p || !own) return;
-    if (al)
-      al->free(al->ctx, p, (void*)stream);
-    else
-      hipFree(p);
-  };
+  auto release = [&](void* p) { batch_free(*this, p); };
   release(d_desc);
   d_desc = nullptr;
+  block_used = 0;
   Launch* all[] = {&init_spins, &init_fields, &thr, &thr_dense, &gather, &cl_mis, &cl_apply, &dh};
   for (Launch* l : all) {
     release(l->map);
@@ -2709,7 +2713,19 @@ hipError_t batch_alloc(Batch& b, void** p, size_t bytes) {
     *p = b.al->alloc(b.al->ctx, bytes, (void*)b.stream);
     return *p ? hipSuccess : hipErrorOutOfMemory;
   }
-  if (!b.arena) return hipMalloc(p, bytes);
+  if (!b.arena) {
+    // a dozen maps, most of them a few kilobytes, at each rebuild: an
+    // allocation and a release cost 20 us, a reset of a small instance 0.25 ms
+    const size_t at = (b.block_used + 255) & ~(size_t)255;
+    if (bytes > kBatchBlock - std::min(at, kBatchBlock)) return hipMalloc(p, bytes);
+    if (!b.block) {
+      const hipError_t e = hipMalloc((void**)&b.block, kBatchBlock);
+      if (e != hipSuccess) return e;
+    }
+    *p = b.block + at;
+    b.block_used = at + bytes;
+    return hipSuccess;
+  }
   const size_t at = (b.arena_used + 255) & ~(size_t)255;
   b.arena_need = at + bytes;
   if (bytes > b.arena_cap || at > b.arena_cap - bytes) return hipErrorOutOfMemory;
