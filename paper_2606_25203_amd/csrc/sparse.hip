@@ -37,6 +37,7 @@ constexpr int kClusterMaxN = 26000;        // LDS: 5 bytes per vertex
 constexpr int kRsMaxR = 16384;
 constexpr int kThrLds = 2048;              // threshold entries staged in LDS when they fit
 constexpr int kThrBlocks = 16;             // threshold work-groups per instance
+constexpr int kLongRow = 512;              // entries from which a row's field is summed by four waves
 constexpr int kOrderLds = 2048;            // class-order entries shuffled in LDS at a time
 constexpr int kInitBlocks = 64;            // spin-init work-groups per instance
 constexpr int kApplyChunks = 16;           // cluster-apply work-groups per target
@@ -947,12 +948,23 @@ __device__ __forceinline__ void sweep_push_body(const PAMC_CONST int32_t* __rest
         if (__ballot(flip)) {
           const int e0 = row_ptr[v], e1 = row_ptr[v + 1];
           const int32_t dd = 2 * snew;
-          for (int e = e0; e < e1; ++e) {
-            const int j = col[e];
-            const int32_t add = Jc[e] * dd;
-            if (flip)
-              __hip_atomic_fetch_add(&H[(hbase + j) * kLanes + lane], add, __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
+          // eight entries at a time (the arrays have room past the last): the
+          // reads of them, not the additions, are waited for
+          for (int e = e0; e < e1; e += 8) {
+            int j[8];
+            int32_t c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+              j[u] = col[e + u];
+              c[u] = Jc[e + u];
+            }
+            if (flip) {
+#pragma unroll
+              for (int u = 0; u < 8; ++u)
+                if (e + u < e1)
+                  __hip_atomic_fetch_add(&H[(hbase + j[u]) * kLanes + lane], c[u] * dd, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+            }
           }
         }
       }
@@ -1294,37 +1306,56 @@ __global__ void __launch_bounds__(256) k_init_fields(const Desc* __restrict__ D,
   const uint32_t* S = b ? d.S1 : d.S0;
   int32_t* H = Hout ? Hout : (b ? d.H1 : d.H0);
   int64_t* E = accumulate_energy ? (b ? d.E1 : d.E0) : nullptr;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const PAMC_CONST int32_t* __restrict__ row_ptr = cmem(d.row_ptr);
+  const PAMC_CONST int32_t* __restrict__ col = cmem(d.col);
+  const PAMC_CONST int32_t* __restrict__ J = cmem(d.J);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t items = (int64_t)d.T * ((d.n + 63) / 64);
   const int64_t nblocks = items < kFieldBlocks ? items : kFieldBlocks;
   for (int64_t it = lb; it < items; it += nblocks) {
     const int tile = (int)(it % d.T);
     const int vchunk = (int)(it / d.T);
+    const int v_end = min(d.n, (vchunk + 1) * 64);
     int64_t acc = 0;
-    for (int v = vchunk * 64 + wave; v < d.n && v < (vchunk + 1) * 64; v += 4) {
-      if (d.potts_K) {
-        // Potts labels (Eq. 6): sum_j J_vj (2 delta(s_v, s_j) - 1); no fields
-        const int32_t lv = spin_at(S, d.nq, tile, v, lane);
-        for (int e = d.row_ptr[v]; e < d.row_ptr[v + 1]; ++e)
-          acc += spin_at(S, d.nq, tile, d.col[e], lane) == lv ? d.J[e] : -d.J[e];
-        if (H) H[((size_t)tile * d.np + v) * kLanes + lane] = 0;
-        continue;
-      }
-      // four independent sums, so that a long (hub) row has several spin
-      // reads in flight rather than one at a time
-      const int e0 = d.row_ptr[v], e1 = d.row_ptr[v + 1];
+    // sum of J s over the entries e0 .. e1 - 1: eight spin reads in flight
+    auto row_field = [&](int e0, int e1) {
       int64_t hp[4] = {0, 0, 0, 0};
       int e = e0;
-      for (; e + 4 <= e1; e += 4) {
+      for (; e + 8 <= e1; e += 8) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) hp[u] += (int64_t)d.J[e + u] * spin_at(S, d.nq, tile, d.col[e + u], lane);
+        for (int u = 0; u < 8; ++u) hp[u & 3] += (int64_t)J[e + u] * spin_at(S, d.nq, tile, col[e + u], lane);
       }
-      for (; e < e1; ++e) hp[0] += (int64_t)d.J[e] * spin_at(S, d.nq, tile, d.col[e], lane);
-      const int64_t h = (hp[0] + hp[1]) + (hp[2] + hp[3]);
+      for (; e < e1; ++e) hp[0] += (int64_t)J[e] * spin_at(S, d.nq, tile, col[e], lane);
+      return (hp[0] + hp[1]) + (hp[2] + hp[3]);
+    };
+    auto keep = [&](int v, int64_t h) {
       if (H) H[((size_t)tile * d.np + v) * kLanes + lane] = (int32_t)h;
       if (!Hout && d.nhub && (v == d.hub_v0 || v == d.hub_v1))  // the kept hub fields
         (b ? d.HF1 : d.HF0)[(v == d.hub_v0 ? 0 : 1) * d.R + tile * kLanes + lane] = (int32_t)h;
       acc += h * spin_at(S, d.nq, tile, v, lane);
+    };
+    for (int v = vchunk * 64 + wave; v < v_end; v += 4) {
+      const int e0 = row_ptr[v], e1 = row_ptr[v + 1];
+      if (d.potts_K) {
+        // Potts labels (Eq. 6): sum_j J_vj (2 delta(s_v, s_j) - 1); no fields
+        const int32_t lv = spin_at(S, d.nq, tile, v, lane);
+        for (int e = e0; e < e1; ++e) acc += spin_at(S, d.nq, tile, col[e], lane) == lv ? J[e] : -J[e];
+        if (H) H[((size_t)tile * d.np + v) * kLanes + lane] = 0;
+      } else if (e1 - e0 < kLongRow) {
+        keep(v, row_field(e0, e1));
+      }
+    }
+    // long (hub) rows: a quarter to each wave.  One row of 21,000 entries walked
+    // by a wave, its entries through vector loads, took 2.1 ms.
+    for (int v = vchunk * 64; v < v_end && !d.potts_K; ++v) {
+      const int e0 = row_ptr[v], e1 = row_ptr[v + 1], len = e1 - e0;
+      if (len < kLongRow) continue;
+      const int from = e0 + (int)((int64_t)len * wave / 4), to = e0 + (int)((int64_t)len * (wave + 1) / 4);
+      __syncthreads();
+      red[wave][lane] = row_field(from, to);
+      __syncthreads();
+      if (wave == 0) keep(v, (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]));
     }
     __syncthreads();
     red[wave][lane] = acc;
