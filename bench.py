@@ -342,12 +342,12 @@ def measure(pamc, torch, name, steps, warmup, fields=None):
     launch_ms = prof["ms"] / max(prof["launches"], 1)
     p_flip = prof["flips"] / max(prof["attempts"], 1)
     if w["kind"] == "dense":
-        # One timed unit is a super-block step: the product completing this
-        # super-block's fields, then k_dense_step (its sequential pass with
-        # the next super-block's product on the other compute units).  Its
+        # One timed unit is a super-block step, k_dense_step: its sequential
+        # pass with the next super-block's field product on the other compute
+        # units (a sweep's first product has a launch of its own).  Its
         # matrix-core work is one super-block's share of the field products,
-        # 2 npad^2 R int8 ops per sweep; the step lasts as long as the
-        # sequential pass, so this fraction is that of the whole dense sweep.
+        # 2 npad^2 R int8 ops per sweep, so this fraction is that of the whole
+        # dense sweep.
         npad = (n + 63) // 64 * 64
         sweeps_done = prof["attempts"] / (n * w["R"])
         ops = 2.0 * npad * npad * w["R"] * sweeps_done / max(prof["launches"], 1)
@@ -356,14 +356,15 @@ def measure(pamc, torch, name, steps, warmup, fields=None):
                 "peak": MFMA_I8_PEAK_TOPS, "unit": "TOP/s (int8)", "frac": achieved / MFMA_I8_PEAK_TOPS,
                 "traffic": None, "launch_ms": launch_ms, "launches": prof["launches"], "ops_per_launch": ops,
                 "flip_rate": p_flip}
-        step_c = counters(w["counters"], "dense.hip", "k_dense_step<0>")
-        gemm_c = counters(w["counters"], "dense.hip", "k_dense_gemm")
+        step_c = counters(w["counters"], "dense.hip", "k_dense_step<0, 256>")
+        gemm_c = counters(w["counters"], "dense.hip", "k_dense_gemm<256>")
         if step_c and gemm_c:
-            # one launch unit = one k_dense_step and one k_dense_gemm dispatch
-            roof["traffic"] = step_c["hbm_bytes_per_dispatch"] + gemm_c["hbm_bytes_per_dispatch"]
+            # one launch unit = one k_dense_step dispatch, and a sweep's k_dense_gemm shared by its steps
+            share = 1.0 / ((n + 1023) // 1024)
+            roof["traffic"] = step_c["hbm_bytes_per_dispatch"] + share * gemm_c["hbm_bytes_per_dispatch"]
             roof["traffic_gbs"] = roof["traffic"] / (launch_ms * 1e-3) / 1e9
             roof["traffic_frac"] = roof["traffic_gbs"] / HBM_PEAK_GBS
-            mops = step_c.get("SQ_INSTS_VALU_MFMA_MOPS_I8", 0.0) + gemm_c.get("SQ_INSTS_VALU_MFMA_MOPS_I8", 0.0)
+            mops = step_c.get("SQ_INSTS_VALU_MFMA_MOPS_I8", 0.0) + share * gemm_c.get("SQ_INSTS_VALU_MFMA_MOPS_I8", 0.0)
             roof["counter_mfma_ops_per_launch"] = 512.0 * mops  # the counter counts units of 512 ops
     else:
         degree = info.nnz / n
@@ -372,7 +373,8 @@ def measure(pamc, torch, name, steps, warmup, fields=None):
         rate = apl / (launch_ms * 1e-3)
         shape = {"tiles_per_wave": info.tiles_per_wave, "quads_per_wave": info.quads_per_wave,
                  "coupling_mode": info.coupling_mode, "tile_sweeps": info.tile_sweeps, "hubs": info.hubs}
-        kname = sweep_kernel(info, w["kind"] == "potts")
+        torus = "torus" in w["counters"]
+        kname = sweep_kernel(info, w["kind"] == "potts", torus)
         if w["kind"] == "potts":
             slots = potts_slots_per_attempt(degree, info.potts_K, info.X)
             achieved = slots * rate / 1e12
@@ -422,7 +424,7 @@ def measure(pamc, torch, name, steps, warmup, fields=None):
         roof.update({"traffic": None, "launch_ms": launch_ms, "launches": prof["launches"],
                      "attempts_per_launch": apl, "flip_rate": p_flip, "fields": "pull" if pull else "push",
                      "kernel_shape": shape, "attempts_per_s_in_kernel": rate})
-        c = counters(w["counters"], "sparse.hip", kname)
+        c = counters(w["counters"], "bits.hip" if torus else "sparse.hip", kname)
         if c and "hbm_bytes_per_dispatch" in c:
             # measured bytes per dispatch of the counted sweeps (at the
             # profiling script's temperature), scaled to this run's launches

@@ -48,11 +48,15 @@ def kernel_source_sha256(src):
     return h.hexdigest()
 
 
-def sweep_kernel(info, potts=False):
+def sweep_kernel(info, potts=False, torus=False):
     """The name rocprofv3 gives (up to the argument list) to the kernel that
-    makes an instance's sweeps, from the instance's chosen shape."""
+    makes an instance's sweeps, from the instance's chosen shape.  torus: a
+    large +-1 torus (rows of four couplings of one magnitude, several sweeps a
+    step), which sweeps bit-packed in groups of four tiles."""
     if info.dense:
-        return "k_dense_step<0>"
+        return "k_dense_step<0, 256>" if info.replicas > 128 else "k_dense_step<0, 128>"
+    if torus and info.pull and not info.tile_sweeps:
+        return "k_sweep_bits_grid<4, false>"
     if potts:
         return f"k_sweep_potts<{info.potts_K}>"
     if info.tile_sweeps == 2:  # one instance (at most 128 tiles): a work-group per 16-replica group
@@ -120,8 +124,9 @@ def main():
            "kernel_ms": prof["ms"], "wall_s": wall, "pull": info.pull, "nnz": info.nnz,
            "tiles_per_wave": info.tiles_per_wave, "quads_per_wave": info.quads_per_wave,
            "coupling_mode": info.coupling_mode, "tile_sweeps": info.tile_sweeps, "hubs": info.hubs,
-           "kernel": sweep_kernel(info, args.workload == "c4p"), "settle_gap_s": SETTLE_GAP_S,
-           "source_sha256": kernel_source_sha256("dense.hip" if info.dense else "sparse.hip")}
+           "kernel": sweep_kernel(info, args.workload == "c4p", args.workload == "c2"), "settle_gap_s": SETTLE_GAP_S,
+           "source_sha256": kernel_source_sha256("dense.hip" if info.dense else
+                                               "bits.hip" if args.workload == "c2" else "sparse.hip")}
     inst.close()
     print(json.dumps(out), flush=True)
     if args.facts_out:
