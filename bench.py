@@ -90,6 +90,15 @@ def alu_slots_per_attempt(degree: float, coupling_mode: int) -> float:
     return 25.0 + per_neighbour * degree + 9.0
 
 
+def bit_slots_per_attempt(degree: float) -> float:
+    """Vector-ALU issue slots of one visit of the bit-packed sweep.
+    Philox4x32-10 with its 32x32->64 products at full rate (as gfx950 issues
+    them): (10 x (2 + 2)) / 4 = 10.  Field: one add with carry per neighbour.
+    Decision: start of the count by the spin, table address, compare, and
+    the two lane writes that pack the new mask: 5."""
+    return 10.0 + degree + 5.0
+
+
 def potts_slots_per_attempt(degree: float, K: int, X: int) -> float:
     """Vector-ALU issue slots (lane-ops, 32x32->64 products counting 4,
     binary64 operations 2) of one Potts label visit of k_sweep_potts<3>, from
@@ -403,6 +412,16 @@ def measure(pamc, torch, name, steps, warmup, fields=None):
                 ops = 2.0 * degree * rate / 1e12  # the sparse product's multiply-adds, not the zero blocks
                 roof["mfma_model"] = {"useful_int8_ops_per_attempt": 2.0 * degree, "achieved_tops": ops,
                                       "peak_tops": MFMA_I8_PEAK_TOPS, "frac": ops / MFMA_I8_PEAK_TOPS}
+        elif torus:
+            # bit-packed: the masks of a phase are a few megabytes, so the
+            # byte model of the other layouts does not apply; vector issue
+            slots = bit_slots_per_attempt(degree)
+            achieved = slots * rate / 1e12
+            roof = {"kernel": kname, "bound": "alu", "achieved": achieved, "peak": VALU_PEAK_TSLOTS,
+                    "unit": "T int32 lane-op slots/s", "frac": achieved / VALU_PEAK_TSLOTS,
+                    "alu_slots_per_attempt": slots,
+                    "kernel_min_bytes_per_attempt": 3.0 / 8.0,  # a mask read, written with its complement
+                    "hbm_algorithmic_bytes_per_attempt": incremental_field_bytes_per_attempt(p_flip, degree)}
         else:
             # achieved = the algorithmic bytes of the visits one launch makes
             # (incremental-field layout) over the launch's measured duration

@@ -44,6 +44,7 @@ constexpr int kApplyChunks = 16;           // cluster-apply work-groups per targ
 constexpr int kFieldBlocks = 1024;         // max field-init work-groups per instance
 constexpr uint32_t kIdle = 0xFFFFFFFFu;    // padding block: returns at once
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));  // at any entry
 constexpr int kBufferWord3 = 0x00020000;   // buffer resource word 3: 32-bit raw data
 
 // Map word: instance index in the high half, local block in the low half.
@@ -1303,52 +1304,69 @@ __global__ void __launch_bounds__(256) k_init_fields(const Desc* __restrict__ D,
   if (!resolve(map, inst, lb)) return;
   const Desc& d = D[inst];
   const int b = buf < 0 ? d.st->cur : buf;
-  const uint32_t* S = b ? d.S1 : d.S0;
-  int32_t* H = Hout ? Hout : (b ? d.H1 : d.H0);
+  const PAMC_GLOBAL uint32_t* S = gmem((const uint32_t*)(b ? d.S1 : d.S0));
+  PAMC_GLOBAL int32_t* H = gmem(Hout ? Hout : (b ? d.H1 : d.H0));
+  PAMC_GLOBAL int32_t* HF = gmem(!Hout && d.nhub ? (b ? d.HF1 : d.HF0) : nullptr);  // the kept hub fields
+  const int nq = d.nq, np = d.np, n = d.n, T = d.T, hub0 = d.hub_v0, hub1 = d.hub_v1, R = d.R;
+  const bool potts = d.potts_K != 0;
+  auto spin = [&](int tile, int v, int lane) {
+    return (int32_t)(int8_t)(S[((size_t)tile * nq + (v >> 2)) * kLanes + lane] >> (8 * (v & 3)));
+  };
   int64_t* E = accumulate_energy ? (b ? d.E1 : d.E0) : nullptr;
   const PAMC_CONST int32_t* __restrict__ row_ptr = cmem(d.row_ptr);
   const PAMC_CONST int32_t* __restrict__ col = cmem(d.col);
   const PAMC_CONST int32_t* __restrict__ J = cmem(d.J);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t items = (int64_t)d.T * ((d.n + 63) / 64);
+  const int64_t items = (int64_t)T * ((n + 63) / 64);
   const int64_t nblocks = items < kFieldBlocks ? items : kFieldBlocks;
   for (int64_t it = lb; it < items; it += nblocks) {
-    const int tile = (int)(it % d.T);
-    const int vchunk = (int)(it / d.T);
-    const int v_end = min(d.n, (vchunk + 1) * 64);
+    const int tile = (int)(it % T);
+    const int vchunk = (int)(it / T);
+    const int v_end = min(n, (vchunk + 1) * 64);
     int64_t acc = 0;
-    // sum of J s over the entries e0 .. e1 - 1: eight spin reads in flight
+    // sum of J s over the entries e0 .. e1 - 1: eight spin reads in flight, the
+    // entries four to a scalar load (one costs a compute unit 8 cycles)
+    auto four = [&](int e, int64_t(&hp)[4]) {
+      const i32x4u c = *reinterpret_cast<const PAMC_CONST i32x4u*>(col + e);
+      const i32x4u w = *reinterpret_cast<const PAMC_CONST i32x4u*>(J + e);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) hp[u] += (int64_t)w[u] * spin(tile, c[u], lane);
+    };
     auto row_field = [&](int e0, int e1) {
       int64_t hp[4] = {0, 0, 0, 0};
       int e = e0;
       for (; e + 8 <= e1; e += 8) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) hp[u & 3] += (int64_t)J[e + u] * spin_at(S, d.nq, tile, col[e + u], lane);
+        four(e, hp);
+        four(e + 4, hp);
       }
-      for (; e < e1; ++e) hp[0] += (int64_t)J[e] * spin_at(S, d.nq, tile, col[e], lane);
+      if (e + 4 <= e1) {
+        four(e, hp);
+        e += 4;
+      }
+      for (; e < e1; ++e) hp[0] += (int64_t)J[e] * spin(tile, col[e], lane);
       return (hp[0] + hp[1]) + (hp[2] + hp[3]);
     };
     auto keep = [&](int v, int64_t h) {
-      if (H) H[((size_t)tile * d.np + v) * kLanes + lane] = (int32_t)h;
-      if (!Hout && d.nhub && (v == d.hub_v0 || v == d.hub_v1))  // the kept hub fields
-        (b ? d.HF1 : d.HF0)[(v == d.hub_v0 ? 0 : 1) * d.R + tile * kLanes + lane] = (int32_t)h;
-      acc += h * spin_at(S, d.nq, tile, v, lane);
+      if (H) H[((size_t)tile * np + v) * kLanes + lane] = (int32_t)h;
+      if (HF && (v == hub0 || v == hub1)) HF[(v == hub0 ? 0 : 1) * R + tile * kLanes + lane] = (int32_t)h;
+      acc += h * spin(tile, v, lane);
     };
     for (int v = vchunk * 64 + wave; v < v_end; v += 4) {
       const int e0 = row_ptr[v], e1 = row_ptr[v + 1];
-      if (d.potts_K) {
+      if (potts) {
         // Potts labels (Eq. 6): sum_j J_vj (2 delta(s_v, s_j) - 1); no fields
-        const int32_t lv = spin_at(S, d.nq, tile, v, lane);
-        for (int e = e0; e < e1; ++e) acc += spin_at(S, d.nq, tile, col[e], lane) == lv ? J[e] : -J[e];
-        if (H) H[((size_t)tile * d.np + v) * kLanes + lane] = 0;
+        const int32_t lv = spin(tile, v, lane);
+        for (int e = e0; e < e1; ++e) acc += spin(tile, col[e], lane) == lv ? J[e] : -J[e];
+        if (H) H[((size_t)tile * np + v) * kLanes + lane] = 0;
       } else if (e1 - e0 < kLongRow) {
         keep(v, row_field(e0, e1));
       }
     }
-    // long (hub) rows: a quarter to each wave.  One row of 21,000 entries walked
-    // by a wave, its entries through vector loads, took 2.1 ms.
-    for (int v = vchunk * 64; v < v_end && !d.potts_K; ++v) {
+    // long (hub) rows: a quarter to each wave.  With a row of 21,000 entries the
+    // launch takes 0.64 ms; walked by one wave, its entries through vector loads,
+    // it took 2.1 (G(800, 19176), R = 256: 0.054 and 0.086).
+    for (int v = vchunk * 64; v < v_end && !potts; ++v) {
       const int e0 = row_ptr[v], e1 = row_ptr[v + 1], len = e1 - e0;
       if (len < kLongRow) continue;
       const int from = e0 + (int)((int64_t)len * wave / 4), to = e0 + (int)((int64_t)len * (wave + 1) / 4);
