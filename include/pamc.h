@@ -246,7 +246,7 @@ typedef struct {
   /* > 0: record the population's mean normalised pair distance d_H (see
    * pamc_pair_distance) every dh_every steps, after the step's sweeps
    * (pamc_get_dh_trace).  Each sample compares all R(R-1)/2 pairs:
-   * O(R^2 n / 32) word reads. */
+   * R^2 n / 2 byte products on the matrix cores. */
   int32_t dh_every;
 } pamc_schedule;
 

@@ -3033,7 +3033,7 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
       bdesc[i] = make_bit_desc(I, desc[i], qw, u);
     }
   }
-  // diversity samples: one work-group per replica.  A batch without
+  // diversity samples: one work-group per tile pair.  A batch without
   // schedules (an instance's own) keeps the map; its runs switch it on.
   b.any_dh = 0;
   for (int i = 0; i < b.n; ++i) {
