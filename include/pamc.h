@@ -206,10 +206,9 @@ pamc_status pamc_reset_population(pamc_instance* inst, uint64_t seed);
  * fields computed on the matrix cores as int8 products of 16 x 64 coupling
  * blocks with the spins (n <= 1024, int8 couplings), one work-group per
  * 16-replica group of a tile while the launch has at most 128 tiles, else
- * one per tile (couplings of one magnitude: tile_sweeps 1, and 2 in batches
- * of more than 128 such tiles, sweep bit-packed instead, one launch per
- * colour class); hubs: vertices whose fields are kept while the others are
- * gathered. */
+ * one per tile (tile_sweeps 1 and couplings of one magnitude: bit-packed
+ * instead where a step has enough sweeps, one launch per colour class); hubs:
+ * vertices whose fields are kept while the others are gathered. */
 typedef struct {
   int32_t n, replicas, num_classes, dense, pull;
   int64_t nnz, W, X; /* X = max_v sum_j |J_vj| */

@@ -538,32 +538,6 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
       }
     }
   }
-  // Rows of the bit-packed sweeps: the higher neighbours first (the energy
-  // sum's edges), padded to multiples of 4 with the mask that is always 0.
-  // Rows start at multiples of one stride where that costs at most three
-  // times the entries: a wave then finds its row without reading bounds.
-  if (h.bits_ok) {
-    int64_t total = 0;
-    for (int32_t iv = 0; iv < n; ++iv) total += (h.rp2[iv + 1] - h.rp2[iv] + 3) & ~3;
-    h.bstride = bits_row_stride(n, maxdeg, total);
-    h.brows.assign((size_t)h.np * 4, 0);
-    int32_t *bounds = h.brows.data(), *base = bounds + 2 * (size_t)h.np, *higher = base + h.np;
-    for (int32_t iv = 0; iv < h.np; ++iv) {
-      if (h.bstride) h.bent.resize((size_t)iv * h.bstride, 8 * h.np);
-      bounds[2 * iv] = bounds[2 * iv + 1] = (int32_t)h.bent.size();
-      if (iv >= n) continue;
-      for (int upper = 1; upper >= 0; --upper)
-        for (int32_t e = h.rp2[iv]; e < h.rp2[iv + 1]; ++e)
-          if ((h.col2[e] > iv) == (upper == 1)) {
-            h.bent.push_back(8 * (h.col2[e] + (both_signs && h.J2[e] < 0 ? h.np + 1 : 0)));
-            higher[iv] += upper;
-          }
-      while (h.bent.size() % 4) h.bent.push_back(8 * h.np);
-      bounds[2 * iv + 1] = (int32_t)h.bent.size();
-      base[iv] = 4 * (h.bmaxdeg - (h.rp2[iv + 1] - h.rp2[iv]));
-    }
-    h.bent.resize(h.bent.size() + 16 + 4 * (size_t)h.bstride, 8 * h.np);
-  }
   const bool tile_candidate = h.pull && !h.nhub && !h.potts_K && tile_fits(h.nq, X);
   if (tile_candidate) {  // a class's gathered rows are staged in LDS next to the spins
     for (int32_t c = 0; c < h.ncls; ++c)
@@ -605,12 +579,43 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
       h.gJ.clear();
     }
   }
-  // Bit-packed sweeps leave the matrix-core tile form to lone instances and
-  // small batches, whose step it makes in one launch (PAMC_BITS = 1: not even
-  // that).
+  // Bit-packed sweeps leave the matrix-core tile form alone (PAMC_BITS = 1: not
+  // even that): its step is one launch, a bit-packed one a launch per class and
+  // sweep.  Batches of 132, 256, 520 and 1,024 replica tiles, 20 steps x 5 sweeps
+  // (in brackets x 1), matrix-core tiles and bit-packed: G(800, 19176) 6.8 and
+  // 16.2, 8.0 and 22.0, 18.5 and 39.4, 25.4 and 80.8 ms (12.3 and 28.9); G(500,
+  // 4100) 4.0 and 7.3, 4.9 and 9.4, 10.9 and 15.8, 15.6 and 32.9 (9.3 and 14.9);
+  // batches of 48 mixed instances, 13 of them such, R = 256: 41.7 and 42.1, R =
+  // 1024: 59.9 and 55.2; of 96, 36 of them such, R = 512: 51.3 and 70.9.
   if (h.bits_ok) {
     h.bits_always = be && atoi(be) == 1;
-    h.bits = h.tile == 2 && !h.bits_always ? 2 : 1;
+    h.bits_ok = h.bits = h.tile != 2 || h.bits_always;
+  }
+  // Rows of the bit-packed sweeps: the higher neighbours first (the energy
+  // sum's edges), padded to multiples of 4 with the mask that is always 0.
+  // Rows start at multiples of one stride where that costs at most three
+  // times the entries: a wave then finds its row without reading bounds.
+  if (h.bits_ok) {
+    int64_t total = 0;
+    for (int32_t iv = 0; iv < n; ++iv) total += (h.rp2[iv + 1] - h.rp2[iv] + 3) & ~3;
+    h.bstride = bits_row_stride(n, maxdeg, total);
+    h.brows.assign((size_t)h.np * 4, 0);
+    int32_t *bounds = h.brows.data(), *base = bounds + 2 * (size_t)h.np, *higher = base + h.np;
+    for (int32_t iv = 0; iv < h.np; ++iv) {
+      if (h.bstride) h.bent.resize((size_t)iv * h.bstride, 8 * h.np);
+      bounds[2 * iv] = bounds[2 * iv + 1] = (int32_t)h.bent.size();
+      if (iv >= n) continue;
+      for (int upper = 1; upper >= 0; --upper)
+        for (int32_t e = h.rp2[iv]; e < h.rp2[iv + 1]; ++e)
+          if ((h.col2[e] > iv) == (upper == 1)) {
+            h.bent.push_back(8 * (h.col2[e] + (both_signs && h.J2[e] < 0 ? h.np + 1 : 0)));
+            higher[iv] += upper;
+          }
+      while (h.bent.size() % 4) h.bent.push_back(8 * h.np);
+      bounds[2 * iv + 1] = (int32_t)h.bent.size();
+      base[iv] = 4 * (h.bmaxdeg - (h.rp2[iv + 1] - h.rp2[iv]));
+    }
+    h.bent.resize(h.bent.size() + 16 + 4 * (size_t)h.bstride, 8 * h.np);
   }
   // Tiles per wavefront: share the per-vertex scalar work among up to 4
   // tiles while keeping enough work-groups (one quad per wave) to fill the
@@ -2027,8 +2032,7 @@ pamc_status pamc_autotune(pamc_instance* I, double beta, int32_t sweeps, int32_t
   }
   std::vector<TuneShape> cand;
   if (I->bits_ok) cand.push_back({initial.tile, initial.tpw, initial.qpw, 1});  // bit-packed
-  // matrix-core fields (bit-packed in large batches all the same)
-  if (I->tmma_ok) cand.push_back({2, initial.tpw, initial.qpw, I->bits_ok ? 2 : 0});
+  if (I->tmma_ok) cand.push_back({2, initial.tpw, initial.qpw, 0});  // matrix-core fields
   for (int tile : {0, 1}) {
     if (tile && !I->tile_ok) continue;
     if (tile) {

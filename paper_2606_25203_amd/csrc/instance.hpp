@@ -101,8 +101,8 @@ struct pamc_instance {
   int32_t order_cap = 0;
   // bit-packed sweeps: every coupling is +-|bcoup| (bits.hip)
   int32_t bits_ok = 0;      // possible
-  int32_t bits = 0;         // taken for the sweeps: 1 by bits_min_sweeps, 2 in large batches
-  bool bits_always = false; // bits == 1 whatever the sweeps per step
+  int32_t bits = 0;         // taken for the sweeps of steps of bits_min_sweeps and more
+  bool bits_always = false; // ... and of steps of fewer
   int32_t bcoup = 0;        // the coupling's magnitude; negative when every coupling is
   int32_t bcopies = 1;      // 2: couplings of both signs, masks kept with their complements
   int32_t bmaxdeg = 0;      // the longest row
@@ -350,7 +350,7 @@ hipError_t launch_refresh_fields(Batch& b);
 // nbins), their sum after them
 hipError_t launch_pair_hist(pamc_instance* I, int32_t nbins, int64_t* out_dev);
 int32_t cluster_max_n();
-// The fewest sweeps per step from which instances of bits == 1 sweep
+// The fewest sweeps per step from which instances of bits != 0 sweep
 // bit-packed as one batch.
 int32_t bits_min_sweeps(const std::vector<pamc_instance*>& insts);
 int32_t sweep_waves();  // wavefronts per sweep work-group

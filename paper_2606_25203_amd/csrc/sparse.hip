@@ -2850,7 +2850,7 @@ int32_t bits_min_sweeps(const std::vector<pamc_instance*>& insts) {
   int64_t all_tiles = 0;
   int32_t ncls = 0, count = 0;
   for (const pamc_instance* I : insts) {
-    if (I->dense || I->bits != 1) continue;
+    if (I->dense || !I->bits) continue;
     const double deg = I->n > 0 ? (double)I->nnz / I->n : 0.0;
     tiles = tiles && I->tile == 1;
     tile_us = std::max(tile_us, I->n * (0.02 + 0.0023 * deg) + I->ncls);
@@ -2881,19 +2881,13 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
   b.stream = insts[0]->stream;
   std::vector<Desc> desc(b.n);
   const int64_t push_wgs = push_budget(insts);
-  // Small instances of the matrix-core tile form sweep bit-packed in batches
-  // of more tiles than that form spreads over 16-replica groups.
-  int64_t mfma_tiles = 0;
-  for (const pamc_instance* I : insts)
-    if (!I->dense && I->tile == 2) mfma_tiles += I->T;
   int32_t most_sweeps = b.n == 1 && !scheds ? insts[0]->self_sweeps : 1;
   if (scheds)
     for (const Schedule& s : *scheds) most_sweeps = std::max(most_sweeps, s.sweeps);
   const bool enough = most_sweeps >= bits_min_sweeps(insts);
   auto sweeps_bits = [&](int i) {
     const pamc_instance* I = insts[i];
-    return allow_bits && !I->dense &&
-           ((I->bits == 1 && (enough || I->bits_always)) || (I->bits == 2 && mfma_tiles > kMfmaGroupTiles));
+    return allow_bits && !I->dense && I->bits && (enough || I->bits_always);
   };
   bool any_bits = false;
   for (int i = 0; i < b.n; ++i) {
