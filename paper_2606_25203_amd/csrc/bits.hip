@@ -26,6 +26,7 @@
 #include <utility>
 #include <vector>
 
+#include "bit_rows.hpp"
 #include "instance.hpp"
 #include "pamc_device.hpp"
 

@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "../../include/pamc.h"
+#include "bit_rows.hpp"
 #include "instance.hpp"
 
 using pamc::Schedule;
@@ -272,29 +273,6 @@ struct HostSparse {
   std::vector<int32_t> brows, bent;
 };
 
-// Bit-packed sweeps (bits.hip) take graphs whose couplings all have one
-// magnitude and whose rows all have at most kBitsMaxDegree entries.  Returns
-// that magnitude, or 0; *both: couplings of both signs.
-int32_t one_magnitude(int32_t n, const int32_t* rp, const int32_t* J, bool* both) {
-  *both = false;
-  if (rp[n] == 0 || n > (1 << 24) || J[0] == INT32_MIN) return 0;
-  const int32_t c = std::abs(J[0]);
-  for (int32_t v = 0; v < n; ++v)
-    if (rp[v + 1] - rp[v] > pamc::kBitsMaxDegree) return 0;
-  for (int32_t e = 0; e < rp[n]; ++e) {
-    if (J[e] != c && J[e] != -c) return 0;
-    if (J[e] != J[0]) *both = true;
-  }
-  return c;
-}
-
-// Row stride of the bit-packed rows (0: rows follow each other), from the
-// longest row and the entries of all rows padded to multiples of 4.
-int32_t bits_row_stride(int64_t n, int64_t maxdeg, int64_t padded) {
-  const int64_t stride = (maxdeg + 3) & ~3;
-  return stride * n <= 3 * padded ? (int32_t)stride : 0;
-}
-
 // A shape forced from the environment means the sweep kernels it names.
 bool shape_forced() {
   for (const char* k : {"PAMC_TILE", "PAMC_TPW", "PAMC_QPW", "PAMC_JMODE"})
@@ -479,10 +457,11 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
   }
   // Couplings of one magnitude sweep bit-packed (PAMC_BITS = 0: never).
   bool both_signs = false;
+  int64_t padded = 0;  // entries of the rows padded to multiples of 4
   const char* be = getenv("PAMC_BITS");
   if (h.allow_bits && !h.potts_K && !(flags & PAMC_FLAG_FIELDS_PUSH) && hubs.empty() && !shape_forced() &&
       !(be && atoi(be) == 0)) {
-    const int32_t c = one_magnitude(n, rp, Jin.data(), &both_signs);
+    const int32_t c = pamc::one_magnitude(n, rp, Jin.data(), &both_signs, &padded);
     if (c > 0) {
       h.bits_ok = 1;
       h.pull = 1;
@@ -593,12 +572,8 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
   }
   // Rows of the bit-packed sweeps: the higher neighbours first (the energy
   // sum's edges), padded to multiples of 4 with the mask that is always 0.
-  // Rows start at multiples of one stride where that costs at most three
-  // times the entries: a wave then finds its row without reading bounds.
   if (h.bits_ok) {
-    int64_t total = 0;
-    for (int32_t iv = 0; iv < n; ++iv) total += (h.rp2[iv + 1] - h.rp2[iv] + 3) & ~3;
-    h.bstride = bits_row_stride(n, maxdeg, total);
+    h.bstride = pamc::bit_row_stride(n, maxdeg, padded);
     h.brows.assign((size_t)h.np * 4, 0);
     int32_t *bounds = h.brows.data(), *base = bounds + 2 * (size_t)h.np, *higher = base + h.np;
     for (int32_t iv = 0; iv < h.np; ++iv) {
@@ -615,7 +590,7 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
       bounds[2 * iv + 1] = (int32_t)h.bent.size();
       base[iv] = 4 * (h.bmaxdeg - (h.rp2[iv + 1] - h.rp2[iv]));
     }
-    h.bent.resize(h.bent.size() + 16 + 4 * (size_t)h.bstride, 8 * h.np);
+    h.bent.resize(pamc::bit_row_entries(n, h.bstride, padded), 8 * h.np);
   }
   // Tiles per wavefront: share the per-vertex scalar work among up to 4
   // tiles while keeping enough work-groups (one quad per wave) to fill the
@@ -2344,7 +2319,9 @@ int64_t estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pam
   const bool tile = !(cfg.flags & PAMC_FLAG_FIELDS_PUSH) && tile_fits(np / 4, X);
   const int64_t ncls = maxdeg + 1;
   bool both;
-  bits = bits && !(cfg.flags & PAMC_FLAG_FIELDS_PUSH) && hubs.empty() && one_magnitude(n, rp, w, &both) > 0;
+  int64_t padded;
+  bits = bits && !(cfg.flags & PAMC_FLAG_FIELDS_PUSH) && hubs.empty() &&
+         pamc::one_magnitude(n, rp, w, &both, &padded) > 0;
   if (bits) pull = true;
   int64_t b = a(4 * (int64_t)(n + 1)) + 2 * a(4 * (nnz + 16));                 // CSR
   if (pull || tile) b += a(4 * (int64_t)(n + 1)) + 2 * a(4 * std::max<int64_t>(gathered, 4));  // gathered CSR
@@ -2356,8 +2333,8 @@ int64_t estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pam
   b += a(4 * std::max<int64_t>(64, sc.sweeps) * ncls);                        // class orders
   b += a(4 * R) + a(8 * 512);                                                  // parents, counters
   if (bits) {
-    const int64_t stride = bits_row_stride(n, maxdeg, gathered);
-    b += a(16 * np) + a(4 * (std::max(stride * np, gathered) + 16 + 4 * stride)) + a(8 * (2 * maxdeg + 2)) +
+    const int64_t entries = pamc::bit_row_entries(n, pamc::bit_row_stride(n, maxdeg, padded), padded);
+    b += a(16 * np) + a(4 * entries) + a(8 * (2 * maxdeg + 2)) +
          a(16 * std::max<int64_t>(64, sc.sweeps) * ncls);
   }
   b += 4 * a(8 * (int64_t)std::max(sc.steps, 1)) + a(4 * (int64_t)std::max(sc.steps, 1)) +

@@ -52,10 +52,6 @@ struct GraphDev {
   int32_t* bent = nullptr;
 };
 
-// Longest row of a bit-packed instance: one wavefront walks a row, and the
-// threshold table (4 deg + 4 entries) is staged in LDS by every work-group.
-constexpr int32_t kBitsMaxDegree = 256;
-
 }  // namespace pamc
 
 struct pamc_instance {
