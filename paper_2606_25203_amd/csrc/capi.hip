@@ -1679,7 +1679,8 @@ pamc_status pamc_anneal_batch_noalloc(pamc_instance* const* insts, const pamc_sc
   pamc::Batch b;
   b.arena = (char*)scratch;
   b.arena_cap = cap;
-  hipError_t e = pamc::batch_build(b, v, &s);
+  // (the schedules and the status follow in the scratch)
+  hipError_t e = pamc::batch_build(b, v, &s, ((sizeof(Schedule) * count + 255) & ~(size_t)255) + sizeof(int32_t) * count);
   pamc::Schedule* d_sched = nullptr;
   int32_t* d_status = nullptr;
   if (e == hipSuccess) e = pamc::batch_alloc(b, (void**)&d_sched, sizeof(Schedule) * count);

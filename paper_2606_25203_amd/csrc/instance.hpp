@@ -321,9 +321,12 @@ hipError_t fixed_scratch(void** ptr, size_t* bytes);
 // sweeps per step and whether cluster moves can occur.  Synchronises the
 // stream.  In arena mode scheds are required and each instance's class
 // orders and cluster-move scratch come from the arena too, sized for its
-// schedule (the instance's own buffers of those kinds are not used, and no
+// schedule (the instance's own buffers of those kinds are not used, except for
+// the phase records of bit-packed sweeps where they are large enough, and no
 // per-step trace is recorded).
-hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const std::vector<Schedule>* scheds);
+// later: in arena mode, bytes that the caller allocates from the batch next.
+hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const std::vector<Schedule>* scheds,
+                       size_t later = 0);
 hipError_t batch_init(Batch& b);                               // sparse instances
 // Loads schedules and clears the controller of the listed instances (all if
 // idx is null): instance idx[i] (or i) gets d_sched[i].

@@ -2913,7 +2913,7 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
       d.tr_cap = 0;
       d.order_cap = std::max(s.sweeps, 1);
       hipError_t e = batch_alloc(b, (void**)&d.order, sizeof(int32_t) * (size_t)d.order_cap * std::max(I->ncls, 1));
-      if (e == hipSuccess && d.bits)
+      if (e == hipSuccess && d.bits && d.order_cap > I->order_cap)  // else the instance's own
         e = batch_alloc(b, (void**)&d.bphases, 4 * sizeof(int32_t) * (size_t)d.order_cap * std::max(I->ncls, 1));
       if (e != hipSuccess) return e;
       const bool cl = s.augmented && s.resample && s.n_top > 0 && s.mis_trials > 0 && !I->potts_K && !I->dense;
@@ -3094,9 +3094,12 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
   return hipStreamSynchronize(b.stream);
 }
 
-hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const std::vector<Schedule>* scheds) {
+hipError_t batch_build(Batch& b, const std::vector<pamc_instance*>& insts, const std::vector<Schedule>* scheds,
+                       size_t later) {
   const hipError_t e = build_batch(b, insts, scheds, true);
-  if (e != hipErrorOutOfMemory || !b.arena || !b.has_bits) return e;
+  if (!b.arena || !b.has_bits) return e;
+  const bool fits = e == hipSuccess && ((b.arena_used + 255) & ~(size_t)255) + later <= b.arena_cap;
+  if (fits || (e != hipSuccess && e != hipErrorOutOfMemory)) return e;
   // the fixed scratch holds the batch without the bit-packed launches' maps:
   // the other sweep kernels give the same results
   b.arena_used = 0;
