@@ -49,39 +49,27 @@ pamc_status dev_fail(hipError_t e, const char* where) {
   } while (0)
 
 // Device memory of an instance: from its allocator when it has one, else
-// hipMalloc; while the instance is made (blocking), small buffers are pieces of
-// blocks.  An instance has some forty buffers, and an allocation with its
-// release costs 20 us: admitting 32 requests took 36 ms, and takes 18 (the
-// device's count and the kernels' limits, asked for and set once, included).
-constexpr size_t kBlock = 2 << 20, kBlockPiece = 512 << 10;
+// hipMalloc.
 hipError_t dev_alloc(pamc_instance* I, void** p, size_t bytes) {
   if (I->use_al) {
     *p = I->al.alloc(I->al.ctx, bytes, (void*)I->stream);
     return *p ? hipSuccess : hipErrorOutOfMemory;
   }
-  if (!I->blocking || bytes > kBlockPiece) return hipMalloc(p, bytes);
-  size_t at = (I->block_used + 255) & ~(size_t)255;
-  if (I->blocks.empty() || at + bytes > kBlock) {
-    char* block = nullptr;
-    const hipError_t e = hipMalloc((void**)&block, kBlock);
-    if (e != hipSuccess) return hipMalloc(p, bytes);
-    I->blocks.push_back(block);
-    at = 0;
-  }
-  *p = I->blocks.back() + at;
-  I->block_used = at + bytes;
-  return hipSuccess;
+  return hipMalloc(p, bytes);
+}
+
+bool in_block(const pamc_instance* I, const void* p) {
+  for (const auto& b : I->blocks)
+    if ((const char*)p >= b.first && (const char*)p < b.first + b.second) return true;
+  return false;
 }
 
 void dev_free(pamc_instance* I, void* p) {
-  if (!p) return;
-  if (I->use_al) {
+  if (!p || in_block(I, p)) return;  // a block goes with the instance
+  if (I->use_al)
     I->al.free(I->al.ctx, p, (void*)I->stream);
-    return;
-  }
-  for (const char* b : I->blocks)
-    if ((char*)p >= b && (char*)p < b + kBlock) return;
-  hipFree(p);
+  else
+    hipFree(p);
 }
 
 // The number of devices, asked for once (0.27 ms each time).
@@ -94,9 +82,23 @@ hipError_t device_count(int* count) {
   return e;
 }
 
+// While an instance without a provider is made (planning), its small buffers
+// are noted first and then placed in one block of their size: an instance has
+// some forty buffers, and an allocation with its release costs 20 us: admitting
+// 32 requests took 36 ms, and takes 18 (the device's count and the kernels'
+// limits, asked for and set once, included).
+constexpr size_t kPlanPiece = 512 << 10;
+inline size_t piece_bytes(size_t bytes) { return (std::max<size_t>(bytes, 16) + 255) & ~(size_t)255; }
+
 template <typename T>
 hipError_t dalloc(pamc_instance* I, T** p, size_t count) {
   const size_t bytes = std::max<size_t>(sizeof(T) * count, 16);
+  const bool member = (char*)p >= (char*)I && (char*)p < (char*)(I + 1);  // outlives the plan
+  if (I->planning && member && bytes <= kPlanPiece) {
+    *p = nullptr;
+    I->plan.push_back({(void**)p, bytes});
+    return hipSuccess;
+  }
   void* q = nullptr;
   hipError_t e = dev_alloc(I, &q, bytes);
   if (e == hipSuccess) {
@@ -106,13 +108,54 @@ hipError_t dalloc(pamc_instance* I, T** p, size_t count) {
   return e;
 }
 
+// The buffers noted since planning began, none of them used so far: a piece
+// each of one block, which counts whole, or where there is no room for it an
+// allocation each.
+hipError_t place_plan(pamc_instance* I) {
+  I->planning = false;
+  std::vector<std::pair<void**, size_t>> plan;
+  plan.swap(I->plan);
+  size_t total = 0;
+  for (const auto& x : plan) total += piece_bytes(x.second);
+  if (!total) return hipSuccess;
+  char* block = nullptr;
+  if (hipMalloc((void**)&block, total) == hipSuccess) {
+    I->blocks.push_back({block, total});
+    I->device_bytes += (int64_t)total;
+    for (const auto& x : plan) {
+      *x.first = block;
+      block += piece_bytes(x.second);
+    }
+    return hipSuccess;
+  }
+  (void)hipGetLastError();
+  for (const auto& x : plan) {
+    const hipError_t e = hipMalloc(x.first, x.second);
+    if (e != hipSuccess) return e;
+    I->device_bytes += (int64_t)x.second;
+  }
+  return hipSuccess;
+}
+
+// Planning from here to place_plan, or to the end of the scope.
+struct Planning {
+  pamc_instance* I;
+  explicit Planning(pamc_instance* inst) : I(inst) { I->planning = !I->use_al; }
+  ~Planning() {
+    I->planning = false;
+    I->plan.clear();
+  }
+};
+
 // Frees a buffer that dalloc made for count elements of T and takes it off
-// the instance's byte count.
+// the instance's byte count (a piece of a block stays held, and counted).
 template <typename T>
 void dfree(pamc_instance* I, T*& p, size_t count) {
   if (!p) return;
-  dev_free(I, p);
-  I->device_bytes -= (int64_t)std::max<size_t>(sizeof(T) * count, 16);
+  if (!in_block(I, p)) {
+    dev_free(I, p);
+    I->device_bytes -= (int64_t)std::max<size_t>(sizeof(T) * count, 16);
+  }
   p = nullptr;
 }
 
@@ -133,7 +176,7 @@ void free_instance(pamc_instance* I) {
                   I->flip_ctr, I->H_scratch, I->ptab, I->g.hubJ, I->pop.HF[0], I->pop.HF[1], I->g.Jt,
                   I->g.brows, I->g.bent, I->btab, I->bphases};
   for (void* p : ptrs) dev_free(I, p);
-  for (char* b : I->blocks) hipFree(b);
+  for (const auto& b : I->blocks) hipFree(b.first);
   if (I->pinned) hipHostFree(I->pinned);
   for (hipEvent_t e : I->ev_pool) hipEventDestroy(e);
   if (I->own_stream && I->stream) hipStreamDestroy(I->stream);
@@ -681,7 +724,8 @@ hipError_t prepare_device(int device) {
 }
 
 // Device half: buffers, upload and the initial population (waits).
-pamc_status upload_sparse(pamc_instance* I, HostSparse& h) {
+// sweeps: the sweeps per step that the class orders are made for at once.
+pamc_status upload_sparse(pamc_instance* I, HostSparse& h, int32_t sweeps = 0) {
   const int32_t n = h.n, ncls = h.ncls;
   I->n = n;
   I->np = h.np;
@@ -718,11 +762,7 @@ pamc_status upload_sparse(pamc_instance* I, HostSparse& h) {
   I->class_ptr = std::move(h.class_ptr);
   I->to_internal = std::move(h.to_internal);
   I->to_input = std::move(h.to_input);
-  struct Blocking {  // pieces of blocks until the return
-    pamc_instance* I;
-    ~Blocking() { I->blocking = false; }
-  } blocking{I};
-  I->blocking = true;
+  Planning planning(I);
   const size_t nnz = (size_t)I->nnz + 16;
   const size_t words = (size_t)I->T * I->nq * 64, hs = (size_t)I->T * I->np * 64;
   HIP_TRY(dalloc(I, &I->g.row_ptr, n + 1), "alloc");
@@ -755,11 +795,12 @@ pamc_status upload_sparse(pamc_instance* I, HostSparse& h) {
   if (I->potts_K)
     HIP_TRY(dalloc(I, &I->ptab, 2 * I->X + 1), "alloc");
   HIP_TRY(dalloc(I, &I->thr, I->potts_K ? 1 : 2 * I->X + 1), "alloc");
-  I->order_cap = 64;
+  I->order_cap = std::max(sweeps, 64);
   HIP_TRY(dalloc(I, &I->order, (size_t)I->order_cap * ncls), "alloc");
   if (I->bits_ok) HIP_TRY(dalloc(I, &I->bphases, 4 * (size_t)I->order_cap * ncls), "alloc");
   HIP_TRY(dalloc(I, &I->rs_parent, I->R), "alloc");
   HIP_TRY(dalloc(I, &I->flip_ctr, 512), "alloc");
+  HIP_TRY(place_plan(I), "alloc");
   HIP_TRY(hipMemsetAsync(I->flip_ctr, 0, sizeof(int64_t) * 512, I->stream), "memset");
   HIP_TRY(hipMemsetAsync(I->st, 0, sizeof(pamc::RunState), I->stream), "memset");
   if (!I->pull) {
@@ -2102,7 +2143,7 @@ pamc_status pamc_pair_distance_hist(pamc_instance* I, int32_t nbins, int64_t* co
   if (I->potts_K) return fail(PAMC_ERR_UNSUPPORTED, "pair distance on Potts labels");
   hipSetDevice(I->device);
   // kept with the instance: an allocation and its release cost more than the kernel
-  if (!I->pair_out) HIP_TRY(dev_alloc(I, (void**)&I->pair_out, sizeof(int64_t) * (kMaxPairBins + 1)), "alloc");
+  if (!I->pair_out) HIP_TRY(dalloc(I, &I->pair_out, kMaxPairBins + 1), "alloc");
   int64_t out[kMaxPairBins + 1];
   hipError_t e = pamc::launch_pair_hist(I, nbins, I->pair_out);
   if (e == hipSuccess) e = hipStreamSynchronize(I->stream);
@@ -2295,8 +2336,8 @@ double now_seconds() {
 }
 
 // Device bytes a sparse instance of this graph will hold: the allocation
-// plan of upload_sparse and prepare_run term by term (each allocation counts
-// at least 16 bytes, as dalloc does), with the colour-class count bounded by
+// plan of upload_sparse and prepare_run term by term (each buffer counts as the
+// piece of a block that it may be), with the colour-class count bounded by
 // the largest degree + 1.  It is an upper bound of the instance's
 // device_bytes, so admission against it never overruns the budget.  The
 // threshold table has 2X + 1 entries, X = max_v sum_j |w_vj| of this graph.
@@ -2304,7 +2345,7 @@ double now_seconds() {
 // field array either).
 int64_t estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pamc_config& cfg,
                        const pamc_schedule& sc, bool bits) {
-  auto a = [](int64_t bytes) { return std::max<int64_t>(bytes, 16); };
+  auto a = [](int64_t bytes) { return (int64_t)piece_bytes((size_t)bytes); };
   const int64_t R = cfg.replicas, np = (n + 3) & ~3, nnz = rp[n];
   int64_t maxdeg = 0, X = 0, gathered = 0;
   for (int32_t v = 0; v < n; ++v) {
@@ -2397,10 +2438,20 @@ pamc_status server_admit(pamc_server* S) {
       c.seed = q.seed;
       c.stream = S->stream;
       if (!st) st = open_device(I, &c);
-      if (!st) st = upload_sparse(I, p.h);
-      if (I) I->blocking = true;  // one run: its trace is made with the instance
-      if (!st) st = prepare_run(I, s);
-      if (I) I->blocking = false;
+      if (!st) st = upload_sparse(I, p.h, s.sweeps);
+      if (!st) {  // one run: its trace is made with the instance
+        Planning planning(I);
+        st = prepare_run(I, s);
+        if (!st) {
+          const hipError_t e = place_plan(I);
+          if (e != hipSuccess) st = dev_fail(e, "alloc run");
+        }
+      }
+      if (!st) {  // its runs are the server's batch's
+        delete I->self;
+        I->self = nullptr;
+        I->self_dirty = true;
+      }
       if (st) err = g_err;
     }
     q.prep.reset();

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/pamc.h"
@@ -149,10 +150,11 @@ struct pamc_instance {
   pamc::Batch* self = nullptr;
   bool self_dirty = true;
   // memory of the small buffers made with the instance: pieces of blocks that
-  // are released with it (not with a provider of its own, see dev_alloc)
-  std::vector<char*> blocks;
-  size_t block_used = 0;
-  bool blocking = false;
+  // are released with it (not with a provider of its own, see dalloc); while
+  // planning, the buffers of the next block and their bytes
+  std::vector<std::pair<char*, size_t>> blocks;
+  std::vector<std::pair<void**, size_t>> plan;
+  bool planning = false;
   int32_t self_sweeps = 1 << 30;  // sweeps per step that its launches were chosen for
   int32_t self_other = 0;         // sweep calls in a row that other launches would suit
   void* d_sched = nullptr;  // device copy of the run's schedule
@@ -298,9 +300,9 @@ struct Batch {
   const pamc_allocator* al = nullptr;
   void free_device();
   // outside arena mode and without a provider: one block whose pieces the
-  // descriptors and maps take, kept over rebuilds
+  // descriptors and maps take, kept over rebuilds that need no larger one
   char* block = nullptr;
-  size_t block_used = 0;
+  size_t block_cap = 0, block_used = 0;
   Batch() = default;
   Batch(const Batch&) = delete;
   Batch& operator=(const Batch&) = delete;

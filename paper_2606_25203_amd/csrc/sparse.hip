@@ -2706,10 +2706,9 @@ int Batch::group_of(const pamc_instance* I) {
   return 1 + 18 * (I->nhub ? 1 : 0) + 9 * wide + 3 * I->jmode + ti;
 }
 
-constexpr size_t kBatchBlock = 256 << 10;  // bytes of a batch's own block
 static void batch_free(Batch& b, void* p) {
   // pieces of an arena or of the batch's block are not freed by themselves
-  if (!p || b.arena || (b.block && (char*)p >= b.block && (char*)p < b.block + kBatchBlock)) return;
+  if (!p || b.arena || (b.block && (char*)p >= b.block && (char*)p < b.block + b.block_cap)) return;
   if (b.al)
     b.al->free(b.al->ctx, p, (void*)b.stream);
   else
@@ -2763,14 +2762,8 @@ hipError_t batch_alloc(Batch& b, void** p, size_t bytes) {
     return *p ? hipSuccess : hipErrorOutOfMemory;
   }
   if (!b.arena) {
-    // a dozen maps, most of them a few kilobytes, at each rebuild: an
-    // allocation and a release cost 20 us, a reset of a small instance 0.25 ms
     const size_t at = (b.block_used + 255) & ~(size_t)255;
-    if (bytes > kBatchBlock - std::min(at, kBatchBlock)) return hipMalloc(p, bytes);
-    if (!b.block) {
-      const hipError_t e = hipMalloc((void**)&b.block, kBatchBlock);
-      if (e != hipSuccess) return e;
-    }
+    if (at > b.block_cap || bytes > b.block_cap - at) return hipMalloc(p, bytes);
     *p = b.block + at;
     b.block_used = at + bytes;
     return hipSuccess;
@@ -3040,6 +3033,32 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
     if (insts[i]->dense || insts[i]->potts_K) continue;
     add_blocks(m_dh, i, pair_tiles(insts[i]->T), false);
     if (scheds) b.any_dh = 1;
+  }
+  if (!b.arena && !b.al) {
+    // One block for the descriptors and the dozen maps, of their size: an
+    // allocation and a release cost 20 us, at each rebuild of a small instance
+    // 0.25 ms in all.  (Without room for it they are allocated one by one.)
+    size_t need = sizeof(Desc) * b.n;
+    auto take = [&](size_t bytes) { need = ((need + 255) & ~(size_t)255) + bytes; };
+    for (const auto* m : {&m_init, &m_fields, &m_thr, &m_gather, &m_mis, &m_apply, &m_dh}) take(8 * m->size());
+    for (const auto& m : m_sweep) take(8 * m.size());
+    for (const auto& m : m_tile) take(8 * m.size());
+    if (b.n > 1) {  // a lone instance's bit-packed launches need none
+      for (const auto* v : {&m_bits, &m_bpack, &m_bunpack})
+        for (const auto& m : *v) take(8 * m.size());
+      take(sizeof(BitDesc) * bdesc.size());
+    }
+    if (need > b.block_cap) {
+      if (b.block) hipFree(b.block);
+      b.block = nullptr;
+      const size_t unit = b.n > 1 ? 65536 : 4096;
+      b.block_cap = (need + unit - 1) / unit * unit;
+      if (hipMalloc((void**)&b.block, b.block_cap) != hipSuccess) {
+        (void)hipGetLastError();
+        b.block = nullptr;
+        b.block_cap = 0;
+      }
+    }
   }
   hipError_t e = batch_alloc(b, (void**)&b.d_desc, sizeof(Desc) * b.n);
   if (e != hipSuccess) return e;
