@@ -316,13 +316,6 @@ struct HostSparse {
   std::vector<int32_t> brows, bent;
 };
 
-// A shape forced from the environment means the sweep kernels it names.
-bool shape_forced() {
-  for (const char* k : {"PAMC_TILE", "PAMC_TPW", "PAMC_QPW", "PAMC_JMODE"})
-    if (getenv(k)) return true;
-  return false;
-}
-
 // Field storage of a sparse graph: gathered at visit time (pull) or kept
 // incrementally (push); both give the same integer fields and trajectory.
 // Gathering a vertex's field costs its degree at every visit; keeping it
@@ -356,6 +349,31 @@ bool choose_fields(int32_t n, const int32_t* rp, uint32_t flags, bool potts, std
     return true;
   }
   return h.empty() && (int64_t)rp[n] <= 16 * (int64_t)n;
+}
+
+// Small instances sweep tile-resident: the spins sit in LDS, so gathering is
+// cheap whatever the degree, and no field array is kept (PAMC_TILE = 0: never).
+bool takes_tile(int64_t nq, int64_t X, uint32_t flags, bool potts) {
+  const char* e = getenv("PAMC_TILE");
+  return !potts && !(flags & PAMC_FLAG_FIELDS_PUSH) && tile_fits(nq, X) && !(e && atoi(e) == 0);
+}
+
+// A shape forced from the environment means the sweep kernels it names.
+bool shape_forced() {
+  for (const char* k : {"PAMC_TILE", "PAMC_TPW", "PAMC_QPW", "PAMC_JMODE"})
+    if (getenv(k)) return true;
+  return false;
+}
+
+// Whether a graph sweeps bit-packed (PAMC_BITS = 0: never): the magnitude of
+// its couplings, or 0; see one_magnitude.  hubs: it keeps hubs' fields.
+int32_t takes_bits(int32_t n, const int32_t* rp, const int32_t* J, uint32_t flags, bool potts, bool hubs, bool* both,
+                   int64_t* padded) {
+  *both = false;
+  *padded = 0;
+  const char* e = getenv("PAMC_BITS");
+  if (potts || hubs || (flags & PAMC_FLAG_FIELDS_PUSH) || shape_forced() || (e && atoi(e) == 0)) return 0;
+  return pamc::one_magnitude(n, rp, J, both, padded);
 }
 
 // Saturation-degree (DSATUR) colouring: the next vertex is the uncoloured
@@ -490,21 +508,17 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
   }
   std::vector<int32_t> hubs;
   h.pull = choose_fields(n, rp, flags, h.potts_K != 0, &hubs) ? 1 : 0;
-  // Small instances sweep tile-resident (see below): the spins sit in LDS,
-  // so gathering is cheap whatever the degree, and no field array is kept.
-  h.tile = (!h.potts_K && !(flags & PAMC_FLAG_FIELDS_PUSH) && tile_fits(h.nq, X)) ? 1 : 0;
-  if (const char* e = getenv("PAMC_TILE")) h.tile = h.tile && atoi(e) != 0 ? 1 : 0;
+  h.tile = takes_tile(h.nq, X, flags, h.potts_K != 0) ? 1 : 0;
   if (h.tile) {
     h.pull = 1;
     hubs.clear();
   }
-  // Couplings of one magnitude sweep bit-packed (PAMC_BITS = 0: never).
+  // Couplings of one magnitude sweep bit-packed.
   bool both_signs = false;
   int64_t padded = 0;  // entries of the rows padded to multiples of 4
-  const char* be = getenv("PAMC_BITS");
-  if (h.allow_bits && !h.potts_K && !(flags & PAMC_FLAG_FIELDS_PUSH) && hubs.empty() && !shape_forced() &&
-      !(be && atoi(be) == 0)) {
-    const int32_t c = pamc::one_magnitude(n, rp, Jin.data(), &both_signs, &padded);
+  if (h.allow_bits) {
+    const int32_t c =
+        takes_bits(n, rp, Jin.data(), flags, h.potts_K != 0, !hubs.empty(), &both_signs, &padded);
     if (c > 0) {
       h.bits_ok = 1;
       h.pull = 1;
@@ -610,6 +624,7 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
   // batches of 48 mixed instances, 13 of them such, R = 256: 41.7 and 42.1, R =
   // 1024: 59.9 and 55.2; of 96, 36 of them such, R = 512: 51.3 and 70.9.
   if (h.bits_ok) {
+    const char* be = getenv("PAMC_BITS");
     h.bits_always = be && atoi(be) == 1;
     h.bits_ok = h.bits = h.tile != 2 || h.bits_always;
   }
@@ -2358,12 +2373,11 @@ int64_t estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pam
   }
   std::vector<int32_t> hubs;
   bool pull = choose_fields(n, rp, cfg.flags, false, &hubs);
-  const bool tile = !(cfg.flags & PAMC_FLAG_FIELDS_PUSH) && tile_fits(np / 4, X);
+  const bool tile = takes_tile(np / 4, X, cfg.flags, false);  // (keeps no hubs' fields)
   const int64_t ncls = maxdeg + 1;
   bool both;
   int64_t padded;
-  bits = bits && !(cfg.flags & PAMC_FLAG_FIELDS_PUSH) && hubs.empty() &&
-         pamc::one_magnitude(n, rp, w, &both, &padded) > 0;
+  bits = bits && takes_bits(n, rp, w, cfg.flags, false, !tile && !hubs.empty(), &both, &padded) > 0;
   if (bits) pull = true;
   int64_t b = a(4 * (int64_t)(n + 1)) + 2 * a(4 * (nnz + 16));                 // CSR
   if (pull || tile) b += a(4 * (int64_t)(n + 1)) + 2 * a(4 * std::max<int64_t>(gathered, 4));  // gathered CSR

@@ -1,5 +1,8 @@
 """The server's memory budget against what the device reports: many small
 requests running at once hold no more than the budget."""
+import time
+
+import numpy as np
 import pytest
 
 import synth
@@ -36,3 +39,58 @@ def test_small_requests_stay_within_the_budget():
     held = base - free
     print(f"  counted {counted} bytes, held {held}", flush=True)
     assert counted <= budget and held <= budget - few
+
+
+def star(n, leaves):
+    """A path over n vertices with vertex 0 also joined to the last `leaves`."""
+    u = list(range(n - 1)) + [0] * leaves
+    v = list(range(1, n)) + list(range(n - leaves, n))
+    return synth.csr_from_edges(n, np.array(u), np.array(v), np.ones(len(u), np.int32))
+
+
+FORMS = {
+    # unit weights and long enough rows for incremental fields, kept from the
+    # bit-packed form by the environment
+    "no_bits": (lambda: synth.random_graph(2600, 44200, 3), None, {"PAMC_BITS": "0"}),
+    "shape": (lambda: synth.random_graph(2600, 44200, 3), None, {"PAMC_QPW": "1"}),
+    "no_tile": (lambda: synth.random_graph(300, 6000, 3), None, {"PAMC_TILE": "0"}),
+    # rows of 65 to 256 entries in a graph small enough for tiles
+    "pull_star": (lambda: star(300, 200), "pull", {}),
+    "star": (lambda: star(300, 200), None, {}),
+    "push": (lambda: synth.torus(20, 20, 1), "push", {}),
+    "plain": (lambda: synth.random_graph(2601, 20000, 3), None, {}),
+}
+
+
+@pytest.mark.parametrize("name", list(FORMS))
+def test_admission_by_an_upper_bound(monkeypatch, name):
+    """A budget one byte short of what two requests take: they do not run
+    together, unless in a form that takes less."""
+    from paper_2606_25203_amd import pamc
+    make, fields, env = FORMS[name]
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    g = make()
+    sched = pamc.schedule(beta0=0.1, dbeta=0.1, steps=6, sweeps=2)
+    print("case admission", name, flush=True)
+
+    def most_in_use(budget):
+        srv = pamc.Server(budget, 2, replicas=128, fields=fields)
+        try:
+            for seed in (5, 6):
+                srv.submit(g, seed, sched)
+        except pamc.PamcError as e:  # refused: that holds nothing
+            assert e.status == pamc.PAMC_ERR_OUT_OF_MEMORY
+            srv.close()
+            return 0, 0
+        time.sleep(0.5)  # both prepared
+        busy = (1, 0)
+        while any(busy):
+            busy = srv.tick(2)
+        st = srv.stats()
+        assert st["finished"] == 2
+        srv.close()
+        return st["peak_bytes"], st["peak_active"]
+
+    both, together = most_in_use(1 << 30)
+    assert together == 2 and most_in_use(both - 1)[0] < both
