@@ -273,20 +273,6 @@ pamc::Batch* self_batch(pamc_instance* I, hipError_t* err) {
   return I->self;
 }
 
-// Before a run (or, for several calls alike, a sweep call) of this many sweeps
-// per step: the batch is rebuilt where that changes its launches.
-void self_for_sweeps(pamc_instance* I, int32_t sweeps, bool run) {
-  if (I->dense || I->bits != 1 || I->bits_always) return;
-  const int32_t least = pamc::bits_min_sweeps(std::vector<pamc_instance*>{I});
-  if ((sweeps >= least) == (I->self_sweeps >= least)) {
-    I->self_other = 0;
-  } else if (run || I->self_dirty || ++I->self_other >= 3) {
-    I->self_sweeps = sweeps;
-    I->self_other = 0;
-    I->self_dirty = true;
-  }
-}
-
 #define SELF_BATCH(I, var)                                  \
   hipError_t var##_err;                                     \
   pamc::Batch* var = self_batch(I, &var##_err);             \
@@ -1363,7 +1349,6 @@ pamc_status pamc_sweep(pamc_instance* I, double beta, int32_t nsweeps) {
   if (I->potts_K && beta < 0) return fail(PAMC_ERR_INVALID_ARG, "negative beta on Potts labels");
   if (nsweeps == 0) return PAMC_OK;
   hipSetDevice(I->device);
-  self_for_sweeps(I, nsweeps, false);
   SELF_BATCH(I, b);
   if (I->dense) {
     HIP_TRY(pamc::launch_dense_prim_sweep(*b, beta, nsweeps), "dense sweep");
@@ -1555,7 +1540,6 @@ pamc_status pamc_anneal(pamc_instance* I, const pamc_schedule* sched, pamc_resul
     st = set_field_mode(I, true);
     if (st) return st;
   }
-  self_for_sweeps(I, s.sweeps, true);
   SELF_BATCH(I, b);
   auto run_flags = [&](pamc::Batch* x) {
     x->max_sweeps = std::max(s.sweeps, 1);

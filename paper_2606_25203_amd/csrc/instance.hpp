@@ -155,8 +155,6 @@ struct pamc_instance {
   std::vector<std::pair<char*, size_t>> blocks;
   std::vector<std::pair<void**, size_t>> plan;
   bool planning = false;
-  int32_t self_sweeps = 1 << 30;  // sweeps per step that its launches were chosen for
-  int32_t self_other = 0;         // sweep calls in a row that other launches would suit
   void* d_sched = nullptr;  // device copy of the run's schedule
   int64_t* pair_out = nullptr;  // pair-distance histogram and sum (allocated at its first call)
 };
@@ -277,6 +275,9 @@ struct Batch {
   BitDesc* d_bits = nullptr;
   BitDesc lone_bits;  // the descriptor of a batch of one
   bool has_bits = false;
+  // an instance's own batch holds the launches of both forms where the choice
+  // depends on the sweeps of a step: bit-packed from this many
+  int32_t bits_from = 1;
   Desc* d_desc = nullptr;
   int32_t n = 0;
   hipStream_t stream = nullptr;

@@ -1548,15 +1548,18 @@ __global__ void k_commit(const Desc* __restrict__ D, int32_t ninst, int32_t in_r
 // the instance's first block also commits the step's resampling / cluster
 // move (commit = in_run); no field read here is changed by that.
 __global__ void __launch_bounds__(256) k_thresholds(const Desc* __restrict__ D,
-                                                    const uint64_t* __restrict__ map, int32_t commit) {
+                                                    const uint64_t* __restrict__ map, int32_t commit,
+                                                    int32_t bit_sweeps) {
   int inst, lb;
   if (!resolve(map, inst, lb)) return;
   const Desc& d = D[inst];
   const RunState* st = d.st;
+  const bool bits = d.bits && bit_sweeps > 0;
+  const int bsw = bits ? min(bit_sweeps, d.order_cap) : 0;  // sweeps whose phases will be launched
   if (!st->active) {
     // an instance at rest: its bit-packed phases are empty
-    if (d.bits && lb == 0)
-      for (int i = threadIdx.x; i < d.order_cap * d.ncls; i += blockDim.x)
+    if (lb == 0)
+      for (int i = threadIdx.x; i < bsw * d.ncls; i += blockDim.x)
         reinterpret_cast<int4*>(d.bphases)[i] = make_int4(0, 0, 0, 0);
     return;
   }
@@ -1570,7 +1573,7 @@ __global__ void __launch_bounds__(256) k_thresholds(const Desc* __restrict__ D,
   if (d.potts_K) {  // e^{beta (syn_k - max syn)} for max syn - syn_k = i
     for (int64_t i = (int64_t)lb * blockDim.x + threadIdx.x; i <= Xt; i += (int64_t)kThrBlocks * blockDim.x)
       d.ptab[i] = exp_cw(beta * (double)(-i));
-  } else if (d.bits) {
+  } else if (bits) {
     // bit-packed sweeps: entry i of one half is T[c (i - X)], of the other
     // T[-c (i - X)] (X the longest row, c the coupling's magnitude)
     const int32_t half = 2 * d.bmaxdeg + 2;
@@ -1617,7 +1620,7 @@ __global__ void __launch_bounds__(256) k_thresholds(const Desc* __restrict__ D,
         for (int i = threadIdx.x; i < ns * ncls; i += blockDim.x) {
           const int32_t c = perm[i];
           d.order[s0 * ncls + i] = c;
-          if (d.bits)  // the phases in visiting order
+          if (bits)  // the phases in visiting order
             reinterpret_cast<int4*>(d.bphases)[s0 * ncls + i] =
                 make_int4(d.class_ptr[c], d.class_ptr[c + 1], (int32_t)(st->gs + (uint32_t)(s0 + i / ncls)), st->cur);
         }
@@ -1635,14 +1638,14 @@ __global__ void __launch_bounds__(256) k_thresholds(const Desc* __restrict__ D,
           o[i] = o[j];
           o[j] = t;
         }
-        if (d.bits)
+        if (bits)
           for (int k = 0; k < ncls; ++k)
             reinterpret_cast<int4*>(d.bphases)[(size_t)s * ncls + k] =
                 make_int4(d.class_ptr[o[k]], d.class_ptr[o[k] + 1], (int32_t)gs, st->cur);
       }
     }
-    if (d.bits)  // sweeps that other instances of a batch still make
-      for (int i = nsw * d.ncls + threadIdx.x; i < d.order_cap * d.ncls; i += blockDim.x)
+    if (bits)  // sweeps that other instances of a batch still make
+      for (int i = nsw * d.ncls + threadIdx.x; i < bsw * d.ncls; i += blockDim.x)
         reinterpret_cast<int4*>(d.bphases)[i] = make_int4(0, 0, 0, 0);
   }
 }
@@ -2874,14 +2877,19 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
   b.stream = insts[0]->stream;
   std::vector<Desc> desc(b.n);
   const int64_t push_wgs = push_budget(insts);
-  int32_t most_sweeps = b.n == 1 && !scheds ? insts[0]->self_sweeps : 1;
+  // An instance's own batch is called with any number of sweeps a step, so it
+  // holds the launches of both forms; a batch of runs knows its schedules'.
+  const bool own = b.n == 1 && !scheds;
+  int32_t most_sweeps = 1;
   if (scheds)
     for (const Schedule& s : *scheds) most_sweeps = std::max(most_sweeps, s.sweeps);
-  const bool enough = most_sweeps >= bits_min_sweeps(insts);
+  const int32_t least = bits_min_sweeps(insts);
+  b.bits_from = own && !insts[0]->bits_always ? least : 1;
   auto sweeps_bits = [&](int i) {
     const pamc_instance* I = insts[i];
-    return allow_bits && !I->dense && I->bits && (enough || I->bits_always);
+    return allow_bits && !I->dense && I->bits && (I->bits_always || (own ? least != INT32_MAX : most_sweeps >= least));
   };
+  auto sweeps_other = [&](int i) { return !sweeps_bits(i) || b.bits_from > 1; };
   bool any_bits = false;
   for (int i = 0; i < b.n; ++i) {
     desc[i] = make_desc(insts[i]);
@@ -2940,7 +2948,7 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
   {
     int64_t mt = 0;
     for (int i = 0; i < b.n; ++i)
-      if (!insts[i]->dense && insts[i]->tile == 2 && !sweeps_bits(i)) mt += insts[i]->T;
+      if (!insts[i]->dense && insts[i]->tile == 2 && sweeps_other(i)) mt += insts[i]->T;
     b.tmma_groups = mt <= kMfmaGroupTiles;
     if (const char* g = getenv("PAMC_TMMA_GROUPS")) b.tmma_groups = atoi(g) != 0;
   }
@@ -2953,8 +2961,9 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
     add_blocks(m_fields, i, field_blocks(I), false);
     add_blocks(m_thr, i, kThrBlocks, false);
     add_blocks(m_gather, i, (int64_t)I->T * ((I->nq + kGatherQuadsPerBlock - 1) / kGatherQuadsPerBlock), true);
-    if (sweeps_bits(i)) {
-      bit_insts.push_back(i);
+    if (sweeps_bits(i)) bit_insts.push_back(i);
+    if (!sweeps_other(i)) {
+      // bit-packed only
     } else if (I->tile == 2) {  // the same with matrix-core fields
       add_blocks(m_tile[3], i, (int64_t)I->T * (b.tmma_groups ? 4 : 1), false);
       b.tile_lds[3] = std::max<int64_t>(b.tile_lds[3], tmma_lds_bytes(I->nks, b.tmma_groups ? 16 : 64));
@@ -3171,16 +3180,19 @@ static inline int tgrid(int n) { return (n + 63) / 64; }
 static hipError_t batch_sweeps(Batch& b, int32_t nsweeps, int32_t commit = -1) {
   pamc_instance* P = b.I[0];
   const bool prof = P->prof && !b.arena;
-  if (b.thr.grid) k_thresholds<<<b.thr.grid, 256, 0, b.stream>>>(b.d_desc, b.thr.map, commit);
+  const bool bits = b.has_bits && nsweeps >= b.bits_from;
+  const bool other = !bits || b.bits_from <= 1;  // also: the other instances' of a batch
+  if (b.thr.grid)
+    k_thresholds<<<b.thr.grid, 256, 0, b.stream>>>(b.d_desc, b.thr.map, commit, bits ? nsweeps : 0);
   int64_t launches = 0;
   if (prof) hipEventRecord(next_event(P), b.stream);
   static const SweepTileKernel tile_kernels[3] = {k_sweep_tile<0>, k_sweep_tile<1>, k_sweep_tile<2>};
   for (int g = 0; g < 3; ++g)
-    if (b.tile[g].grid) {  // every sweep of the step, in one launch
+    if (other && b.tile[g].grid) {  // every sweep of the step, in one launch
       tile_kernels[g]<<<b.tile[g].grid, kTileWaves * 64, b.tile_lds[g], b.stream>>>(b.d_desc, b.tile[g].map);
       ++launches;
     }
-  if (b.tile[3].grid) {
+  if (other && b.tile[3].grid) {
     if (b.tmma_groups)
       k_sweep_tmma_g<8><<<b.tile[3].grid, 8 * 64, b.tile_lds[3], b.stream>>>(b.d_desc, b.tile[3].map);
     else if (b.tmma_waves == 8)
@@ -3189,7 +3201,7 @@ static hipError_t batch_sweeps(Batch& b, int32_t nsweeps, int32_t commit = -1) {
       k_sweep_tmma<16><<<b.tile[3].grid, 16 * 64, b.tile_lds[3], b.stream>>>(b.d_desc, b.tile[3].map);
     ++launches;
   }
-  int max_ncls = b.max_ncls;
+  int max_ncls = other ? b.max_ncls : 0;
   BitLaunch bl;
   bl.D = b.d_bits;
   if (b.n == 1) bl.lone = b.lone_bits;
@@ -3198,7 +3210,7 @@ static hipError_t batch_sweeps(Batch& b, int32_t nsweeps, int32_t commit = -1) {
     return bl;
   };
   for (int f = 0; f < Batch::kBitForms; ++f)
-    if (b.bit_pack[f].grid) {
+    if (bits && b.bit_pack[f].grid) {
       launch_bits_pack(f, bits_map(b.bit_pack[f]), b.bit_pack[f].grid, true, b.stream);
       for (int r = 0; r < 2; ++r) max_ncls = std::max(max_ncls, (int)b.bit_grid[r][f].size());
     }
@@ -3206,19 +3218,19 @@ static hipError_t batch_sweeps(Batch& b, int32_t nsweeps, int32_t commit = -1) {
     for (int p = 0; p < max_ncls; ++p) {
       for (int r = 0; r < 2; ++r)
         for (int f = 0; f < Batch::kBitForms; ++f) {
-          if (p >= (int)b.bit_grid[r][f].size()) continue;
+          if (!bits || p >= (int)b.bit_grid[r][f].size()) continue;
           launch_bits_sweep(r, f, bits_map(b.bit_sweep[r][f]), b.bit_grid[r][f][p], s, p, b.stream);
           ++launches;
         }
       for (int g = 0; g < Batch::kGroups; ++g) {
-        if (!b.sweep[g].grid || p >= b.group_ncls[g]) continue;  // no instance of the group has class p
+        if (!other || !b.sweep[g].grid || p >= b.group_ncls[g]) continue;  // no instance of the group has class p
         sweep_kernel_of_group(g)<<<b.sweep[g].grid, 256, 0, b.stream>>>(b.d_desc, b.sweep[g].map, s, p);
         ++launches;
       }
     }
   }
   for (int f = 0; f < Batch::kBitForms; ++f)
-    if (b.bit_unpack[f].grid) launch_bits_pack(f, bits_map(b.bit_unpack[f]), b.bit_unpack[f].grid, false, b.stream);
+    if (bits && b.bit_unpack[f].grid) launch_bits_pack(f, bits_map(b.bit_unpack[f]), b.bit_unpack[f].grid, false, b.stream);
   if (prof) {
     hipEventRecord(next_event(P), b.stream);
     P->prof_launches += launches;
@@ -3415,7 +3427,7 @@ hipError_t ctl_thresholds(Batch& b) {
     e = hipMemcpy(b.thr_dense.map, m.data(), sizeof(uint64_t) * m.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) return e;
   }
-  k_thresholds<<<b.thr_dense.grid, 256, 0, b.stream>>>(b.d_desc, b.thr_dense.map, -1);
+  k_thresholds<<<b.thr_dense.grid, 256, 0, b.stream>>>(b.d_desc, b.thr_dense.map, -1, 0);
   return hipGetLastError();
 }
 hipError_t ctl_step_end(Batch& b, int32_t in_run) {

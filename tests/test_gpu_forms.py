@@ -5,6 +5,7 @@ results as in the other forms."""
 import numpy as np
 import pytest
 
+import oracle
 import synth
 
 pytestmark = pytest.mark.gpu
@@ -44,3 +45,45 @@ def test_matrix_core_batch_is_one_launch_a_step(pamc, weights, count):
         alone.close()
     for i in insts:
         i.close()
+
+
+@pytest.mark.parametrize("gname", ["tile", "pull", "torus"])
+def test_sweep_counts_change_no_launch_state(pamc, gname):
+    """Sweep calls of few and of many sweeps, each in its own form, leave what
+    the others' launches use in place: a captured sequence of both can be
+    replayed after (and between) eager calls of either, and takes no wait
+    while it is captured."""
+    import torch
+    g = {"tile": lambda: synth.random_graph(150, 500, 3, weights="pm1"),
+         "pull": lambda: synth.random_graph(2600, 7000, 4, weights="pm1"),
+         "torus": lambda: synth.torus(50, 48, 5)}[gname]()
+    stream = torch.cuda.Stream()
+    inst = pamc.Instance.csr(g, replicas=128, seed=5, stream=stream.cuda_stream)
+    o = oracle.Oracle.sparse(g.n, g.row_ptr, g.col, g.w, 128, 5)
+
+    def eager(betas):
+        for beta, k in betas:
+            inst.sweep(beta, k)
+            o.sweep(beta, k)
+
+    def same(what):
+        for name, a, b in zip(("spins", "fields", "energies", "family"), inst.state(), o.state()):
+            assert np.array_equal(a, b), f"{what}: {name} differ"
+
+    print("case captured sweeps", gname, flush=True)
+    eager([(0.2, 6)])
+    same("before")
+    captured = [(0.3, 1), (0.35, 1), (0.4, 1), (0.45, 1), (0.5, 7), (0.5, 7), (0.55, 7), (0.6, 1)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        for beta, k in captured:
+            inst.sweep(beta, k)
+    for rep in range(4):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        for beta, k in captured:
+            o.sweep(beta, k)
+        same(f"replay {rep}")
+        eager([(0.3, 1)] * 4 if rep % 2 else [(0.3, 6)] * 4)
+        same(f"after replay {rep}")
+    inst.close()
