@@ -296,8 +296,7 @@ struct HostSparse {
   int32_t hub_tpw = 1, hub_qpw = 1, push_tpw = 1, push_qpw = 1;  // the two forms' wave shapes
   int64_t nnz = 0, W = 0, X = 0;
   std::vector<int32_t> class_ptr, to_internal, to_input, rp2, col2, J2, grow, gcol, gJ, hubJ;
-  int32_t bits_ok = 0, bits = 0, bcoup = 0, bcopies = 1, bmaxdeg = 0, bstride = 0;  // bit-packed sweeps
-  bool bits_always = false;
+  int32_t bits_ok = 0, bits_from = 0, bcoup = 0, bcopies = 1, bmaxdeg = 0, bstride = 0;  // bit-packed sweeps
   int32_t allow_bits = 1;  // set by the caller
   std::vector<int32_t> brows, bent;
 };
@@ -611,8 +610,8 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
   // 1024: 59.9 and 55.2; of 96, 36 of them such, R = 512: 51.3 and 70.9.
   if (h.bits_ok) {
     const char* be = getenv("PAMC_BITS");
-    h.bits_always = be && atoi(be) == 1;
-    h.bits_ok = h.bits = h.tile != 2 || h.bits_always;
+    h.bits_from = be && atoi(be) == 1 ? 1 : 0;
+    h.bits_ok = h.tile != 2 || h.bits_from;
   }
   // Rows of the bit-packed sweeps: the higher neighbours first (the energy
   // sum's edges), padded to multiples of 4 with the mask that is always 0.
@@ -675,8 +674,9 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
 }
 
 // Sweep shapes chosen by pamc_autotune, per instance shape (this process).
+// bits_from: see pamc_instance.
 struct TuneShape {
-  int32_t tile, tpw, qpw, bits;
+  int32_t tile, tpw, qpw, bits_from;
 };
 
 std::mutex g_tune_mutex;
@@ -692,8 +692,7 @@ std::string tune_key(const pamc_instance* I) {
 
 void apply_shape(pamc_instance* I, const TuneShape& t) {
   I->tile = t.tile;
-  I->bits = t.bits;
-  I->bits_always = t.bits == 1;
+  I->bits_from = t.bits_from;
   I->tpw = t.tpw;
   I->qpw = t.qpw;
   if (I->dual && !I->pull) {  // the incremental-field form's shape
@@ -706,7 +705,7 @@ void apply_shape(pamc_instance* I, const TuneShape& t) {
 // A new instance of a shape the autotuner has seen takes its choice (unless
 // a shape is forced from the environment).
 void apply_cached_shape(pamc_instance* I) {
-  if (getenv("PAMC_TPW") || getenv("PAMC_QPW") || getenv("PAMC_TILE")) return;
+  if (getenv("PAMC_TPW") || getenv("PAMC_QPW") || getenv("PAMC_TILE") || getenv("PAMC_BITS")) return;
   std::lock_guard<std::mutex> g(g_tune_mutex);
   auto it = g_tune_cache.find(tune_key(I));
   if (it != g_tune_cache.end()) apply_shape(I, it->second);
@@ -753,8 +752,7 @@ pamc_status upload_sparse(pamc_instance* I, HostSparse& h, int32_t sweeps = 0) {
   I->push_tpw = h.push_tpw;
   I->push_qpw = h.push_qpw;
   I->bits_ok = h.bits_ok;
-  I->bits = h.bits;
-  I->bits_always = h.bits_always;
+  I->bits_from = h.bits_from;
   I->bcoup = h.bcoup;
   I->bcopies = h.bcopies;
   I->bmaxdeg = h.bmaxdeg;
@@ -2032,7 +2030,7 @@ pamc_status pamc_autotune(pamc_instance* I, double beta, int32_t sweeps, int32_t
     return fail(PAMC_ERR_INVALID_ARG, "bad tuning sweeps or beta");
   hipSetDevice(I->device);
   memset(out, 0, sizeof *out);
-  const TuneShape initial{I->tile, I->tpw, I->qpw, I->bits};
+  const TuneShape initial{I->tile, I->tpw, I->qpw, I->bits_from};
   const std::string key = tune_key(I);
   if (!force) {
     std::lock_guard<std::mutex> g(g_tune_mutex);
@@ -2046,20 +2044,24 @@ pamc_status pamc_autotune(pamc_instance* I, double beta, int32_t sweeps, int32_t
       return PAMC_OK;
     }
   }
-  std::vector<TuneShape> cand;
-  if (I->bits_ok) cand.push_back({initial.tile, initial.tpw, initial.qpw, 1});  // bit-packed
-  if (I->tmma_ok) cand.push_back({2, initial.tpw, initial.qpw, 0});  // matrix-core fields
+  constexpr int32_t kNever = INT32_MAX;
+  std::vector<TuneShape> cand;  // the bit-packed form of the steps' sweeps, and the other forms
+  if (I->bits_ok) cand.push_back({initial.tile, initial.tpw, initial.qpw, 1});
+  if (I->tmma_ok) cand.push_back({2, initial.tpw, initial.qpw, kNever});  // matrix-core fields
   for (int tile : {0, 1}) {
     if (tile && !I->tile_ok) continue;
     if (tile) {
-      cand.push_back({1, initial.tpw, initial.qpw, 0});  // the tile-resident sweep ignores the wave shape
+      cand.push_back({1, initial.tpw, initial.qpw, kNever});  // the tile-resident sweep ignores the wave shape
       continue;
     }
     for (int tpw : {1, 2, 4}) {
       if (tpw > 1 && (!I->pull || I->potts_K || I->T % tpw)) continue;
-      for (int qpw : {1, 2, 4}) cand.push_back({0, tpw, qpw, 0});
+      for (int qpw : {1, 2, 4}) cand.push_back({0, tpw, qpw, kNever});
     }
   }
+  // the sweeps per step from which the instance sweeps bit-packed as it is
+  int32_t from = kNever;
+  if (I->bits_ok) from = I->bits_from ? I->bits_from : pamc::bits_min_sweeps(std::vector<pamc_instance*>{I});
   // scratch copy of the run state and of what sweeps change
   pamc::RunState st0;
   pamc_status st = read_state(I, &st0);
@@ -2084,7 +2086,7 @@ pamc_status pamc_autotune(pamc_instance* I, double beta, int32_t sweeps, int32_t
     if (r == hipSuccess) r = hipMemcpy(I->st, &st0, sizeof st0, hipMemcpyHostToDevice);
     return r;
   };
-  double best = 1e300, dflt = -1.0;
+  double best = 1e300, bits_ms = 1e300, dflt = -1.0;
   TuneShape best_shape = initial;
   for (const TuneShape& c : cand) {
     if (e != hipSuccess) break;
@@ -2106,8 +2108,11 @@ pamc_status pamc_autotune(pamc_instance* I, double beta, int32_t sweeps, int32_t
     }
     if (e != hipSuccess) break;
     const double per = ms / sweeps;
-    if (c.tile == initial.tile && c.tpw == initial.tpw && c.qpw == initial.qpw && c.bits == initial.bits) dflt = per;
-    if (per < best) {
+    const bool bits = c.bits_from == 1;
+    if (bits == (sweeps >= from) && c.tile == initial.tile && c.tpw == initial.tpw && c.qpw == initial.qpw) dflt = per;
+    if (bits) {
+      bits_ms = per;
+    } else if (per < best) {
       best = per;
       best_shape = c;
     }
@@ -2121,6 +2126,13 @@ pamc_status pamc_autotune(pamc_instance* I, double beta, int32_t sweeps, int32_t
     apply_shape(I, initial);
     return dev_fail(e, "autotune");
   }
+  // Packing pays from some number of sweeps on: these sweeps were enough, or
+  // more are.
+  best_shape.bits_from = !I->bits_ok ? initial.bits_from
+                         : bits_ms < best ? std::min(from, sweeps)
+                         : sweeps == kNever ? kNever
+                                            : std::max(from, sweeps + 1);
+  best = std::min(best, bits_ms);
   apply_shape(I, best_shape);
   {
     std::lock_guard<std::mutex> g(g_tune_mutex);

@@ -98,8 +98,7 @@ struct pamc_instance {
   int32_t order_cap = 0;
   // bit-packed sweeps: every coupling is +-|bcoup| (bits.hip)
   int32_t bits_ok = 0;      // possible
-  int32_t bits = 0;         // taken for the sweeps of steps of bits_min_sweeps and more
-  bool bits_always = false; // ... and of steps of fewer
+  int32_t bits_from = 0;    // taken for steps of this many sweeps and more (INT32_MAX: never); 0: of bits_min_sweeps
   int32_t bcoup = 0;        // the coupling's magnitude; negative when every coupling is
   int32_t bcopies = 1;      // 2: couplings of both signs, masks kept with their complements
   int32_t bmaxdeg = 0;      // the longest row
@@ -215,7 +214,7 @@ struct Desc {
   int32_t n, np, nq, R, T, ncls, rule, pull, dense, shuffle, tr_cap, order_cap, qpw;
   int32_t sweep_stride;   // incremental-field sweeps: a tile's work-groups take chunks c, c + stride, ...
   uint32_t k0, k1;
-  // bit-packed sweeps (bits != 0): what k_thresholds fills for them
+  // bit-packed sweeps (bits: the batch holds their launches): what k_thresholds fills for them
   uint32_t* btab;
   int32_t* bphases;
   int32_t bits, bcoup, bmaxdeg, bpad;
@@ -352,8 +351,8 @@ hipError_t launch_refresh_fields(Batch& b);
 // nbins), their sum after them
 hipError_t launch_pair_hist(pamc_instance* I, int32_t nbins, int64_t* out_dev);
 int32_t cluster_max_n();
-// The fewest sweeps per step from which instances of bits != 0 sweep
-// bit-packed as one batch.
+// The fewest sweeps per step from which instances without a bits_from of their
+// own sweep bit-packed as one batch.
 int32_t bits_min_sweeps(const std::vector<pamc_instance*>& insts);
 int32_t sweep_waves();  // wavefronts per sweep work-group
 int32_t tile_max_quads();  // vertex quads a tile-resident sweep holds in LDS

@@ -2653,7 +2653,6 @@ Desc make_desc(const pamc_instance* I) {
   d.k1 = (uint32_t)(I->seed >> 32);
   d.btab = I->btab;
   d.bphases = I->bphases;
-  d.bits = I->bits;
   d.bcoup = I->bcoup;
   d.bmaxdeg = I->bmaxdeg;
   d.not_monotone = I->dense ? reinterpret_cast<int32_t*>(I->flip_ctr + kMonotoneSlot) : nullptr;
@@ -2846,7 +2845,7 @@ int32_t bits_min_sweeps(const std::vector<pamc_instance*>& insts) {
   int64_t all_tiles = 0;
   int32_t ncls = 0, count = 0;
   for (const pamc_instance* I : insts) {
-    if (I->dense || !I->bits) continue;
+    if (I->dense || !I->bits_ok || I->bits_from) continue;
     const double deg = I->n > 0 ? (double)I->nnz / I->n : 0.0;
     tiles = tiles && I->tile == 1;
     tile_us = std::max(tile_us, I->n * (0.02 + 0.0023 * deg) + I->ncls);
@@ -2884,10 +2883,11 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
   if (scheds)
     for (const Schedule& s : *scheds) most_sweeps = std::max(most_sweeps, s.sweeps);
   const int32_t least = bits_min_sweeps(insts);
-  b.bits_from = own && !insts[0]->bits_always ? least : 1;
+  auto bits_from = [&](int i) { return insts[i]->bits_from ? insts[i]->bits_from : least; };
+  b.bits_from = own ? bits_from(0) : 1;
   auto sweeps_bits = [&](int i) {
     const pamc_instance* I = insts[i];
-    return allow_bits && !I->dense && I->bits && (I->bits_always || (own ? least != INT32_MAX : most_sweeps >= least));
+    return allow_bits && !I->dense && I->bits_ok && (own ? bits_from(i) != INT32_MAX : most_sweeps >= bits_from(i));
   };
   auto sweeps_other = [&](int i) { return !sweeps_bits(i) || b.bits_from > 1; };
   bool any_bits = false;

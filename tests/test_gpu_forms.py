@@ -87,3 +87,41 @@ def test_sweep_counts_change_no_launch_state(pamc, gname):
         eager([(0.3, 1)] * 4 if rep % 2 else [(0.3, 6)] * 4)
         same(f"after replay {rep}")
     inst.close()
+
+
+def launches_of(pamc, inst, k):
+    pamc.pamc_profile_enable(inst.h, True)
+    inst.sweep(0.5, k)
+    n = pamc.pamc_profile_read(inst.h)["launches"]
+    pamc.pamc_profile_enable(inst.h, False)
+    return n
+
+
+@pytest.mark.parametrize("sweeps", [1, 40])
+def test_tuning_at_some_sweeps_keeps_the_choice_for_others(pamc, monkeypatch, sweeps):
+    """A small graph whose step of one sweep is one launch and whose steps of
+    many go bit-packed: tuned at either count, it still takes its form at the
+    other, a new instance of the shape does too, and one made under PAMC_BITS=1
+    goes bit-packed always."""
+    g = synth.random_graph(600 + sweeps, 2100, 3)  # a shape of its own: tuned shapes are remembered
+    make = lambda seed: pamc.Instance.csr(g, replicas=256, seed=seed)
+    inst = make(1)
+    ncls = inst.info().num_classes
+    print(f"case tuned at {sweeps}, {ncls} classes", flush=True)
+    other = 41 - sweeps
+    form = {1: 1, 40: 40 * ncls}
+    assert [launches_of(pamc, inst, k) for k in (1, 40)] == [form[1], form[40]]
+    before = inst.state()
+    t = inst.autotune(0.5, sweeps=sweeps, force=True)
+    assert t.candidates > 2 and t.best_ms_per_sweep <= t.default_ms_per_sweep
+    assert all(np.array_equal(a, b) for a, b in zip(before, inst.state()))
+    new = make(2)
+    for i in (inst, new):
+        assert launches_of(pamc, i, other) == form[other]
+    assert new.autotune(0.5, sweeps=other).cached == 1
+    assert launches_of(pamc, new, other) == form[other]
+    monkeypatch.setenv("PAMC_BITS", "1")
+    forced = make(3)
+    assert launches_of(pamc, forced, 1) == ncls
+    for i in (inst, new, forced):
+        i.close()
