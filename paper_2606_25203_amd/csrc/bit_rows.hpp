@@ -53,4 +53,37 @@ inline int32_t one_magnitude(int32_t n, const int32_t* rp, const int32_t* J, boo
   return c;
 }
 
+// How a graph of couplings of one magnitude keeps its fields when its longest
+// row is far longer than the others: one wavefront walks a row, so a phase then
+// lasts as long as that row whatever else it does.
+enum class LongRows { kBits, kGathered, kAsOthers };
+
+// Rows of more than 128 entries and more than 8 times the average are long
+// (none: kBits).  With them a population of at most two tiles, or of fewer than
+// 2^20 spins, is as long as its rows' chains in any form but incremental fields
+// (kAsOthers: what graphs of several magnitudes take); up to 2^24 spins gathering
+// shares the row's entries among the tiles of a wave, four with few masks in
+// flight do not; above that all rows together take longer.  From 16 neighbours
+// on average the other rows weigh more: bit-packed also below 2^20 (up to two
+// tiles) and 2^22 spins.  Runs of 20 steps of 1 (3) sweeps up to beta 4, fields
+// kept, gathered, bit-packed, ms; heavy-tailed degrees up to 256, average 8:
+// n = 3,000, R = 64: 1.35 (2.5), 1.64 (3.4), 1.73 (2.9); R = 1,024: 1.73 (3.4),
+// 1.58 (3.1), 2.49 (4.1); n = 20,000, R = 64: 1.67 (3.3), 2.04 (4.4), 2.31 (4.0);
+// R = 256: 2.27 (4.7), 2.11 (4.5), 3.51 (6.2); R = 1,024: 4.33 (10.2), 3.42 (8.2),
+// 4.29 (7.7).  Average 20: n = 3,000, R = 512: 2.12 (4.5), 2.51 (6.1), 2.39 (4.8);
+// n = 20,000, R = 256: 3.11 (7.0), 3.63 (7.9), 5.19 (10.1).  Average 34, R = 512,
+// n = 20,000: 5.68 (14.2), 6.40 (17.0), 6.60 (13.3).  Up to beta 1, where flips
+// are many: average 8, n = 20,000, R = 256: 3.18 (7.7), 2.30 (5.1), 3.54 (6.3);
+// average 20: 4.54 (12.0), 3.70 (8.4), 5.18 (10.1), n = 3,000, R = 512: 2.61 (6.2),
+// 2.54 (6.2), 2.42 (4.9).  A graph whose only rows
+// above 64 are one or two keeps those rows' fields in either form (kAsOthers).
+inline LongRows long_row_form(int64_t n, int64_t entries, int64_t maxdeg, int64_t above64, int64_t tiles) {
+  if (maxdeg <= 128 || maxdeg * n <= 8 * entries) return LongRows::kBits;
+  const bool few = entries < 16 * n;
+  const int64_t spins = 64 * n * tiles, million = 1 << 20;
+  if (tiles <= 2 ? few || spins >= million : few && spins < million) return LongRows::kAsOthers;
+  if (tiles <= 2 || spins < (few ? 1 : 4) * million || spins >= 16 * million) return LongRows::kBits;
+  return above64 <= 2 ? LongRows::kAsOthers : LongRows::kGathered;
+}
+
 }  // namespace pamc

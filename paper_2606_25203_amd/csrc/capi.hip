@@ -350,15 +350,26 @@ bool shape_forced() {
   return false;
 }
 
-// Whether a graph sweeps bit-packed (PAMC_BITS = 0: never): the magnitude of
-// its couplings, or 0; see one_magnitude.  hubs: it keeps hubs' fields.
-int32_t takes_bits(int32_t n, const int32_t* rp, const int32_t* J, uint32_t flags, bool potts, bool hubs, bool* both,
-                   int64_t* padded) {
-  *both = false;
+// Whether a graph sweeps bit-packed (PAMC_BITS = 0: never, 1: whatever its
+// rows): the magnitude of its couplings, or 0; see one_magnitude.  hubs: it
+// keeps hubs' fields.  *gathered: not bit-packed, but gathered where it would
+// keep incremental fields (long_row_form).
+int32_t takes_bits(int32_t n, const int32_t* rp, const int32_t* J, uint32_t flags, bool potts, bool hubs, int64_t tiles,
+                   bool* both, int64_t* padded, bool* gathered) {
+  *both = *gathered = false;
   *padded = 0;
   const char* e = getenv("PAMC_BITS");
   if (potts || hubs || (flags & PAMC_FLAG_FIELDS_PUSH) || shape_forced() || (e && atoi(e) == 0)) return 0;
-  return pamc::one_magnitude(n, rp, J, both, padded);
+  const int32_t c = pamc::one_magnitude(n, rp, J, both, padded);
+  if (c == 0 || (e && atoi(e) == 1)) return c;
+  int32_t maxdeg = 0, above64 = 0;
+  for (int32_t v = 0; v < n; ++v) {
+    maxdeg = std::max(maxdeg, rp[v + 1] - rp[v]);
+    above64 += rp[v + 1] - rp[v] > 64;
+  }
+  const pamc::LongRows form = pamc::long_row_form(n, rp[n], maxdeg, above64, tiles);
+  *gathered = form == pamc::LongRows::kGathered;
+  return form == pamc::LongRows::kBits ? c : 0;
 }
 
 // Saturation-degree (DSATUR) colouring: the next vertex is the uncoloured
@@ -499,11 +510,12 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
     hubs.clear();
   }
   // Couplings of one magnitude sweep bit-packed.
-  bool both_signs = false;
+  bool both_signs = false, gathered = false;
   int64_t padded = 0;  // entries of the rows padded to multiples of 4
   if (h.allow_bits) {
-    const int32_t c =
-        takes_bits(n, rp, Jin.data(), flags, h.potts_K != 0, !hubs.empty(), &both_signs, &padded);
+    const int32_t c = takes_bits(n, rp, Jin.data(), flags, h.potts_K != 0, !hubs.empty(), T, &both_signs, &padded,
+                                 &gathered);
+    if (gathered) h.pull = 1;
     if (c > 0) {
       h.bits_ok = 1;
       h.pull = 1;
@@ -593,7 +605,7 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
   }
   if (h.tile == 1 && !h.tile_ok) {  // the rows do not fit: per-class launches
     h.tile = 0;
-    if (!h.bits_ok && !choose_fields(n, rp, flags, false, &hubs)) {  // back to the field storage it would have had
+    if (!h.bits_ok && !gathered && !choose_fields(n, rp, flags, false, &hubs)) {  // back to the field storage it would have had
       h.pull = 0;
       h.grow.clear();
       h.gcol.clear();
@@ -2371,10 +2383,11 @@ int64_t estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pam
   bool pull = choose_fields(n, rp, cfg.flags, false, &hubs);
   const bool tile = takes_tile(np / 4, X, cfg.flags, false);  // (keeps no hubs' fields)
   const int64_t ncls = maxdeg + 1;
-  bool both;
+  bool both, gather = false;
   int64_t padded;
-  bits = bits && takes_bits(n, rp, w, cfg.flags, false, !tile && !hubs.empty(), &both, &padded) > 0;
-  if (bits) pull = true;
+  bits = bits &&
+         takes_bits(n, rp, w, cfg.flags, false, !tile && !hubs.empty(), R / 64, &both, &padded, &gather) > 0;
+  if (bits || gather) pull = true;
   int64_t b = a(4 * (int64_t)(n + 1)) + 2 * a(4 * (nnz + 16));                 // CSR
   if (pull || tile) b += a(4 * (int64_t)(n + 1)) + 2 * a(4 * std::max<int64_t>(gathered, 4));  // gathered CSR
   if (pull && !hubs.empty()) b += a(4 * np * pamc::kMaxHubs) + 2 * a(4 * pamc::kMaxHubs * R);  // hubs

@@ -16,9 +16,13 @@ PROGRAM = r"""
 #include <vector>
 int main() {
   char what;
-  long long a, b, c;
+  long long a, b, c, d;
   while (scanf(" %c %lld %lld %lld", &what, &a, &b, &c) == 4) {
-    if (what == 's') {  // stride of n rows, and the entries with it
+    if (what == 'f') {  // form of n rows, b entries in all, the longest of c, d tiles
+      if (scanf(" %lld", &d) != 1) return 1;
+      for (int above64 : {2, 3}) printf("%d ", (int)pamc::long_row_form(a, b, c, above64, d));
+      printf("\n");
+    } else if (what == 's') {  // stride of n rows, and the entries with it
       const int32_t s = pamc::bit_row_stride(a, b, c);
       printf("%d %lld %d\n", s, (long long)pamc::bit_row_entries(a, s, c), (int)pamc::bit_rows_fit(c));
     } else {  // n rows of b entries each: the entries themselves are not read before the rows are counted
@@ -43,8 +47,8 @@ def ask(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover",
                     "-I", CSRC, str(d / "rows.cpp"), "-o", exe], check=True)
 
-    def run(what, a, b, c):
-        out = subprocess.run([exe], input=f"{what} {a} {b} {c}\n", capture_output=True, text=True, check=True).stdout
+    def run(what, *args):
+        out = subprocess.run([exe], input=" ".join(map(str, (what, *args))) + "\n", capture_output=True, text=True, check=True).stdout
         return [int(x) for x in out.split()]
     return run
 
@@ -73,3 +77,30 @@ def test_rows_that_do_not_fit(ask):
     assert ask("o", 8_400_000, 253, 1)[0] == 0
     assert ask("o", 1_000, 7, 7_000) == [3, 0, 8_000]
     assert ask("o", 1_000, 257, 1)[0] == 0
+
+
+BITS, GATHERED, OTHERS = 0, 1, 2
+
+
+@pytest.mark.parametrize("n,average,longest,tiles,form", [
+    (3000, 4, 128, 1, BITS),          # long rows begin above 128 entries ..
+    (3000, 4, 129, 1, OTHERS),
+    (3000, 16, 128, 1, BITS),
+    (3000, 20, 160, 64, BITS),        # .. and above 8 times the average
+    (20000, 20, 161, 4, GATHERED),
+    (3000, 8, 256, 1, OTHERS),
+    (3000, 8, 256, 4, OTHERS),        # 768,000 spins
+    (3000, 8, 256, 6, GATHERED),      # 1,152,000
+    (3000, 8, 256, 87, GATHERED),     # 16,704,000
+    (3000, 8, 256, 88, BITS),         # 16,896,000
+    (20000, 8, 256, 2, OTHERS),
+    (20000, 8, 256, 3, GATHERED),
+    (8000, 20, 256, 2, BITS),         # 1,024,000
+    (9000, 20, 256, 2, OTHERS),
+    (9000, 20, 256, 3, BITS),
+    (20000, 20, 256, 4, GATHERED),    # 5,120,000
+])
+def test_form_of_long_rows(ask, n, average, longest, tiles, form):
+    got = ask("f", n, average * n, longest, tiles)
+    # one or two rows above 64: never gathered without their fields kept
+    assert got == [OTHERS if form == GATHERED else form, form]

@@ -125,3 +125,38 @@ def test_tuning_at_some_sweeps_keeps_the_choice_for_others(pamc, monkeypatch, sw
     assert launches_of(pamc, forced, 1) == ncls
     for i in (inst, new, forced):
         i.close()
+
+
+def long_rows(n, rows, length, seed):
+    """A ring with `rows` vertices of about `length` neighbours, weights 1."""
+    rng = np.random.default_rng(seed)
+    pairs = {(i, i + 1) for i in range(rows, n - 1)}
+    for k in range(rows):
+        pairs |= {(k, int(v)) for v in rng.choice(np.arange(rows, n), length, replace=False)}
+    u, v = np.array(sorted(pairs)).T
+    return synth.csr_from_edges(n, u, v, np.ones(len(u), np.int32))
+
+
+@pytest.mark.parametrize("n,rows,R,pull,hubs", [
+    (2600, 4, 64, 0, 0),       # incremental fields, as for other magnitudes
+    (2600, 1, 64, 0, 1),       # both field forms
+    (2600, 4, 512, 1, 0),      # gathered
+    (1500, 4, 64, 1, 0),       # a work-group per tile
+])
+def test_rows_far_longer_than_the_others(pamc, n, rows, R, pull, hubs):
+    """Graphs of one magnitude with a few rows of more than 128 entries: the
+    field form they take, and their states in it."""
+    g = long_rows(n, rows, 200, n + rows)
+    print(f"case long rows n={n} rows={rows} R={R}", flush=True)
+    inst = pamc.Instance.csr(g, replicas=R, seed=3)
+    info = inst.info()
+    assert (info.pull, info.hubs) == (pull, hubs)
+    o = oracle.Oracle.sparse(g.n, g.row_ptr, g.col, g.w, R, 3)
+    for beta, k in ((0.2, 1), (0.6, 4), (1.5, 2)):
+        inst.sweep(beta, k)
+        o.sweep(beta, k)
+    kw = dict(beta0=0.2, dbeta=0.1, steps=8, sweeps=3)
+    assert inst.anneal(pamc.schedule(**kw)).best_cut == o.anneal(oracle.default_schedule(**kw)).best_cut
+    for name, a, b in zip(("spins", "fields", "energies", "family"), inst.state(), o.state()):
+        assert np.array_equal(a, b), name
+    inst.close()
