@@ -4,6 +4,8 @@
 #include <stdint.h>
 #include <stdlib.h>
 
+#include <vector>
+
 namespace pamc {
 
 // Longest row of a bit-packed instance: one wavefront walks a row, and the
@@ -51,6 +53,41 @@ inline int32_t one_magnitude(int32_t n, const int32_t* rp, const int32_t* J, boo
     if (J[e] != J[0]) *both = true;
   }
   return c;
+}
+
+// The rows of a graph (rp, col, J: internal ids): an entry is the byte offset of
+// the neighbour's mask in a group of one tile, of its complement along negative
+// couplings where there are both; the higher neighbours come first (the edges
+// of the energy sum), then the lower, then the mask that is always 0 up to a
+// multiple of 4 (with a stride, to the next row).  brows: per vertex (np of
+// them) its bounds, then the table offset of a count of 0, then the number of
+// higher neighbours.
+inline void fill_bit_rows(int32_t n, const int32_t* rp, const int32_t* col, const int32_t* J, bool both,
+                          int32_t maxdeg, int32_t stride, int64_t padded, std::vector<int32_t>& brows,
+                          std::vector<int32_t>& bent) {
+  const int32_t np = (n + 3) & ~3;
+  brows.assign((size_t)np * 4, 0);
+  bent.assign((size_t)bit_row_entries(n, stride, padded), 8 * np);
+  int32_t *bounds = brows.data(), *base = bounds + 2 * (size_t)np, *higher = base + np;
+  int32_t at = 0;
+  for (int32_t v = 0; v < np; ++v) {
+    if (stride) at = v * stride;
+    bounds[2 * v] = bounds[2 * v + 1] = at;
+    if (v >= n) continue;
+    const int32_t e0 = rp[v], deg = rp[v + 1] - e0;
+    int32_t* const row = bent.data() + at;
+    int32_t up = 0, low = deg;
+    for (int32_t e = e0; e < e0 + deg; ++e) {  // (no branch: the order of neighbours is random)
+      const bool above = col[e] > v;
+      low -= !above;
+      row[above ? up : low] = 8 * (col[e] + (both && J[e] < 0 ? np + 1 : 0));
+      up += above;
+    }
+    at += (deg + 3) & ~3;
+    bounds[2 * v + 1] = at;
+    base[v] = 4 * (maxdeg - deg);
+    higher[v] = up;
+  }
 }
 
 // How a graph of couplings of one magnitude keeps its fields when its longest

@@ -207,7 +207,7 @@ pamc_status validate_csr(int32_t n, const int32_t* rp, const int32_t* col, const
       bwd.emplace_back(u, v, w[e]);
     }
   }
-  std::sort(fwd.begin(), fwd.end());
+  if (!std::is_sorted(fwd.begin(), fwd.end())) std::sort(fwd.begin(), fwd.end());
   for (size_t i = 1; i < fwd.size(); ++i)
     if (std::get<0>(fwd[i]) == std::get<0>(fwd[i - 1]) && std::get<1>(fwd[i]) == std::get<1>(fwd[i - 1]))
       return fail(PAMC_ERR_INVALID_ARG, "duplicate edge");
@@ -564,10 +564,19 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
     h.gJ.assign(std::max(h.grow[n], 4), 0);
     for (int32_t iv = 0; iv < n; ++iv) {
       if (is_hub(iv)) continue;
-      int32_t p = h.grow[iv];
-      for (int32_t e = h.rp2[iv]; e < h.rp2[iv + 1]; ++e, ++p) {
-        h.gcol[p] = (h.col2[e] >> 2) * 256 + (h.jmode == 2 ? 0 : (h.col2[e] & 3));
-        h.gJ[p] = h.jmode == 2 ? (int32_t)((uint32_t)(uint8_t)(int8_t)h.J2[e] << (8 * (h.col2[e] & 3))) : h.J2[e];
+      const int32_t *c = h.col2.data() + h.rp2[iv], *w = h.J2.data() + h.rp2[iv];
+      int32_t *gc = h.gcol.data() + h.grow[iv], *gw = h.gJ.data() + h.grow[iv];
+      const int32_t deg = h.rp2[iv + 1] - h.rp2[iv];
+      if (h.jmode == 2) {
+        for (int32_t e = 0; e < deg; ++e) {
+          gc[e] = (c[e] >> 2) * 256;
+          gw[e] = (int32_t)((uint32_t)(uint8_t)(int8_t)w[e] << (8 * (c[e] & 3)));
+        }
+      } else {
+        for (int32_t e = 0; e < deg; ++e) {
+          gc[e] = (c[e] >> 2) * 256 + (c[e] & 3);
+          gw[e] = w[e];
+        }
       }
     }
   }
@@ -625,27 +634,10 @@ pamc_status prepare_sparse(HostSparse& h, int32_t n, const int32_t* rp, const in
     h.bits_from = be && atoi(be) == 1 ? 1 : 0;
     h.bits_ok = h.tile != 2 || h.bits_from;
   }
-  // Rows of the bit-packed sweeps: the higher neighbours first (the energy
-  // sum's edges), padded to multiples of 4 with the mask that is always 0.
   if (h.bits_ok) {
     h.bstride = pamc::bit_row_stride(n, maxdeg, padded);
-    h.brows.assign((size_t)h.np * 4, 0);
-    int32_t *bounds = h.brows.data(), *base = bounds + 2 * (size_t)h.np, *higher = base + h.np;
-    for (int32_t iv = 0; iv < h.np; ++iv) {
-      if (h.bstride) h.bent.resize((size_t)iv * h.bstride, 8 * h.np);
-      bounds[2 * iv] = bounds[2 * iv + 1] = (int32_t)h.bent.size();
-      if (iv >= n) continue;
-      for (int upper = 1; upper >= 0; --upper)
-        for (int32_t e = h.rp2[iv]; e < h.rp2[iv + 1]; ++e)
-          if ((h.col2[e] > iv) == (upper == 1)) {
-            h.bent.push_back(8 * (h.col2[e] + (both_signs && h.J2[e] < 0 ? h.np + 1 : 0)));
-            higher[iv] += upper;
-          }
-      while (h.bent.size() % 4) h.bent.push_back(8 * h.np);
-      bounds[2 * iv + 1] = (int32_t)h.bent.size();
-      base[iv] = 4 * (h.bmaxdeg - (h.rp2[iv + 1] - h.rp2[iv]));
-    }
-    h.bent.resize(pamc::bit_row_entries(n, h.bstride, padded), 8 * h.np);
+    pamc::fill_bit_rows(n, h.rp2.data(), h.col2.data(), h.J2.data(), both_signs, h.bmaxdeg, h.bstride, padded, h.brows,
+                        h.bent);
   }
   // Tiles per wavefront: share the per-vertex scalar work among up to 4
   // tiles while keeping enough work-groups (one quad per wave) to fill the
@@ -2364,10 +2356,13 @@ double now_seconds() {
 // the largest degree + 1.  It is an upper bound of the instance's
 // device_bytes, so admission against it never overruns the budget.  The
 // threshold table has 2X + 1 entries, X = max_v sum_j |w_vj| of this graph.
-// bits: with the bit-packed sweeps' rows where the graph takes them (then no
-// field array either).
-int64_t estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pamc_config& cfg,
-                       const pamc_schedule& sc, bool bits) {
+// bytes_bits: where the graph takes bit-packed sweeps, with their rows (then
+// no field array either).
+struct Estimate {
+  int64_t bytes, bytes_bits;
+};
+Estimate estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pamc_config& cfg,
+                        const pamc_schedule& sc) {
   auto a = [](int64_t bytes) { return (int64_t)piece_bytes((size_t)bytes); };
   const int64_t R = cfg.replicas, np = (n + 3) & ~3, nnz = rp[n];
   int64_t maxdeg = 0, X = 0, gathered = 0;
@@ -2380,35 +2375,40 @@ int64_t estimate_bytes(int32_t n, const int32_t* rp, const int32_t* w, const pam
     X = std::max(X, ab);
   }
   std::vector<int32_t> hubs;
-  bool pull = choose_fields(n, rp, cfg.flags, false, &hubs);
+  const bool stored_pull = choose_fields(n, rp, cfg.flags, false, &hubs);
   const bool tile = takes_tile(np / 4, X, cfg.flags, false);  // (keeps no hubs' fields)
   const int64_t ncls = maxdeg + 1;
   bool both, gather = false;
   int64_t padded;
-  bits = bits &&
-         takes_bits(n, rp, w, cfg.flags, false, !tile && !hubs.empty(), R / 64, &both, &padded, &gather) > 0;
-  if (bits || gather) pull = true;
-  int64_t b = a(4 * (int64_t)(n + 1)) + 2 * a(4 * (nnz + 16));                 // CSR
-  if (pull || tile) b += a(4 * (int64_t)(n + 1)) + 2 * a(4 * std::max<int64_t>(gathered, 4));  // gathered CSR
-  if (pull && !hubs.empty()) b += a(4 * np * pamc::kMaxHubs) + 2 * a(4 * pamc::kMaxHubs * R);  // hubs
-  b += a(4 * (ncls + 1));                                                      // class_ptr
-  b += 2 * (a(R * np) + (pull ? 0 : a(4 * R * np)) + a(8 * R) + a(4 * R));     // two populations
-  b += a(np) + a(4 * (int64_t)n) + a((int64_t)sizeof(pamc::RunState));        // best, ids, run state
-  b += a(4 * (2 * X + 1));                                                     // threshold table
-  b += a(4 * std::max<int64_t>(64, sc.sweeps) * ncls);                        // class orders
-  b += a(4 * R) + a(8 * 512);                                                  // parents, counters
-  if (bits) {
-    const int64_t entries = pamc::bit_row_entries(n, pamc::bit_row_stride(n, maxdeg, padded), padded);
-    b += a(16 * np) + a(4 * entries) + a(8 * (2 * maxdeg + 2)) +
-         a(16 * std::max<int64_t>(64, sc.sweeps) * ncls);
-  }
-  b += 4 * a(8 * (int64_t)std::max(sc.steps, 1)) + a(4 * (int64_t)std::max(sc.steps, 1)) +
-       a(8 * (int64_t)std::max(sc.steps, 1));                                  // trace
-  if (sc.augmented && sc.resample && sc.n_top > 0 && sc.mis_trials > 0) {    // cluster scratch
-    const int64_t t = std::min<int64_t>(sc.n_top, R);
-    b += a(4 * t) + a(t * sc.mis_trials * np) + a(4 * t * sc.mis_trials);
-  }
-  return b;
+  const bool takes =
+      takes_bits(n, rp, w, cfg.flags, false, !tile && !hubs.empty(), R / 64, &both, &padded, &gather) > 0;
+  auto bytes = [&](bool bits, bool pull) {
+    int64_t b = a(4 * (int64_t)(n + 1)) + 2 * a(4 * (nnz + 16));                 // CSR
+    if (pull || tile) b += a(4 * (int64_t)(n + 1)) + 2 * a(4 * std::max<int64_t>(gathered, 4));  // gathered CSR
+    if (pull && !hubs.empty()) b += a(4 * np * pamc::kMaxHubs) + 2 * a(4 * pamc::kMaxHubs * R);  // hubs
+    b += a(4 * (ncls + 1));                                                      // class_ptr
+    b += 2 * (a(R * np) + (pull ? 0 : a(4 * R * np)) + a(8 * R) + a(4 * R));     // two populations
+    b += a(np) + a(4 * (int64_t)n) + a((int64_t)sizeof(pamc::RunState));        // best, ids, run state
+    b += a(4 * (2 * X + 1));                                                     // threshold table
+    b += a(4 * std::max<int64_t>(64, sc.sweeps) * ncls);                        // class orders
+    b += a(4 * R) + a(8 * 512);                                                  // parents, counters
+    if (bits) {
+      const int64_t entries = pamc::bit_row_entries(n, pamc::bit_row_stride(n, maxdeg, padded), padded);
+      b += a(16 * np) + a(4 * entries) + a(8 * (2 * maxdeg + 2)) +
+           a(16 * std::max<int64_t>(64, sc.sweeps) * ncls);
+    }
+    b += 4 * a(8 * (int64_t)std::max(sc.steps, 1)) + a(4 * (int64_t)std::max(sc.steps, 1)) +
+         a(8 * (int64_t)std::max(sc.steps, 1));                                  // trace
+    if (sc.augmented && sc.resample && sc.n_top > 0 && sc.mis_trials > 0) {    // cluster scratch
+      const int64_t t = std::min<int64_t>(sc.n_top, R);
+      b += a(4 * t) + a(t * sc.mis_trials * np) + a(4 * t * sc.mis_trials);
+    }
+    return b;
+  };
+  Estimate est;
+  est.bytes = bytes(false, stored_pull);
+  est.bytes_bits = takes || gather ? bytes(takes, true) : est.bytes;
+  return est;
 }
 
 void server_prepare(ServerPrep& p, uint32_t flags, int32_t T, bool bits) {
@@ -2612,12 +2612,11 @@ pamc_status pamc_server_submit(pamc_server* S, int32_t n, const int32_t* row_ptr
   pamc_status st = check_schedule(&probe, sched);
   if (st) return st;
   pamc_server::Req q;
-  q.est = estimate_bytes(n, row_ptr, w ? w : row_ptr, S->cfg, *sched, false);
-  if (q.est > S->budget) return fail(PAMC_ERR_OUT_OF_MEMORY, "request larger than the server's memory budget");
+  const Estimate est = estimate_bytes(n, row_ptr, w ? w : row_ptr, S->cfg, *sched);
+  if (est.bytes > S->budget) return fail(PAMC_ERR_OUT_OF_MEMORY, "request larger than the server's memory budget");
   // bit-packed where that fits the budget too
-  const int64_t est_bits = estimate_bytes(n, row_ptr, w ? w : row_ptr, S->cfg, *sched, true);
-  const bool bits = est_bits <= S->budget;
-  if (bits) q.est = est_bits;
+  const bool bits = est.bytes_bits <= S->budget;
+  q.est = bits ? est.bytes_bits : est.bytes;
   auto prep = std::make_shared<ServerPrep>();
   prep->n = n;
   prep->objective = objective;

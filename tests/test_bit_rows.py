@@ -5,6 +5,7 @@ apart from those that fit."""
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2606_25203_amd", "csrc")
@@ -21,6 +22,25 @@ int main() {
     if (what == 'f') {  // form of n rows, b entries in all, the longest of c, d tiles
       if (scanf(" %lld", &d) != 1) return 1;
       for (int above64 : {2, 3}) printf("%d ", (int)pamc::long_row_form(a, b, c, above64, d));
+      printf("\n");
+    } else if (what == 'r') {  // rows of a graph of a vertices, b entries; c: couplings of both signs; d: stride or not
+      if (scanf(" %lld", &d) != 1) return 1;
+      std::vector<int32_t> rp(a + 1), col(b), J(b), brows, bent;
+      for (auto* x : {&rp, &col, &J})
+        for (int32_t& y : *x)
+          if (scanf(" %d", &y) != 1) return 1;
+      int32_t maxdeg = 0;
+      int64_t padded = 0;
+      for (long long v = 0; v < a; ++v) {
+        const int32_t deg = rp[v + 1] - rp[v];
+        maxdeg = deg > maxdeg ? deg : maxdeg;
+        padded += (deg + 3) & ~3;
+      }
+      const int32_t stride = d ? (maxdeg + 3) & ~3 : 0;
+      pamc::fill_bit_rows((int32_t)a, rp.data(), col.data(), J.data(), c != 0, maxdeg, stride, padded, brows, bent);
+      printf("%d %zu", stride, brows.size());
+      for (int32_t x : brows) printf(" %d", x);
+      for (int32_t x : bent) printf(" %d", x);
       printf("\n");
     } else if (what == 's') {  // stride of n rows, and the entries with it
       const int32_t s = pamc::bit_row_stride(a, b, c);
@@ -104,3 +124,46 @@ def test_form_of_long_rows(ask, n, average, longest, tiles, form):
     got = ask("f", n, average * n, longest, tiles)
     # one or two rows above 64: never gathered without their fields kept
     assert got == [OTHERS if form == GATHERED else form, form]
+
+
+@pytest.mark.parametrize("stride", [0, 1])
+@pytest.mark.parametrize("both", [0, 1])
+@pytest.mark.parametrize("n,m", [(1, 0), (2, 1), (5, 10), (41, 60), (64, 900)])
+def test_row_entries(ask, n, m, both, stride):
+    """Every row entry by entry: higher neighbours, lower ones, the zero mask."""
+    rng = np.random.default_rng(n + both)
+    pairs = {}
+    while len(pairs) < m:
+        u, v = sorted(int(x) for x in rng.integers(0, n, 2))
+        if u != v:
+            pairs[u, v] = 5 if not both or rng.random() < 0.5 else -5
+    rows = [[] for _ in range(n)]
+    for (u, v), w in pairs.items():
+        rows[u].append((v, w))
+        rows[v].append((u, w))
+    for r in rows:
+        rng.shuffle(r)
+    ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])])
+    flat = [(int(c), int(w)) for r in rows for c, w in r]
+    out = ask("r", n, 2 * m, both, stride, *ptr, *(c for c, _ in flat), *(w for _, w in flat))
+    np4, longest = (n + 3) // 4 * 4, max(len(r) for r in rows)
+    step, size, out = out[0], out[1], out[2:]
+    assert step == (stride and (longest + 3) // 4 * 4) and size == 4 * np4
+    brows, ent = out[:size], out[size:]
+    end = 0
+    for v in range(np4):
+        first, last = brows[2 * v], brows[2 * v + 1]
+        if v >= n:
+            assert first == last
+            continue
+        assert first == (v * step if step else end) and (last - first) % 4 == 0
+        end = last
+        want = [8 * (c + (np4 + 1 if both and w < 0 else 0)) for c, w in ([] if n == 1 else rows[v]) if c > v]
+        below = [8 * (c + (np4 + 1 if both and w < 0 else 0)) for c, w in ([] if n == 1 else rows[v]) if c < v]
+        deg = len(want) + len(below)
+        assert sorted(ent[first:first + len(want)]) == sorted(want)
+        assert sorted(ent[first + len(want):first + deg]) == sorted(below)
+        assert set(ent[first + deg:last]) <= {8 * np4} and last - first - deg < 4
+        assert brows[2 * np4 + v] == 4 * (longest - deg) and brows[3 * np4 + v] == len(want)
+    assert len(ent) >= (np4 * step if step else end) + 16
+    assert set(ent[end:]) == {8 * np4}
