@@ -40,14 +40,6 @@ constexpr int kBitTab = 2 * (2 * kBitsMaxDegree + 2);  // threshold entries, sta
 typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-// a + (bit of this lane in m); m comes from a scalar load (inline asm: no wait
-// states are kept between a vector instruction that writes m and this one).
-__device__ __forceinline__ uint32_t add_bit(uint32_t a, uint64_t m) {
-  uint32_t r;
-  asm("v_addc_co_u32_e64 %0, vcc, %1, 0, %2" : "=v"(r) : "v"(a), "s"(m) : "vcc");
-  return r;
-}
-
 // Lane L of v becomes s.  The intrinsic, not inline asm: the compiler then
 // keeps the wait states between a compare that writes s and this read of it.
 extern "C" __device__ uint32_t llvm_writelane(uint32_t s, uint32_t lane, uint32_t v) __asm("llvm.amdgcn.writelane.i32");
@@ -75,22 +67,58 @@ __device__ __forceinline__ uint64_t mask_of(const typename Masks<G>::type& m, in
     return m[t];
 }
 
-// Adds N masks to the lanes' counts.
+// Adds N masks (1 or 4) to the lanes' counts, an instruction each with the mask
+// as the carry-in; from C the compiler makes one and a half.  It keeps no wait
+// states before inline assembly between a vector instruction that writes a
+// scalar register (a spilled one read back, a compare) and a vector
+// instruction that reads it: the s_nop does, two of them.
+#define PAMC_ADDC(a, m) "v_addc_co_u32_e64 %" #a ", vcc, %" #a ", 0, %" #m "\n\t"
 template <int G, int N>
 __device__ __forceinline__ void count_masks(const typename Masks<G>::type* m, uint32_t (&acc)[G]) {
+  static_assert((N == 1 || N == 4) && (G == 1 || G == 2 || G == 4), "");
+  auto at = [&](int u, int t) { return mask_of<G>(m[u], t); };
+  if constexpr (N == 1 && G == 1) {
+    asm("s_nop 1\n\t" PAMC_ADDC(0, 1) : "+v"(acc[0]) : "s"(at(0, 0)) : "vcc");
+  } else if constexpr (N == 1 && G == 2) {
+    asm("s_nop 1\n\t" PAMC_ADDC(0, 2) PAMC_ADDC(1, 3)
+        : "+v"(acc[0]), "+v"(acc[1])
+        : "s"(at(0, 0)), "s"(at(0, 1))
+        : "vcc");
+  } else if constexpr (N == 1) {
+    asm("s_nop 1\n\t" PAMC_ADDC(0, 4) PAMC_ADDC(1, 5) PAMC_ADDC(2, 6) PAMC_ADDC(3, 7)
+        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+        : "s"(at(0, 0)), "s"(at(0, 1)), "s"(at(0, 2)), "s"(at(0, 3))
+        : "vcc");
+  } else if constexpr (G == 1) {
+    asm("s_nop 1\n\t" PAMC_ADDC(0, 1) PAMC_ADDC(0, 2) PAMC_ADDC(0, 3) PAMC_ADDC(0, 4)
+        : "+v"(acc[0])
+        : "s"(at(0, 0)), "s"(at(1, 0)), "s"(at(2, 0)), "s"(at(3, 0))
+        : "vcc");
+  } else {
 #pragma unroll
-  for (int u = 0; u < N; ++u)
-#pragma unroll
-    for (int t = 0; t < G; ++t) acc[t] = add_bit(acc[t], mask_of<G>(m[u], t));
+    for (int t = 0; t < G; t += 2)
+      asm("s_nop 1\n\t" PAMC_ADDC(0, 2) PAMC_ADDC(1, 3) PAMC_ADDC(0, 4) PAMC_ADDC(1, 5)
+          PAMC_ADDC(0, 6) PAMC_ADDC(1, 7) PAMC_ADDC(0, 8) PAMC_ADDC(1, 9)
+          : "+v"(acc[t]), "+v"(acc[t + 1])
+          : "s"(at(0, t)), "s"(at(0, t + 1)), "s"(at(1, t)), "s"(at(1, t + 1)), "s"(at(2, t)), "s"(at(2, t + 1)),
+            "s"(at(3, t)), "s"(at(3, t + 1))
+          : "vcc");
+  }
 }
+#undef PAMC_ADDC
 
-// N byte offsets of masks in a group of one tile (times G in a group of G).
+// N byte offsets of masks in a group of one tile (times G in a group of G),
+// read at any entry.
 template <int N>
 using Offsets = int32_t __attribute__((ext_vector_type(N)));
+template <int N>
+struct OffsetsAt {
+  typedef int32_t type __attribute__((ext_vector_type(N), aligned(4)));
+};
 
 template <int N>
 __device__ __forceinline__ Offsets<N> load_offsets(const PAMC_CONST int32_t* ent) {
-  return *reinterpret_cast<const PAMC_CONST Offsets<N>*>(ent);
+  return *reinterpret_cast<const PAMC_CONST typename OffsetsAt<N>::type*>(ent);
 }
 
 // Counts of a row's entries e .. e1 - 1, the first N offsets given.  N masks
