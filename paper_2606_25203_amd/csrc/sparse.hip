@@ -2485,21 +2485,30 @@ __global__ void __launch_bounds__(kPairThreads) k_pair_hist(const uint32_t* S0, 
                              __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// In a run with a diversity trace: local block p of an instance sums
-// min(d, n - d) over its tile pair of the population just swept, on the
+__host__ __device__ static inline int32_t pair_tiles(int32_t T) { return T * (T + 1) / 2; }  // tile pairs ta <= tb
+// Work-groups of a sample: a tile pair each, in turns where there are more pairs
+// than replicas (a batch's map has no more entries than that).
+__host__ __device__ static inline int32_t pair_blocks(int32_t T) { return min(pair_tiles(T), T * kLanes); }
+
+// In a run with a diversity trace: local block lb of an instance sums
+// min(d, n - d) over its tile pairs of the population just swept, on the
 // steps the trace samples.
 __global__ void __launch_bounds__(kPairThreads) k_step_dh(const Desc* __restrict__ D,
                                                           const uint64_t* __restrict__ map) {
   __shared__ int32_t dot[64 * 64];
-  int inst, p;
-  if (!resolve(map, inst, p)) return;
+  int inst, lb;
+  if (!resolve(map, inst, lb)) return;
   const Desc& d = D[inst];
   RunState* st = d.st;
   if (!st->active || st->dh_every <= 0 || st->step % st->dh_every != 0) return;
-  int ta, tb;
-  pair_products(st->cur ? d.S1 : d.S0, d.n, d.nq, d.T, p, ta, tb, dot);
+  const int pairs = pair_tiles(d.T), blocks = pair_blocks(d.T);
   int64_t acc = 0;
-  for_pair_distances(dot, d.n, ta, tb, [&](int32_t dh) { acc += dh; });
+  for (int p = lb; p < pairs; p += blocks) {
+    int ta, tb;
+    if (p != lb) __syncthreads();  // the products before are read
+    pair_products(st->cur ? d.S1 : d.S0, d.n, d.nq, d.T, p, ta, tb, dot);
+    for_pair_distances(dot, d.n, ta, tb, [&](int32_t dh) { acc += dh; });
+  }
   acc = wave_sum_i64(acc);
   if ((threadIdx.x & 63) == 0 && acc)
     __hip_atomic_fetch_add((unsigned long long*)&st->dh_sum, (unsigned long long)acc, __ATOMIC_RELAXED,
@@ -2528,7 +2537,6 @@ __global__ void k_step_dh_finish(const Desc* __restrict__ D, int32_t ninst) {
 // ===========================================================================
 int32_t cluster_max_n() { return kClusterMaxN; }
 int32_t sweep_waves() { return kSweepWaves; }
-static inline int32_t pair_tiles(int32_t T) { return T * (T + 1) / 2; }  // tile pairs ta <= tb
 int32_t tile_max_quads() { return kTileMaxQuads; }
 int64_t tile_lds_bytes(int32_t nq, int32_t rows) { return (int64_t)nq * kLanes * 4 + kThrLds * 4 + 8 * (int64_t)rows; }
 int64_t tile_lds_limit() { return kTileLdsBytes; }
@@ -3029,7 +3037,7 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
       bdesc[i] = make_bit_desc(I, desc[i], qw, u);
     }
   }
-  // diversity samples: one work-group per tile pair.  A batch without
+  // diversity samples: pair_blocks work-groups.  A batch without
   // schedules (an instance's own) keeps the map; its runs switch it on.
   b.any_dh = 0;
   for (int i = 0; i < b.n; ++i) {
@@ -3040,7 +3048,7 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
       if (s.dh_every <= 0) continue;
     }
     if (insts[i]->dense || insts[i]->potts_K) continue;
-    add_blocks(m_dh, i, pair_tiles(insts[i]->T), false);
+    add_blocks(m_dh, i, pair_blocks(insts[i]->T), false);
     if (scheds) b.any_dh = 1;
   }
   if (!b.arena && !b.al) {

@@ -74,3 +74,35 @@ def test_same_results_either_way(pamc, monkeypatch, sweeps):
         assert all(np.array_equal(m, n) for m, n in zip(p.state(), q.state()))
         p.close()
         q.close()
+
+
+def test_diversity_samples_of_many_replicas(pamc, monkeypatch):
+    """The largest population's diversity samples: a launch map of at most a
+    word per replica (the scratch is filled by class orders of 8 bytes a sweep,
+    cut in pieces of 256), and the mean of all pairs."""
+    monkeypatch.setenv("PAMC_BITS", "0")
+    R = 16384
+    print("case diversity samples, R = 16384", flush=True)
+    inst = pamc.Instance.csr(synth.torus(6, 4, 1), replicas=R, seed=1)
+
+    def most_sweeps(dh_every):
+        lo, hi = 1, 1 << 22
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            try:
+                pamc.anneal_batch_noalloc([inst], [pamc.schedule(steps=0, sweeps=mid, dh_every=dh_every)])
+                lo = mid
+            except pamc.PamcError as e:
+                assert e.status == pamc.PAMC_ERR_UNSUPPORTED
+                hi = mid
+        return lo
+
+    assert 8 * (most_sweeps(0) - most_sweeps(1)) <= 8 * R + 512
+    inst.anneal(pamc.schedule(beta0=0.1, dbeta=0.2, steps=3, sweeps=2, dh_every=1))
+    dh = pamc.pamc_get_dh_trace(inst.h, 3)
+    assert dh[2] == inst.pair_distance() and 0 < dh[0] <= 0.5
+    s = inst.state()[0].astype(np.int64)
+    d = (s.shape[1] - s[:512] @ s.T) // 2  # of the first 512 replicas to all
+    d = np.minimum(d, s.shape[1] - d).sum() / s.shape[1] / (512 * (R - 1))
+    assert abs(d - dh[2]) < 0.05
+    inst.close()
