@@ -304,7 +304,7 @@ def measure(pamc, torch, name, steps, warmup, fields=None):
     roofline: HIP events bracket each step's sweep launches, the algorithmic
     bytes (or ops) per launch come from the model of the workload's path,
     and the HBM traffic per launch from the committed counter summary."""
-    from paper_2606_25203_amd.profile_kernels import sweep_kernel
+    from paper_2606_25203_amd.profile_kernels import kernel_source, sweep_kernel
 
     w = workload(name)
     inst = make_instance(pamc, w, 0, fields=fields)
@@ -382,15 +382,15 @@ def measure(pamc, torch, name, steps, warmup, fields=None):
         rate = apl / (launch_ms * 1e-3)
         shape = {"tiles_per_wave": info.tiles_per_wave, "quads_per_wave": info.quads_per_wave,
                  "coupling_mode": info.coupling_mode, "tile_sweeps": info.tile_sweeps, "hubs": info.hubs}
-        torus = "torus" in w["counters"]
-        kname = sweep_kernel(info, w["kind"] == "potts", torus)
+        kname = sweep_kernel(info, w["sweeps"])
+        bits = 0 < info.bit_sweeps <= w["sweeps"]
         if w["kind"] == "potts":
             slots = potts_slots_per_attempt(degree, info.potts_K, info.X)
             achieved = slots * rate / 1e12
             roof = {"kernel": kname, "bound": "alu", "achieved": achieved, "peak": VALU_PEAK_TSLOTS,
                     "unit": "T int32 lane-op slots/s", "frac": achieved / VALU_PEAK_TSLOTS,
                     "alu_slots_per_attempt": slots}
-        elif info.tile_sweeps:
+        elif info.tile_sweeps and not bits:
             # one work-group per 64-replica tile holds the tile's spins in
             # LDS for all of a step's sweeps: HBM is idle, and a single
             # instance occupies R/64 compute units; the vector-issue model
@@ -412,7 +412,7 @@ def measure(pamc, torch, name, steps, warmup, fields=None):
                 ops = 2.0 * degree * rate / 1e12  # the sparse product's multiply-adds, not the zero blocks
                 roof["mfma_model"] = {"useful_int8_ops_per_attempt": 2.0 * degree, "achieved_tops": ops,
                                       "peak_tops": MFMA_I8_PEAK_TOPS, "frac": ops / MFMA_I8_PEAK_TOPS}
-        elif torus:
+        elif bits:
             # bit-packed: the masks of a phase are a few megabytes, so the
             # byte model of the other layouts does not apply; vector issue
             slots = bit_slots_per_attempt(degree)
@@ -443,7 +443,7 @@ def measure(pamc, torch, name, steps, warmup, fields=None):
         roof.update({"traffic": None, "launch_ms": launch_ms, "launches": prof["launches"],
                      "attempts_per_launch": apl, "flip_rate": p_flip, "fields": "pull" if pull else "push",
                      "kernel_shape": shape, "attempts_per_s_in_kernel": rate})
-        c = counters(w["counters"], "bits.hip" if torus else "sparse.hip", kname)
+        c = counters(w["counters"], kernel_source(kname), kname)
         if c and "hbm_bytes_per_dispatch" in c:
             # measured bytes per dispatch of the counted sweeps (at the
             # profiling script's temperature), scaled to this run's launches

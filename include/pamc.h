@@ -206,11 +206,15 @@ pamc_status pamc_reset_population(pamc_instance* inst, uint64_t seed);
  * fields computed on the matrix cores as int8 products of 16 x 64 coupling
  * blocks with the spins (n <= 1024, int8 couplings), one work-group per
  * 16-replica group of a tile while the launch has at most 128 tiles, else
- * one per tile (tile_sweeps 1 and couplings of one magnitude: bit-packed
- * instead where a step has enough sweeps, one launch per colour class); hubs:
- * vertices whose fields are kept while the others are gathered. */
+ * one per tile; hubs: vertices whose fields are kept while the others are
+ * gathered.  bit_sweeps: the fewest sweeps of a step or call that are made on
+ * spins packed one bit each instead (couplings of one magnitude, one launch per
+ * colour class; a batch decides for its instances together), 0: none are;
+ * bit_tiles: the tiles whose masks a wavefront then takes together, negative
+ * where the vertices of a quad go to different wavefronts. */
 typedef struct {
   int32_t n, replicas, num_classes, dense, pull;
+  int16_t bit_sweeps, bit_tiles;
   int64_t nnz, W, X; /* X = max_v sum_j |J_vj| */
   int64_t device_bytes;
   int32_t tiles_per_wave, quads_per_wave, coupling_mode;

@@ -1332,6 +1332,10 @@ pamc_status pamc_get_info(const pamc_instance* I, pamc_info* out) {
   out->num_classes = I->ncls;
   out->dense = I->dense;
   out->pull = I->pull;
+  int32_t bit_sweeps, bit_tiles;
+  pamc::bits_info(I, &bit_sweeps, &bit_tiles);
+  out->bit_sweeps = (int16_t)std::min<int32_t>(bit_sweeps, INT16_MAX);
+  out->bit_tiles = (int16_t)bit_tiles;
   out->nnz = I->nnz;
   out->W = I->W;
   out->X = I->X;

@@ -354,6 +354,8 @@ int32_t cluster_max_n();
 // The fewest sweeps per step from which instances without a bits_from of their
 // own sweep bit-packed as one batch.
 int32_t bits_min_sweeps(const std::vector<pamc_instance*>& insts);
+// pamc_info's bit_sweeps (not capped) and bit_tiles.
+void bits_info(const pamc_instance* I, int32_t* sweeps, int32_t* tiles);
 int32_t sweep_waves();  // wavefronts per sweep work-group
 int32_t tile_max_quads();  // vertex quads a tile-resident sweep holds in LDS
 int64_t tile_lds_bytes(int32_t nq, int32_t rows);  // its LDS: spins, table, a class's gathered rows

@@ -2870,6 +2870,38 @@ int32_t bits_min_sweeps(const std::vector<pamc_instance*>& insts) {
   return degree >= 20.0 ? 1 : (degree >= 8.0 ? 2 : 3);
 }
 
+// The form of an instance's bit-packed launches (Batch::kBitForms), quads: quads
+// x tiles of a phase over its batch.
+//
+// Rows of at most four entries: a quad per wave, else a quad per
+// work-group.  A scalar load costs a compute unit about 8 cycles whatever its
+// width, so wide tile groups pay once there are enough quads to go round.
+// Runs timed with groups of 1, 2 and 4 tiles, a quad per wave: torus 60 x 60,
+// R = 512 (3,600 quads x tiles a phase): 1.95, 2.13 and 2.35 ms; R = 4096
+// (28,800): 4.68, 3.95 and 3.71; 100 x 200, R = 4096 (160,000): 200, 107 and 89.
+// A quad per work-group: G(2000, degree 7), R = 256 (500): 2.65, 2.86 and
+// 3.16 ms; G(11999, degree 34), R = 512 (2,000): 37.6, 30.6 and 31.7; G(5000,
+// degree 5), R = 1024 (4,000): 5.78, 4.25 and 3.79.  Quads per wave or
+// work-group, 1 and 2: the last 3.79 and 4.04 ms; G(20000, degree 5), R = 1024
+// (16,000) 8.15 and 7.77; the large torus 90.6 and 89.2 (3: 88.5, 4: 91.1).
+static int bit_form(const pamc_instance* I, int64_t quads) {
+  int f = I->bstride == 4 ? (quads < 8192 ? 3 : 5) : (quads < 1000 ? 0 : (quads < 2500 ? 1 : 2));
+  if (const char* e = getenv("PAMC_BITS_FORM")) f = std::min(5, std::max(0, atoi(e)));
+  if (f >= 3 && I->bstride != 4) f -= 3;
+  while (f % 3 > 0 && I->T % (f % 3 == 2 ? 4 : 2) != 0) --f;
+  return f;
+}
+
+void bits_info(const pamc_instance* I, int32_t* sweeps, int32_t* tiles) {
+  *sweeps = *tiles = 0;
+  if (I->dense || !I->bits_ok) return;
+  const int32_t from = I->bits_from ? I->bits_from : bits_min_sweeps({const_cast<pamc_instance*>(I)});
+  if (from == INT32_MAX) return;
+  const int f = bit_form(I, (int64_t)I->T * I->max_class_quads);
+  *sweeps = from;
+  *tiles = f >= 3 ? 1 << (f - 3) : -(1 << f);
+}
+
 static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts, const std::vector<Schedule>* scheds,
                               bool allow_bits) {
   // the old maps may still be read by queued kernels
@@ -3001,31 +3033,15 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
                      [&](int x, int y) { return insts[x]->ncls > insts[y]->ncls; });
     int64_t quads = 0;  // quads x tiles of a phase, over the batch
     for (int i : bit_insts) quads += (int64_t)insts[i]->T * insts[i]->max_class_quads;
-    // Rows of at most four entries: a quad per wave, else a quad per
-    // work-group.  A scalar load costs a compute unit about 8 cycles whatever its
-    // width, so wide tile groups pay once there are enough quads to go round.
-    // Runs timed with groups of 1, 2 and 4 tiles, a quad per wave: torus 60 x 60,
-    // R = 512 (3,600 quads x tiles a phase): 1.95, 2.13 and 2.35 ms; R = 4096
-    // (28,800): 4.68, 3.95 and 3.71; 100 x 200, R = 4096 (160,000): 200, 107 and 89.
-    // A quad per work-group: G(2000, degree 7), R = 256 (500): 2.65, 2.86 and
-    // 3.16 ms; G(11999, degree 34), R = 512 (2,000): 37.6, 30.6 and 31.7; G(5000,
-    // degree 5), R = 1024 (4,000): 5.78, 4.25 and 3.79.  Quads per wave or
-    // work-group, 1 and 2: the last 3.79 and 4.04 ms; G(20000, degree 5), R = 1024
-    // (16,000) 8.15 and 7.77; the large torus 90.6 and 89.2 (3: 88.5, 4: 91.1).
-    int qpw = 0, form = -1;
-    if (const char* e = getenv("PAMC_BITS_FORM")) form = std::min(5, std::max(0, atoi(e)));
+    int qpw = 0, uq = 0;
     if (const char* e = getenv("PAMC_BITS_QPW")) qpw = std::max(1, atoi(e));
-    int uq = 0;
     if (const char* e = getenv("PAMC_BITS_UQ")) uq = std::max(1, atoi(e));
     for (int i : bit_insts) {
       const pamc_instance* I = insts[i];
-      int f = form, qw = qpw, u = uq;
-      if (f < 0 && I->bstride == 4) f = quads < 8192 ? 3 : 5;
-      if (f < 0) f = quads < 1000 ? 0 : (quads < 2500 ? 1 : 2);
-      if (f >= 3 && I->bstride != 4) f -= 3;
+      const int f = bit_form(I, quads);
+      int qw = qpw, u = uq;
       if (!qw) qw = quads >= (I->bstride == 4 ? 65536 : 12000) ? 2 : 1;
       if (!u) u = I->nq >= 4096 ? 8 : 4;  // G(20000, degree 9), R = 64: 2.24 and 2.03 ms; n = 5,000: 2.05 and 2.11
-      while (f % 3 > 0 && I->T % (f % 3 == 2 ? 4 : 2) != 0) --f;
       const int G = 1 << (f % 3);
       std::vector<uint64_t>& m = m_bits[I->rule * Batch::kBitForms + f];
       std::vector<int32_t>& grid = b.bit_grid[I->rule][f];

@@ -5,11 +5,11 @@
 Each workload builds its instance exactly as the benchmark does, then calls
 only the primitive that launches the kernel of interest, so a counter pass
 sees that kernel (and the small per-call setup kernels) and nothing else:
-  c2   pamc_sweep on the 100 x 200 +-1 torus, R = 4096 (k_sweep_pull)
+  c2   pamc_sweep on the 100 x 200 +-1 torus, R = 4096 (k_sweep_bits_grid)
   c4   pamc_sweep on the Max-3-Cut embedding of G(7000, 21000), R = 2048
        (k_sweep_push, incremental fields)
   c3   pamc_sweep on the dense +-1 n = 100,000 instance, R = 256 (k_dense_*)
-  c1   pamc_sweep on G(800, 19176), R = 256 (k_sweep_tile: all sweeps of a
+  c1   pamc_sweep on G(800, 19176), R = 256 (k_sweep_tmma_g: all sweeps of a
        call in one launch)
   c4p  pamc_sweep on G(7000, 21000) with 3-state Potts labels, R = 2048
        (k_sweep_potts<3>)
@@ -42,25 +42,27 @@ def kernel_source_sha256(src):
     """Hash of one kernel source file and the device headers it includes:
     counters taken on other sources no longer describe the kernels."""
     h = hashlib.sha256()
-    for f in (src, "pamc_device.hpp", "instance.hpp"):
+    for f in (src, "pamc_device.hpp", "instance.hpp", "bit_rows.hpp"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
 
 
-def sweep_kernel(info, potts=False, torus=False):
+def sweep_kernel(info, sweeps, rule=0):
     """The name rocprofv3 gives (up to the argument list) to the kernel that
-    makes an instance's sweeps, from the instance's chosen shape.  torus: a
-    large +-1 torus (rows of four couplings of one magnitude, several sweeps a
-    step), which sweeps bit-packed in groups of four tiles."""
+    makes an instance's sweeps in steps or calls of `sweeps`, from the form and
+    shape the library reports (rule: the update rule it was made with)."""
+    metropolis = "true" if rule == 1 else "false"
     if info.dense:
-        return "k_dense_step<0, 256>" if info.replicas > 128 else "k_dense_step<0, 128>"
-    if torus and info.pull and not info.tile_sweeps:
-        return "k_sweep_bits_grid<4, false>"
-    if potts:
+        replicas = 64 if info.replicas <= 64 else 128 if info.replicas <= 128 else 256
+        return f"k_dense_step<{rule}, {replicas}>"
+    if info.potts_K:
         return f"k_sweep_potts<{info.potts_K}>"
+    if 0 < info.bit_sweeps <= sweeps:
+        form = "quad" if info.bit_tiles < 0 else "grid"
+        return f"k_sweep_bits_{form}<{abs(info.bit_tiles)}, {metropolis}>"
     if info.tile_sweeps == 2:  # one instance (at most 128 tiles): a work-group per 16-replica group
-        return "k_sweep_tmma_g<8>"
+        return "k_sweep_tmma_g<8>" if info.replicas // 64 <= 128 else "k_sweep_tmma<16>"
     if info.tile_sweeps:
         return f"k_sweep_tile<{info.coupling_mode}>"
     if info.pull:
@@ -68,6 +70,11 @@ def sweep_kernel(info, potts=False, torus=False):
         return (f"k_sweep_pull<{info.coupling_mode}, {info.tiles_per_wave}, {wide}, "
                 f"{'true' if info.hubs else 'false'}>")
     return "k_sweep_push"
+
+
+def kernel_source(kernel):
+    """The source file of a sweep kernel."""
+    return "dense.hip" if "dense" in kernel else "bits.hip" if "bits" in kernel else "sparse.hip"
 
 
 def main():
@@ -118,15 +125,15 @@ def main():
     total = args.calls * args.sweeps
     prof = pamc.pamc_profile_read(inst.h) if not args.no_events else \
         {"attempts": total * info.n * info.replicas, "flips": -1, "launches": -1, "ms": -1.0}
+    kernel = sweep_kernel(info, args.sweeps)
     out = {"workload": args.workload, "n": info.n, "replicas": info.replicas, "beta": beta,
            "sweeps": total, "sweeps_per_call": args.sweeps, "attempts": prof["attempts"], "flips": prof["flips"],
            "flip_rate": prof["flips"] / max(prof["attempts"], 1), "launches": prof["launches"],
            "kernel_ms": prof["ms"], "wall_s": wall, "pull": info.pull, "nnz": info.nnz,
            "tiles_per_wave": info.tiles_per_wave, "quads_per_wave": info.quads_per_wave,
            "coupling_mode": info.coupling_mode, "tile_sweeps": info.tile_sweeps, "hubs": info.hubs,
-           "kernel": sweep_kernel(info, args.workload == "c4p", args.workload == "c2"), "settle_gap_s": SETTLE_GAP_S,
-           "source_sha256": kernel_source_sha256("dense.hip" if info.dense else
-                                               "bits.hip" if args.workload == "c2" else "sparse.hip")}
+           "kernel": kernel, "settle_gap_s": SETTLE_GAP_S,
+           "source_sha256": kernel_source_sha256(kernel_source(kernel))}
     inst.close()
     print(json.dumps(out), flush=True)
     if args.facts_out:

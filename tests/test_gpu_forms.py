@@ -160,3 +160,28 @@ def test_rows_far_longer_than_the_others(pamc, n, rows, R, pull, hubs):
     for name, a, b in zip(("spins", "fields", "energies", "family"), inst.state(), o.state()):
         assert np.array_equal(a, b), name
     inst.close()
+
+
+def test_reported_form_is_the_one_launched(pamc, monkeypatch):
+    """bit_sweeps tells from how many sweeps on a step of a small graph is no
+    longer one launch; graphs that never pack report 0."""
+    g = synth.random_graph(620, 2170, 3)
+    inst = pamc.Instance.csr(g, replicas=256, seed=1)
+    info = inst.info()
+    print("case reported form", info.bit_sweeps, info.bit_tiles, flush=True)
+    assert 1 < info.bit_sweeps < 40 and info.bit_tiles != 0 and info.tile_sweeps == 1
+    for k in (info.bit_sweeps - 1, info.bit_sweeps):
+        assert launches_of(pamc, inst, k) == (k * info.num_classes if k >= info.bit_sweeps else 1)
+    inst.close()
+    others = [pamc.Instance.csr(synth.random_graph(300, 2400, 5), replicas=128, seed=1),     # matrix-core tiles
+              pamc.Instance.csr(synth.torus(50, 48, 5), replicas=128, seed=1, fields="push"),
+              pamc.Instance.potts(synth.random_graph(300, 600, 1), 3, replicas=64, seed=1),
+              pamc.Instance.dense_random(100, 1, replicas=64, seed=1)]
+    monkeypatch.setenv("PAMC_BITS", "0")
+    others.append(pamc.Instance.csr(g, replicas=256, seed=1))
+    assert [(i.info().bit_sweeps, i.info().bit_tiles) for i in others] == [(0, 0)] * 5
+    monkeypatch.setenv("PAMC_BITS", "1")
+    forced = pamc.Instance.csr(synth.torus(100, 200, 1), replicas=4096, seed=1)
+    assert (forced.info().bit_sweeps, forced.info().bit_tiles) == (1, 4)
+    for i in others + [forced]:
+        i.close()
