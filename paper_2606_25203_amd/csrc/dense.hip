@@ -126,10 +126,9 @@ __global__ void __launch_bounds__(256) k_dense_init_spins(int8_t* S, int32_t* fa
 // by 16 bytes against bank conflicts).  Operand fragments: lane l
 // supplies 16 consecutive K bytes at 16*(l/16) of row (A) / replica (B) l %
 // 16; the result holds rows 4*(l/16)..+3 of column l % 16.
-// The product runs over a K domain given as columns kbase .. kbase + kcount
-// + xlen with the xlen columns from kbase + x0 left out (x0, xlen, kbase and
-// kcount multiples of 64): compacted column k maps to kbase + k, plus xlen
-// once k >= x0.
+// The product runs over the columns 0 .. kcount + xlen with the xlen columns
+// from x0 left out (x0, xlen and kcount multiples of 64): compacted column k
+// maps to k, plus xlen once k >= x0.
 struct GemmArgs {
   const int8_t* J;
   const int8_t* S0;
@@ -137,7 +136,7 @@ struct GemmArgs {
   int32_t* G;
   const RunState* st;
   int32_t row0, rows, np, R, use_state, kslice;
-  int32_t kbase, kcount, x0, xlen;
+  int32_t kcount, x0, xlen;
 };
 
 //
@@ -177,7 +176,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& g, int bid, GemmLds<NT
   const int steps = (k_end - k_beg) / 64, nst = (steps + 1) / 2;
   auto column = [&](int step) {  // of a step of the slice, clamped to its last
     const int kc = k_beg + 64 * min(step, steps - 1);
-    return g.kbase + kc + (kc >= g.x0 ? g.xlen : 0);
+    return kc + (kc >= g.x0 ? g.xlen : 0);
   };
   // A: the wave's row blocks (past the super-block: the last one again, its
   // results are dropped below)
@@ -912,14 +911,14 @@ static inline GemmShape gemm_shape(const pamc_instance* I, int rows, int kcount)
   return {tiles * ((slices + 7) / 8) * 8, kslice};
 }
 
-// Field product G = J[row0 .. row0 + rows) . S over the K domain (kbase,
-// kcount, x0, xlen; see GemmArgs), and its grid.
+// Field product G = J[row0 .. row0 + rows) . S over the K domain (kcount, x0,
+// xlen; see GemmArgs), and its grid.
 struct GemmLaunch {
   GemmArgs g;
   int grid;
 };
 static GemmLaunch gemm_launch(const pamc_instance* I, int32_t row0, int32_t rows, int32_t use_state, int32_t* G,
-                              int32_t kbase, int32_t kcount, int32_t x0, int32_t xlen) {
+                              int32_t kcount, int32_t x0, int32_t xlen) {
   const GemmShape gsh = gemm_shape(I, rows, kcount);
   GemmArgs g;
   g.J = I->Jd;
@@ -933,7 +932,6 @@ static GemmLaunch gemm_launch(const pamc_instance* I, int32_t row0, int32_t rows
   g.R = I->R;
   g.use_state = use_state;
   g.kslice = gsh.kslice;
-  g.kbase = kbase;
   g.kcount = kcount;
   g.x0 = x0;
   g.xlen = xlen;
@@ -947,7 +945,7 @@ static void launch_gemm(const pamc_instance* I, const GemmLaunch& gl) {
   }
 }
 static GemmLaunch gemm_full(const pamc_instance* I, int32_t row0, int32_t rows, int32_t use_state, int32_t* G) {
-  return gemm_launch(I, row0, rows, use_state, G, 0, I->dn_pad, I->dn_pad, 0);
+  return gemm_launch(I, row0, rows, use_state, G, I->dn_pad, I->dn_pad, 0);
 }
 
 static hipError_t dense_full_energy(pamc_instance* I, int buf) {
@@ -1044,7 +1042,7 @@ static hipError_t dense_sweeps(Batch& b, int32_t nsweeps) {
       GemmLaunch nx{};
       if (next) {
         const int n0 = row0 + kSB;
-        nx = gemm_launch(I, n0, sb_rows(I, n0), 1, gbuf(i + 1), 0, I->dn_pad - rows, row0, rows);
+        nx = gemm_launch(I, n0, sb_rows(I, n0), 1, gbuf(i + 1), I->dn_pad - rows, row0, rows);
       }
       step<<<NG + (next ? nx.grid : 0), kDenseThreads, 0, I->stream>>>(a, nx.g, s, row0, rows, NG, next ? 1 : 0);
       if (I->prof) {

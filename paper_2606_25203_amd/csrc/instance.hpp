@@ -368,7 +368,7 @@ hipError_t prepare_kernel_lds();
 // Work-groups per tile group of a launch over that many quads, each taking
 // qpw (quad_per_block) or 4 qpw of them.
 int32_t bits_work_groups(int32_t quads, int32_t qpw, bool quad_per_block);
-int32_t bits_pack_chunks(int32_t nq);                  // pack and unpack work-groups per tile group
+int32_t bits_pack_chunks(int32_t nq);                  // pack work-groups per tile group
 void launch_bits_sweep(int rule, int form, const BitLaunch& b, int grid, int sweep, int phase, hipStream_t s);
 void launch_bits_pack(int form, const BitLaunch& b, int grid, bool pack, hipStream_t s);
 

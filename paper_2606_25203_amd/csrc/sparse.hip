@@ -2881,9 +2881,7 @@ int32_t bits_min_sweeps(const std::vector<pamc_instance*>& insts) {
 // (28,800): 4.68, 3.95 and 3.71; 100 x 200, R = 4096 (160,000): 200, 107 and 89.
 // A quad per work-group: G(2000, degree 7), R = 256 (500): 2.65, 2.86 and
 // 3.16 ms; G(11999, degree 34), R = 512 (2,000): 37.6, 30.6 and 31.7; G(5000,
-// degree 5), R = 1024 (4,000): 5.78, 4.25 and 3.79.  Quads per wave or
-// work-group, 1 and 2: the last 3.79 and 4.04 ms; G(20000, degree 5), R = 1024
-// (16,000) 8.15 and 7.77; the large torus 90.6 and 89.2 (3: 88.5, 4: 91.1).
+// degree 5), R = 1024 (4,000): 5.78, 4.25 and 3.79.
 static int bit_form(const pamc_instance* I, int64_t quads) {
   int f = I->bstride == 4 ? (quads < 8192 ? 3 : 5) : (quads < 1000 ? 0 : (quads < 2500 ? 1 : 2));
   if (const char* e = getenv("PAMC_BITS_FORM")) f = std::min(5, std::max(0, atoi(e)));
@@ -3033,6 +3031,10 @@ static hipError_t build_batch(Batch& b, const std::vector<pamc_instance*>& insts
                      [&](int x, int y) { return insts[x]->ncls > insts[y]->ncls; });
     int64_t quads = 0;  // quads x tiles of a phase, over the batch
     for (int i : bit_insts) quads += (int64_t)insts[i]->T * insts[i]->max_class_quads;
+    // Quads per wave or work-group, 1 and 2: G(5000, degree 5), R = 1024 (4,000
+    // quads x tiles a phase) 3.79 and 4.04 ms; G(20000, degree 5), R = 1024 (16,000)
+    // 8.15 and 7.77; torus 100 x 200, R = 4096 (160,000) 90.6 and 89.2 (3: 88.5, 4:
+    // 91.1).
     int qpw = 0, uq = 0;
     if (const char* e = getenv("PAMC_BITS_QPW")) qpw = std::max(1, atoi(e));
     if (const char* e = getenv("PAMC_BITS_UQ")) uq = std::max(1, atoi(e));
