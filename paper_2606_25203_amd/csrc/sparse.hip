@@ -45,6 +45,7 @@ constexpr int kFieldBlocks = 1024;         // max field-init work-groups per ins
 constexpr uint32_t kIdle = 0xFFFFFFFFu;    // padding block: returns at once
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));  // at any entry
+typedef int i32x8u __attribute__((ext_vector_type(8), aligned(4)));
 constexpr int kBufferWord3 = 0x00020000;   // buffer resource word 3: 32-bit raw data
 
 // Map word: instance index in the high half, local block in the low half.
@@ -928,48 +929,57 @@ __device__ __forceinline__ void sweep_push_body(const PAMC_CONST int32_t* __rest
       uint32_t sw = swq[i];
       const u32x4 rnd = philox10((uint32_t)q, gs, r, kTagSweep, d.k0, d.k1);
       const int32_t (&hq)[4] = hqq[i];
-      bool dirty = false;
+      uint32_t flips = 0;  // bit k: vertex k of the quad
+      int32_t x[4];
+      uint32_t T[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = (int32_t)(int8_t)(sw >> (8 * k)) * hq[k];
+      // The four thresholds together, of vertices outside the class too: a
+      // choice of table for each with its wait cost 0.7 us a launch (Max-3-Cut
+      // embedding of G(7000, 21000), R = 2,048, at beta 2 and 4: 15.4 and 14.2 us;
+      // 14.7 and 13.4 so).
+      if (thr_lds) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) T[k] = thr_s[min(max(x[k], -Xt), Xt) + Xt];
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) T[k] = thr_g[min(max(x[k], -Xt), Xt) + Xt];
+      }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int v = 4 * q + k;
         if (v < v0 || v >= v1) continue;
-        const int32_t h = hq[k];
-        const int32_t s = (int32_t)(int8_t)(sw >> (8 * k));
-        const int32_t x = s * h;
-        const int32_t xi = x < -Xt ? -Xt : (x > Xt ? Xt : x);
-        const uint32_t T = thr_lds ? thr_s[xi + Xt] : thr_g[xi + Xt];
-        const bool flip = (rule == 1 && x <= 0) || (pick(rnd, k) < T);
-        const int32_t snew = -s;
+        const bool flip = (rule == 1 && x[k] <= 0) || (pick(rnd, k) < T[k]);
         if (flip) {
-          dE += 2 * (int64_t)x;
+          dE += 2 * (int64_t)x[k];
           sw ^= (0xFEu << (8 * k));
-          dirty = true;
+          flips |= 1u << k;
           ++nflip;
         }
-        if (__ballot(flip)) {
-          const int e0 = row_ptr[v], e1 = row_ptr[v + 1];
-          const int32_t dd = 2 * snew;
-          // eight entries at a time (the arrays have room past the last): the
-          // reads of them, not the additions, are waited for
-          for (int e = e0; e < e1; e += 8) {
-            int j[8];
-            int32_t c[8];
+      }
+      // the flipped vertices' rows
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              j[u] = col[e + u];
-              c[u] = Jc[e + u];
-            }
-            if (flip) {
+      for (int k = 0; k < 4; ++k) {
+        const bool flip = flips >> k & 1u;
+        if (!__ballot(flip)) continue;
+        const int v = 4 * q + k;
+        const int e0 = row_ptr[v], e1 = row_ptr[v + 1];
+        const int32_t dd = 2 * (int32_t)(int8_t)(sw >> (8 * k));  // twice the new spin
+        // eight entries at a time (the arrays have room past the last): the
+        // reads of them, not the additions, are waited for
+        for (int e = e0; e < e1; e += 8) {
+          const i32x8u j = *reinterpret_cast<const PAMC_CONST i32x8u*>(col + e);
+          const i32x8u c = *reinterpret_cast<const PAMC_CONST i32x8u*>(Jc + e);
+          if (flip) {
 #pragma unroll
-              for (int u = 0; u < 8; ++u)
-                if (e + u < e1)
-                  __hip_atomic_fetch_add(&H[(hbase + j[u]) * kLanes + lane], c[u] * dd, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
-            }
+            for (int u = 0; u < 8; ++u)
+              if (e + u < e1)
+                __hip_atomic_fetch_add(&H[(hbase + j[u]) * kLanes + lane], c[u] * dd, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
           }
         }
       }
-      if (dirty) S[sidx] = sw;
+      if (flips) S[sidx] = sw;
     }
   }
   red[wave][lane] = dE;
