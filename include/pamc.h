@@ -72,10 +72,12 @@ typedef enum { PAMC_MEM_HOST = 0, PAMC_MEM_DEVICE = 1 } pamc_mem;
  * every decision and the trajectory, are the same; the default picks PULL
  * when the average degree is at most 16 and no vertex has more than 64
  * neighbours, and when all couplings have one magnitude and no vertex has
- * more than 256 neighbours: such instances (and with the PULL flag too)
- * sweep with their spins packed one bit each.  PULL with at most two longer rows ("hubs") keeps the hubs'
- * fields.  With neither flag, a graph whose only long rows are one or two
- * hubs keeps both forms: pamc_anneal and pamc_anneal_batch sweep with PULL
+ * more than 256 neighbours (a few rows far longer than the others excepted,
+ * by population size): such instances (and with the PULL flag too) make the
+ * sweeps of a step that has enough of them with their spins packed one bit
+ * each (pamc_get_info's bit_sweeps).  PULL with at most two longer rows
+ * ("hubs") keeps the hubs' fields.  With neither flag, a graph whose only
+ * long rows are one or two hubs keeps both forms: pamc_anneal and pamc_anneal_batch sweep with PULL
  * while the scheduled beta is below 0.8 and with PUSH after, recomputing
  * the fields at the switch (pamc_get_info reports the form in use, PUSH
  * between runs). */

@@ -13,6 +13,8 @@ sees that kernel (and the small per-call setup kernels) and nothing else:
        call in one launch)
   c4p  pamc_sweep on G(7000, 21000) with 3-state Potts labels, R = 2048
        (k_sweep_potts<3>)
+  pairs  pamc_pair_distance_hist on the 100 x 200 +-1 torus, R = 1024
+       (k_pair_hist); its "attempts" are replica pairs
 Before the counted sweeps the population is brought to the inverse
 temperature the workload's runs spend most sweeps near, so flip rates (and
 hence bytes) are representative; then the script idles for a second, a gap
@@ -79,7 +81,7 @@ def kernel_source(kernel):
 
 def main():
     ap = argparse.ArgumentParser()
-    ap.add_argument("--workload", default="c2", choices=["c1", "c2", "c3", "c4", "c4p"])
+    ap.add_argument("--workload", default="c2", choices=["c1", "c2", "c3", "c4", "c4p", "pairs"])
     ap.add_argument("--facts-out", default=None, help="also write the JSON line to this file")
     ap.add_argument("--sweeps", type=int, default=20, help="sweeps per call")
     ap.add_argument("--calls", type=int, default=1, help="counted calls of the sweep primitive")
@@ -93,6 +95,9 @@ def main():
 
     if args.workload == "c2":
         inst = pamc.Instance.csr(synth.torus(100, 200, seed=1), replicas=4096, seed=0)
+        beta = 2.0
+    elif args.workload == "pairs":
+        inst = pamc.Instance.csr(synth.torus(100, 200, seed=1), replicas=1024, seed=0)
         beta = 2.0
     elif args.workload == "c4":
         inst = pamc.Instance.max3cut(synth.random_graph(7000, 21000, seed=1), replicas=2048, seed=0)
@@ -113,25 +118,35 @@ def main():
     inst.sweep(beta, 5)  # settle at beta (not counted in the summary below)
     inst.synchronize()
     time.sleep(SETTLE_GAP_S)
-    if not args.no_events:
+    pairs = args.workload == "pairs"
+    if not args.no_events and not pairs:
         pamc.pamc_profile_enable(inst.h, True)
     print(f"profile_kernels: {args.workload} n={info.n} R={info.replicas} beta={beta:.4g}, "
           f"{args.calls} x {args.sweeps} sweeps", file=sys.stderr, flush=True)
     t0 = time.perf_counter()
     for _ in range(args.calls):
-        inst.sweep(beta, args.sweeps)
+        if pairs:
+            inst.pair_distance_hist(64)
+        else:
+            inst.sweep(beta, args.sweeps)
     inst.synchronize()
     wall = time.perf_counter() - t0
     total = args.calls * args.sweeps
-    prof = pamc.pamc_profile_read(inst.h) if not args.no_events else \
-        {"attempts": total * info.n * info.replicas, "flips": -1, "launches": -1, "ms": -1.0}
-    kernel = sweep_kernel(info, args.sweeps)
+    if pairs:
+        prof = {"attempts": args.calls * info.replicas * (info.replicas - 1) // 2, "flips": -1, "launches": args.calls,
+                "ms": -1.0}
+    elif args.no_events:
+        prof = {"attempts": total * info.n * info.replicas, "flips": -1, "launches": -1, "ms": -1.0}
+    else:
+        prof = pamc.pamc_profile_read(inst.h)
+    kernel = "k_pair_hist" if pairs else sweep_kernel(info, args.sweeps)
     out = {"workload": args.workload, "n": info.n, "replicas": info.replicas, "beta": beta,
            "sweeps": total, "sweeps_per_call": args.sweeps, "attempts": prof["attempts"], "flips": prof["flips"],
            "flip_rate": prof["flips"] / max(prof["attempts"], 1), "launches": prof["launches"],
            "kernel_ms": prof["ms"], "wall_s": wall, "pull": info.pull, "nnz": info.nnz,
            "tiles_per_wave": info.tiles_per_wave, "quads_per_wave": info.quads_per_wave,
            "coupling_mode": info.coupling_mode, "tile_sweeps": info.tile_sweeps, "hubs": info.hubs,
+           "bit_sweeps": info.bit_sweeps, "bit_tiles": info.bit_tiles,
            "kernel": kernel, "settle_gap_s": SETTLE_GAP_S,
            "source_sha256": kernel_source_sha256(kernel_source(kernel))}
     inst.close()
